@@ -6,9 +6,19 @@
 // BF16 operands, FP32 accumulation.  Bias, GELU, loss and Adam are FP32 on
 // FP32 master weights.  Every product is written as one "NT" form,
 //     C[m][n] = sum_k A[m][k] B[n][k]      (both operands K-contiguous),
-// so each lane loads its 8-element MFMA fragment with one 16-byte load.  The
-// backward products need transposed operands; the epilogues that produce
-// activations and gradients therefore also write transposed BF16 copies.
+// so each lane takes its 8-element MFMA fragment with one 16-byte load.
+//
+// The network is small (76,832 parameters), so a step is bound by the chain
+// of its launches, not by its 0.12 GFLOP at a batch of 256.  A training step
+// is two launches: k_mlp_rows takes 16 rows of the batch through the whole
+// forward and backward pass (every product of it is local to the rows;
+// activations pass between the layers in LDS) and k_mlp_update forms the
+// weight gradients over the batch, each 16 x 16 tile by one wavefront, and
+// takes the Adam step on them where they are.  Measured at a batch of 256:
+// 22.4 us a step, against 98 us for 15 launches of one product or
+// elementwise pass each.  Every product adds its K chunks of 32 in ascending
+// order and every bias sum its rows in a fixed order, whatever the batch is
+// split into.
 //
 // GELU is the exact form 0.5 z (1 + erf(z / sqrt 2)), derivative
 // Phi(z) + z phi(z).
@@ -38,97 +48,6 @@ __device__ inline float gelu_grad(float z) {
   return 0.5f * (1.0f + erff(z * 0.70710678118654752f)) + z * 0.39894228040143268f * expf(-0.5f * z * z);
 }
 
-enum { EPI_STORE = 0, EPI_BIAS_GELU = 1, EPI_BIAS = 2, EPI_DGELU = 3 };
-
-struct Epi {
-  const float* bias;  // [N]
-  float* f32;         // [M][ld_f32]: result (STORE/BIAS), pre-activation (BIAS_GELU), dz (DGELU)
-  int ld_f32;
-  bf16_t* bf;         // [M][ld_bf]: activation / dz in BF16 (may be null)
-  int ld_bf;
-  bf16_t* bft;        // [N][ld_bft]: transposed BF16 copy (may be null)
-  int ld_bft;
-  const float* z;     // [M][ld_z]: pre-activation for DGELU
-  int ld_z;
-};
-
-// One block = 4 waves = a 64 x 64 tile of C; each wave a 32 x 32 sub-tile
-// of 2 x 2 MFMA 16 x 16 blocks.  K must be a multiple of 32; rows of A or B
-// beyond M or N read as zero and outputs beyond M or N are not written.
-// MFMA 16x16x32 fragments: lane l holds A[l%16][8(l/16) .. 8(l/16)+7] and
-// B[8(l/16) .. +7][l%16]; the 16 x 16 result leaves D[4(l/16)+t][l%16],
-// t = 0..3, in lane l.
-template <int EPI>
-__global__ __launch_bounds__(256) void k_gemm_nt(int M, int N, int K, const bf16_t* __restrict__ A, int lda,
-                                                 const bf16_t* __restrict__ B, int ldb, Epi ep) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int m0 = blockIdx.y * 64 + (wave >> 1) * 32;
-  const int n0 = blockIdx.x * 64 + (wave & 1) * 32;
-  const int r = lane & 15, kq = (lane >> 4) * 8;
-  f32x4 acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = (f32x4)0.0f;
-  for (int k0 = 0; k0 < K; k0 += 32) {
-    bf16x8 a[2], b[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int row = m0 + 16 * i + r;
-      a[i] = row < M ? *(const bf16x8*)(A + (int64_t)row * lda + k0 + kq) : (bf16x8)0.0f;
-      const int col = n0 + 16 * i + r;
-      b[i] = col < N ? *(const bf16x8*)(B + (int64_t)col * ldb + k0 + kq) : (bf16x8)0.0f;
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-  }
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int m = m0 + 16 * i + 4 * (lane >> 4) + t;
-        const int n = n0 + 16 * j + (lane & 15);
-        if (m >= M || n >= N) continue;
-        float v = acc[i][j][t];
-        if (EPI == EPI_STORE) {
-          ep.f32[(int64_t)m * ep.ld_f32 + n] = v;
-        } else if (EPI == EPI_BIAS) {
-          ep.f32[(int64_t)m * ep.ld_f32 + n] = v + ep.bias[n];
-        } else if (EPI == EPI_BIAS_GELU) {
-          const float z = v + ep.bias[n];
-          ep.f32[(int64_t)m * ep.ld_f32 + n] = z;
-          const bf16_t h = to_bf16(gelu(z));
-          if (ep.bf) ep.bf[(int64_t)m * ep.ld_bf + n] = h;
-          if (ep.bft) ep.bft[(int64_t)n * ep.ld_bft + m] = h;
-        } else {  // EPI_DGELU
-          const float dz = v * gelu_grad(ep.z[(int64_t)m * ep.ld_z + n]);
-          ep.f32[(int64_t)m * ep.ld_f32 + n] = dz;
-          const bf16_t h = to_bf16(dz);
-          if (ep.bf) ep.bf[(int64_t)m * ep.ld_bf + n] = h;
-          if (ep.bft) ep.bft[(int64_t)n * ep.ld_bft + m] = h;
-        }
-      }
-}
-
-// Input rows: X[b] = xi[idx ? idx[b] : b] padded with zeros to 32 columns,
-// in BF16, plain and transposed; targets gathered likewise (FP32).
-__global__ void k_mlp_input(int B, const float* __restrict__ xi, const float* __restrict__ tgt,
-                            const int32_t* __restrict__ idx, bf16_t* __restrict__ xb, bf16_t* __restrict__ xbt,
-                            float* __restrict__ tb) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= B * kInPad) return;
-  const int b = t / kInPad, k = t % kInPad;
-  const int src = idx ? idx[b] : b;
-  const bf16_t v = k < kIn ? to_bf16(xi[(int64_t)src * kIn + k]) : (bf16_t)0;
-  xb[(int64_t)b * kInPad + k] = v;
-  xbt[(int64_t)k * B + b] = v;
-  if (tgt) tb[(int64_t)b * kOut + k] = tgt[(int64_t)src * kOut + k];  // kOut == kInPad
-}
-
 // BF16 copies of the weights: W1 [256][32] (K padded), W2 and W2^T, W3 and W3^T.
 __global__ void k_mlp_weights(const float* __restrict__ p, bf16_t* __restrict__ w1, bf16_t* __restrict__ w2,
                               bf16_t* __restrict__ w2t, bf16_t* __restrict__ w3, bf16_t* __restrict__ w3t) {
@@ -151,99 +70,344 @@ __global__ void k_mlp_weights(const float* __restrict__ p, bf16_t* __restrict__ 
   }
 }
 
-// dY = 2 (Y - T) / (B * 32), plain BF16 and transposed BF16 copies; one
-// block accumulates the mean squared error in a fixed order.
-__global__ __launch_bounds__(256) void k_mse(int B, const float* __restrict__ y, const float* __restrict__ t,
-                                             float* __restrict__ dy, bf16_t* __restrict__ dyb,
-                                             bf16_t* __restrict__ dybt, float* __restrict__ loss) {
-  __shared__ double red[256];
-  const int total = B * kOut;
-  const float sc = 2.0f / (float)total;
-  double acc = 0.0;
-  for (int i = threadIdx.x; i < total; i += blockDim.x) {
-    const float d = y[i] - t[i];
-    acc += (double)d * (double)d;
-    const float g = sc * d;
-    dy[i] = g;
-    const bf16_t h = to_bf16(g);
-    dyb[i] = h;
-    const int b = i / kOut, n = i % kOut;
-    dybt[(int64_t)n * B + b] = h;
-  }
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0 && loss) *loss = (float)(red[0] / total);
-}
-
-// Column sums of an FP32 [M][N] matrix (bias gradients), fixed order.
-// out[n] = sum over m of a[m][n]: a block of 256 threads covers 64 columns,
-// four thread groups take interleaved rows with four running sums each, and
-// the sixteen partial sums of a column are added in a fixed order.
-__global__ __launch_bounds__(256) void k_colsum(int M, int N, const float* __restrict__ a, float* __restrict__ out) {
-  __shared__ float part[4][64];
-  const int col = blockIdx.x * 64 + (threadIdx.x & 63);
-  const int g = threadIdx.x >> 6;
-  float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, s3 = 0.0f;
-  if (col < N) {
-    int m = g;
-    for (; m + 12 < M; m += 16) {
-      s0 += a[(int64_t)m * N + col];
-      s1 += a[(int64_t)(m + 4) * N + col];
-      s2 += a[(int64_t)(m + 8) * N + col];
-      s3 += a[(int64_t)(m + 12) * N + col];
-    }
-    for (; m < M; m += 4) s0 += a[(int64_t)m * N + col];
-  }
-  part[g][threadIdx.x & 63] = (s0 + s1) + (s2 + s3);
-  __syncthreads();
-  if (g == 0 && col < N) out[col] = (part[0][threadIdx.x] + part[1][threadIdx.x]) + (part[2][threadIdx.x] + part[3][threadIdx.x]);
-}
-
 // One Adam step (Kingma and Ba 2015, Algorithm 1) per element, FP32:
 // moving averages of g and g^2, divided by the bias corrections c1 = 1 - b1^t
 // and c2 = 1 - b2^t, eps added to the square root of the second moment.
 // omb1 = 1 - b1 and omb2 = 1 - b2 come in as arguments, each the FP32
 // rounding of the exact value (1.0f - 0.999f would carry the 1.3e-5 relative
 // error of 0.999f into every second moment).
-__global__ void k_adam(int64_t P, float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
-                       float* __restrict__ v, float lr, float b1, float b2, float omb1, float omb2, float eps,
-                       float c1, float c2) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= P) return;
-  const float gi = g[i];
-  const float mi = b1 * m[i] + omb1 * gi;
-  const float vi = b2 * v[i] + omb2 * gi * gi;
-  m[i] = mi;
-  v[i] = vi;
-  p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+struct AdamStep {
+  float lr, b1, b2, omb1, omb2, eps, c1, c2;
+};
+
+__device__ inline void adam_element(float& p, float g, float& m, float& v, const AdamStep& k) {
+  m = fmaf(k.omb1, g, k.b1 * m);  // the contractions spelt out: every kernel rounds alike
+  v = fmaf(g, k.omb2 * g, k.b2 * v);
+  p -= k.lr * (m / k.c1) / (sqrtf(v / k.c2) + k.eps);
 }
 
-// Adam with beta = (0.9, 0.999), eps = 1e-8 at step t (1-based) over P
-// elements; 1 - beta and the bias corrections 1 - beta^t are formed in FP64
-// from the decimal betas and rounded once to FP32.
-static void adam_launch(int64_t P, float* p, const float* g, float* m, float* v, int t, float lr,
-                        hipStream_t stream) {
-  const double b1 = 0.9, b2 = 0.999;
+__global__ void k_adam(int64_t P, float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
+                       float* __restrict__ v, AdamStep k) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= P) return;
+  adam_element(p[i], g[i], m[i], v[i], k);
+}
+
+// Bias corrections 1 - beta^t of step t = 1, 2, ... for beta = (0.9, 0.999);
+// the powers are the products of the steps in order, carried from step to
+// step.  1 - beta and 1 - beta^t are formed in FP64 from the decimal betas
+// and rounded once to FP32.
+struct AdamPowers {
   double p1 = 1.0, p2 = 1.0;
-  for (int k = 0; k < t; ++k) {
-    p1 *= b1;
-    p2 *= b2;
+  void advance(int steps) {
+    for (int k = 0; k < steps; ++k) {
+      p1 *= 0.9;
+      p2 *= 0.999;
+    }
   }
-  hipLaunchKernelGGL(k_adam, dim3((unsigned)((P + 255) / 256)), dim3(256), 0, stream, P, p, g, m, v, lr, (float)b1,
-                     (float)b2, (float)(1.0 - b1), (float)(1.0 - b2), 1e-8f, (float)(1.0 - p1), (float)(1.0 - p2));
+  AdamStep step(float lr) const {
+    return AdamStep{lr,    (float)0.9, (float)0.999,      (float)(1.0 - 0.9), (float)(1.0 - 0.999),
+                    1e-8f, (float)(1.0 - p1), (float)(1.0 - p2)};
+  }
+};
+
+// ------------------------------------------------------ the fused kernels ---
+
+struct MlpWork {
+  // transposed BF16 activations and gradients, [unit][batch]: the operands of
+  // the weight gradients
+  bf16_t *xt, *h1t, *h2t, *dyt, *dz2t, *dz1t;
+  bf16_t *w1, *w2, *w2t, *w3, *w3t;
+  float *dy, *dz2, *dz1;  // [batch][unit] FP32, summed into the bias gradients
+  double* lossp;          // squared error of each 16 rows
+};
+
+constexpr int kRows = 16;            // batch rows of one k_mlp_rows workgroup
+constexpr int kLdH = kHid + 8;       // LDS row of an activation tile: 16-byte aligned, rows on different banks
+constexpr int kLdY = kOut + 8;
+
+typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
+typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
+
+__device__ inline f32x4 mfma_bf16(bf16x8 a, bf16x8 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+// Inputs k0 .. k0 + 7 of an FP32 row as a BF16 fragment, zero past its end.
+__device__ inline bf16x8 input_frag(const float* __restrict__ row, int k0) {
+  u16x8 u;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) u[j] = k0 + j < kIn ? to_bf16(row[k0 + j]) : (uint16_t)0;
+  return __builtin_bit_cast(bf16x8, u);
+}
+
+// 16 rows of the batch through the network, 16 wavefronts, each on 16 units
+// (columns) of every layer; with TRAIN also the backward pass of the mean
+// squared error down to the pre-activation gradients.  MFMA 16x16x32
+// fragments: lane l holds A[l%16][8(l/16) .. 8(l/16)+7] and B[8(l/16) ..
+// +7][l%16]; the result leaves D[4(l/16)+t][l%16], t = 0..3, in lane l, which
+// is also how it holds the layer's pre-activations until the backward pass
+// needs them.  The time is the chain of five products and their barriers;
+// the weights (0.3 MB, from L2) do not depend on it, so their fragments are
+// loaded ahead.  Reading the weights in FP32 and rounding them here, which
+// would spare a forward pass the launch of k_mlp_weights, took 28 us longer:
+// a lane's eight dwords are eight loads that touch 64 lines each.
+template <bool TRAIN>
+__global__ __launch_bounds__(1024) void k_mlp_rows(int B, const float* __restrict__ p, const float* __restrict__ xi,
+                                                   const float* __restrict__ tgt, const int32_t* __restrict__ idx,
+                                                   MlpWork w, float* __restrict__ out) {
+  __shared__ __attribute__((aligned(16))) bf16_t s_h1[kRows * kLdH];
+  __shared__ __attribute__((aligned(16))) bf16_t s_h2[kRows * kLdH];
+  __shared__ __attribute__((aligned(16))) bf16_t s_dy[kRows * kLdY];
+  __shared__ double s_loss[2];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r = lane & 15, q = lane >> 4, n = 16 * wave + r, m0 = blockIdx.x * kRows;
+  const int src = idx ? idx[m0 + r] : m0 + r;
+  const bf16x8 xa = input_frag(xi + (int64_t)src * kIn, 8 * q);
+  const bf16x8 w1f = *(const bf16x8*)(w.w1 + n * kInPad + 8 * q);
+  bf16x8 w2f[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) w2f[k] = *(const bf16x8*)(w.w2 + n * kHid + 32 * k + 8 * q);
+  const float b1 = p[kOffB1 + n], b2 = p[kOffB2 + n];
+
+  f32x4 z1 = mfma_bf16(xa, w1f, (f32x4)0.0f);
+  {
+    u16x4 h;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      z1[t] = z1[t] + b1;
+      h[t] = to_bf16(gelu(z1[t]));
+      s_h1[(4 * q + t) * kLdH + n] = h[t];
+    }
+    if (TRAIN) {
+      *(u16x4*)(w.h1t + (int64_t)n * B + m0 + 4 * q) = h;
+      if (wave == 0) {
+        const u16x8 xu = __builtin_bit_cast(u16x8, xa);
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          if (8 * q + j < kIn) w.xt[(int64_t)(8 * q + j) * B + m0 + r] = xu[j];
+      }
+    }
+  }
+  __syncthreads();
+
+  f32x4 z2 = (f32x4)0.0f;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) z2 = mfma_bf16(*(const bf16x8*)(s_h1 + r * kLdH + 32 * k + 8 * q), w2f[k], z2);
+  {
+    u16x4 h;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      z2[t] = z2[t] + b2;
+      h[t] = to_bf16(gelu(z2[t]));
+      s_h2[(4 * q + t) * kLdH + n] = h[t];
+    }
+    if (TRAIN) *(u16x4*)(w.h2t + (int64_t)n * B + m0 + 4 * q) = h;
+  }
+  bf16x8 w3tf, w2tf[8];
+  if (TRAIN) {
+    w3tf = *(const bf16x8*)(w.w3t + n * kOut + 8 * q);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) w2tf[k] = *(const bf16x8*)(w.w2t + n * kHid + 32 * k + 8 * q);
+  }
+  __syncthreads();
+
+  if (wave < kOut / 16) {
+    f32x4 y = (f32x4)0.0f;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const bf16x8 w3f = *(const bf16x8*)(w.w3 + n * kHid + 32 * k + 8 * q);
+      y = mfma_bf16(*(const bf16x8*)(s_h2 + r * kLdH + 32 * k + 8 * q), w3f, y);
+    }
+    const float b3 = p[kOffB3 + n];
+    const float sc = 2.0f / (float)(B * kOut);
+    double sq = 0.0;
+    u16x4 h;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int m = 4 * q + t;
+      const float yv = y[t] + b3;
+      if (out) out[(int64_t)(m0 + m) * kOut + n] = yv;
+      if (TRAIN) {
+        const int row = idx ? idx[m0 + m] : m0 + m;
+        const float d = yv - tgt[(int64_t)row * kOut + n];
+        sq += (double)d * (double)d;
+        const float g = sc * d;
+        w.dy[(int64_t)(m0 + m) * kOut + n] = g;
+        h[t] = to_bf16(g);
+        s_dy[m * kLdY + n] = h[t];
+      }
+    }
+    if (TRAIN) {
+      *(u16x4*)(w.dyt + (int64_t)n * B + m0 + 4 * q) = h;
+      sq = wave_sum_stride<1>(sq);
+      if (lane == 0) s_loss[wave] = sq;
+    }
+  }
+  if (!TRAIN) return;
+  __syncthreads();
+  if (threadIdx.x == 0) w.lossp[blockIdx.x] = s_loss[0] + s_loss[1];
+
+  // dZ2 = (dY W3) GELU'(Z2), its BF16 tile in place of H1
+  f32x4 dz = mfma_bf16(*(const bf16x8*)(s_dy + r * kLdY + 8 * q), w3tf, (f32x4)0.0f);
+  {
+    u16x4 h;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const float g = dz[t] * gelu_grad(z2[t]);
+      w.dz2[(int64_t)(m0 + 4 * q + t) * kHid + n] = g;
+      h[t] = to_bf16(g);
+      s_h1[(4 * q + t) * kLdH + n] = h[t];
+    }
+    *(u16x4*)(w.dz2t + (int64_t)n * B + m0 + 4 * q) = h;
+  }
+  __syncthreads();
+
+  // dZ1 = (dZ2 W2) GELU'(Z1)
+  dz = (f32x4)0.0f;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) dz = mfma_bf16(*(const bf16x8*)(s_h1 + r * kLdH + 32 * k + 8 * q), w2tf[k], dz);
+  {
+    u16x4 h;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const float g = dz[t] * gelu_grad(z1[t]);
+      w.dz1[(int64_t)(m0 + 4 * q + t) * kHid + n] = g;
+      h[t] = to_bf16(g);
+    }
+    *(u16x4*)(w.dz1t + (int64_t)n * B + m0 + 4 * q) = h;
+  }
+}
+
+// Workgroups of k_mlp_update: the 16 x 16 tiles of dW2, dW3 and dW1 (four a
+// workgroup, one per wavefront), 16 bias columns each, and the loss.
+constexpr int kTilesW2 = 256, kTilesW3 = 32, kTilesW1 = 16;
+constexpr int kTileBlocks = (kTilesW2 + kTilesW3 + kTilesW1) / 4;
+constexpr int kBiasBlocks = (kHid + kHid + kOut) / 16;
+constexpr int kUpdateBlocks = kTileBlocks + kBiasBlocks + 1;
+
+// The gradients of a batch whose rows k_mlp_rows took, each formed by the
+// lane that owns the parameter: stored to grad, or (ADAM) used for the
+// parameter's Adam step at once, the BF16 copies of the weights refreshed
+// beside it, so neither the gradient nor the old copies cross a launch.
+//   dW3[n][k] = sum_b dY[b][n] H2[b][k], dW2 and dW1 likewise;
+//   db[n] = the column sums of dZ1, dZ2, dY in FP32: sixteen running sums over
+//   the rows of equal b mod 16, combined in a fixed order.
+template <bool ADAM>
+__global__ __launch_bounds__(256) void k_mlp_update(int B, MlpWork w, float* __restrict__ p, float* __restrict__ am,
+                                                    float* __restrict__ av, AdamStep ad, float* __restrict__ grad,
+                                                    float* __restrict__ loss) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int blk = blockIdx.x;
+  if (blk < kTileBlocks) {
+    const int r = lane & 15, q = lane >> 4;
+    int t = blk * 4 + wave, nt, kt, ldw, cols;
+    const bf16_t *a, *b;
+    int64_t off;
+    bf16_t *wc, *wt;
+    int ldc, ldt;
+    if (t < kTilesW2) {
+      nt = t >> 4, kt = t & 15, ldw = kHid, cols = kHid, off = kOffW2;
+      a = w.dz2t, b = w.h1t, wc = w.w2, wt = w.w2t, ldc = kHid, ldt = kHid;
+    } else if (t < kTilesW2 + kTilesW3) {
+      t -= kTilesW2;
+      nt = t >> 4, kt = t & 15, ldw = kHid, cols = kHid, off = kOffW3;
+      a = w.dyt, b = w.h2t, wc = w.w3, wt = w.w3t, ldc = kHid, ldt = kOut;
+    } else {
+      nt = t - kTilesW2 - kTilesW3, kt = 0, ldw = kIn, cols = kIn, off = kOffW1;
+      a = w.dz1t, b = w.xt, wc = w.w1, wt = nullptr, ldc = kInPad, ldt = 0;
+    }
+    const int k = 16 * kt + r;
+    const bf16_t* ar = a + (int64_t)(16 * nt + r) * B + 8 * q;
+    const bf16_t* br = b + (int64_t)(k < cols ? k : 0) * B + 8 * q;
+    const int64_t i0 = off + (int64_t)(16 * nt + 4 * q) * ldw + k;
+    // the parameters and moments do not depend on the gradient: on their way
+    // while it is formed
+    float pv[4], mv[4], vv[4];
+    if (ADAM && k < cols) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int64_t i = i0 + (int64_t)j * ldw;
+        pv[j] = p[i];
+        mv[j] = am[i];
+        vv[j] = av[i];
+      }
+    }
+    // K in chunks of 32 rows, the operands of eight chunks in flight
+    f32x4 acc = (f32x4)0.0f;
+    for (int c = 0; c < B; c += 256) {
+      bf16x8 af[8], bf[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        if (c + 32 * j < B) {
+          af[j] = *(const bf16x8*)(ar + c + 32 * j);
+          bf[j] = *(const bf16x8*)(br + c + 32 * j);
+        }
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        if (c + 32 * j < B) acc = mfma_bf16(af[j], bf[j], acc);
+    }
+    if (k >= cols) return;
+    u16x4 h;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int64_t i = i0 + (int64_t)j * ldw;
+      if (ADAM) {
+        adam_element(pv[j], acc[j], mv[j], vv[j], ad);
+        p[i] = pv[j];
+        am[i] = mv[j];
+        av[i] = vv[j];
+        h[j] = to_bf16(pv[j]);
+        wc[(int64_t)(16 * nt + 4 * q + j) * ldc + k] = h[j];
+      } else {
+        grad[i] = acc[j];
+      }
+    }
+    if (ADAM && wt) *(u16x4*)(wt + (int64_t)k * ldt + 16 * nt + 4 * q) = h;
+    return;
+  }
+  blk -= kTileBlocks;
+  if (blk < kBiasBlocks) {
+    __shared__ float part[16][16];
+    const float* a = blk < 16 ? w.dz1 : blk < 32 ? w.dz2 : w.dy;
+    const int N = blk < 32 ? kHid : kOut;
+    const int c0 = (blk < 16 ? blk : blk < 32 ? blk - 16 : blk - 32) * 16;
+    const int64_t off = (blk < 16 ? kOffB1 : blk < 32 ? kOffB2 : kOffB3) + c0;
+    const int col = threadIdx.x & 15, res = threadIdx.x >> 4;
+    const float* col0 = a + (int64_t)res * N + c0 + col;
+    float s = 0.0f;
+    for (int m = 0; m < B; m += 256) {
+      float v[16];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) v[j] = m + 16 * j < B ? col0[(int64_t)(m + 16 * j) * N] : 0.0f;
+#pragma unroll
+      for (int j = 0; j < 16; ++j)
+        if (m + 16 * j < B) s += v[j];
+    }
+    part[res][col] = s;
+    __syncthreads();
+    if (threadIdx.x < 16) {
+      float g[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) g[j] = (part[j][col] + part[j + 4][col]) + (part[j + 8][col] + part[j + 12][col]);
+      const float sum = (g[0] + g[1]) + (g[2] + g[3]);
+      const int64_t i = off + col;
+      if (ADAM) adam_element(p[i], sum, am[i], av[i], ad);
+      else grad[i] = sum;
+    }
+    return;
+  }
+  if (!loss) return;
+  __shared__ double red[4];
+  double s = 0.0;
+  for (int i = threadIdx.x; i < B / kRows; i += 256) s += w.lossp[i];
+  s = wave_sum_stride<1>(s);
+  if (lane == 0) red[wave] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) *loss = (float)(((red[0] + red[1]) + (red[2] + red[3])) / (double)(B * kOut));
 }
 
 // ------------------------------------------------------------ host side ---
-
-struct MlpWork {
-  bf16_t *xb, *xbt, *h1b, *h1bt, *h2b, *h2bt, *dyb, *dybt, *dz2b, *dz2bt, *dz1bt;
-  bf16_t *w1, *w2, *w2t, *w3, *w3t;
-  float *tb, *z1, *z2, *y, *dy, *dz2, *dz1, *grad, *loss;
-};
 
 static size_t r256(size_t b) { return (b + 255) & ~(size_t)255; }
 
@@ -256,85 +420,23 @@ static size_t mlp_layout(int B, MlpWork* w, char* base) {
   };
   const size_t bh = sizeof(bf16_t), f = sizeof(float);
   MlpWork t;
-  t.xb = (bf16_t*)take((size_t)B * kInPad * bh);
-  t.xbt = (bf16_t*)take((size_t)B * kInPad * bh);
-  t.h1b = (bf16_t*)take((size_t)B * kHid * bh);
-  t.h1bt = (bf16_t*)take((size_t)B * kHid * bh);
-  t.h2b = (bf16_t*)take((size_t)B * kHid * bh);
-  t.h2bt = (bf16_t*)take((size_t)B * kHid * bh);
-  t.dyb = (bf16_t*)take((size_t)B * kOut * bh);
-  t.dybt = (bf16_t*)take((size_t)B * kOut * bh);
-  t.dz2b = (bf16_t*)take((size_t)B * kHid * bh);
-  t.dz2bt = (bf16_t*)take((size_t)B * kHid * bh);
-  t.dz1bt = (bf16_t*)take((size_t)B * kHid * bh);
+  t.xt = (bf16_t*)take((size_t)B * kIn * bh);
+  t.h1t = (bf16_t*)take((size_t)B * kHid * bh);
+  t.h2t = (bf16_t*)take((size_t)B * kHid * bh);
+  t.dyt = (bf16_t*)take((size_t)B * kOut * bh);
+  t.dz2t = (bf16_t*)take((size_t)B * kHid * bh);
+  t.dz1t = (bf16_t*)take((size_t)B * kHid * bh);
   t.w1 = (bf16_t*)take((size_t)kHid * kInPad * bh);
   t.w2 = (bf16_t*)take((size_t)kHid * kHid * bh);
   t.w2t = (bf16_t*)take((size_t)kHid * kHid * bh);
   t.w3 = (bf16_t*)take((size_t)kOut * kHid * bh);
   t.w3t = (bf16_t*)take((size_t)kOut * kHid * bh);
-  t.tb = (float*)take((size_t)B * kOut * f);
-  t.z1 = (float*)take((size_t)B * kHid * f);
-  t.z2 = (float*)take((size_t)B * kHid * f);
-  t.y = (float*)take((size_t)B * kOut * f);
   t.dy = (float*)take((size_t)B * kOut * f);
   t.dz2 = (float*)take((size_t)B * kHid * f);
   t.dz1 = (float*)take((size_t)B * kHid * f);
-  t.grad = (float*)take((size_t)kParams * f);
-  t.loss = (float*)take(64);
+  t.lossp = (double*)take((size_t)B / kRows * sizeof(double));
   if (w) *w = t;
   return off;
-}
-
-template <int EPI>
-static void gemm(int M, int N, int K, const bf16_t* A, int lda, const bf16_t* B, int ldb, const Epi& ep,
-                 hipStream_t st) {
-  dim3 grid((N + 63) / 64, (M + 63) / 64);
-  hipLaunchKernelGGL((k_gemm_nt<EPI>), grid, dim3(256), 0, st, M, N, K, A, lda, B, ldb, ep);
-}
-
-static Epi epi(const float* bias, float* f32, int ld_f32, bf16_t* bf, int ld_bf, bf16_t* bft, int ld_bft,
-               const float* z = nullptr, int ld_z = 0) {
-  Epi e;
-  e.bias = bias;
-  e.f32 = f32;
-  e.ld_f32 = ld_f32;
-  e.bf = bf;
-  e.ld_bf = ld_bf;
-  e.bft = bft;
-  e.ld_bft = ld_bft;
-  e.z = z;
-  e.ld_z = ld_z;
-  return e;
-}
-
-// Forward on the batch already in w.xb / w.xbt; output Y (FP32) in w.y.
-static void forward(const float* p, int B, const MlpWork& w, hipStream_t st) {
-  gemm<EPI_BIAS_GELU>(B, kHid, kInPad, w.xb, kInPad, w.w1, kInPad,
-                      epi(p + kOffB1, w.z1, kHid, w.h1b, kHid, w.h1bt, B), st);
-  gemm<EPI_BIAS_GELU>(B, kHid, kHid, w.h1b, kHid, w.w2, kHid, epi(p + kOffB2, w.z2, kHid, w.h2b, kHid, w.h2bt, B),
-                      st);
-  gemm<EPI_BIAS>(B, kOut, kHid, w.h2b, kHid, w.w3, kHid, epi(p + kOffB3, w.y, kOut, nullptr, 0, nullptr, 0), st);
-}
-
-// Backward of the mean squared error against w.tb; gradients in w.grad.
-static void backward(int B, const MlpWork& w, hipStream_t st) {
-  hipLaunchKernelGGL(k_mse, dim3(1), dim3(256), 0, st, B, w.y, w.tb, w.dy, w.dyb, w.dybt, w.loss);
-  float* g = w.grad;
-  // dW3[n][k] = sum_b dY[b][n] H2[b][k]
-  gemm<EPI_STORE>(kOut, kHid, B, w.dybt, B, w.h2bt, B, epi(nullptr, g + kOffW3, kHid, nullptr, 0, nullptr, 0), st);
-  // dZ2 = (dY W3) * GELU'(Z2)
-  gemm<EPI_DGELU>(B, kHid, kOut, w.dyb, kOut, w.w3t, kOut,
-                  epi(nullptr, w.dz2, kHid, w.dz2b, kHid, w.dz2bt, B, w.z2, kHid), st);
-  // dW2[n][k] = sum_b dZ2[b][n] H1[b][k]
-  gemm<EPI_STORE>(kHid, kHid, B, w.dz2bt, B, w.h1bt, B, epi(nullptr, g + kOffW2, kHid, nullptr, 0, nullptr, 0), st);
-  // dZ1 = (dZ2 W2) * GELU'(Z1)
-  gemm<EPI_DGELU>(B, kHid, kHid, w.dz2b, kHid, w.w2t, kHid,
-                  epi(nullptr, w.dz1, kHid, nullptr, 0, w.dz1bt, B, w.z1, kHid), st);
-  // dW1[n][k] = sum_b dZ1[b][n] X[b][k], k < 10
-  gemm<EPI_STORE>(kHid, kIn, B, w.dz1bt, B, w.xbt, B, epi(nullptr, g + kOffW1, kIn, nullptr, 0, nullptr, 0), st);
-  hipLaunchKernelGGL(k_colsum, dim3((kHid + 63) / 64), dim3(256), 0, st, B, kHid, w.dz1, g + kOffB1);
-  hipLaunchKernelGGL(k_colsum, dim3((kHid + 63) / 64), dim3(256), 0, st, B, kHid, w.dz2, g + kOffB2);
-  hipLaunchKernelGGL(k_colsum, dim3((kOut + 63) / 64), dim3(256), 0, st, B, kOut, w.dy, g + kOffB3);
 }
 
 static void weights_bf16(const float* p, const MlpWork& w, hipStream_t st) {
@@ -342,10 +444,11 @@ static void weights_bf16(const float* p, const MlpWork& w, hipStream_t st) {
                      w.w3t);
 }
 
-static void load_batch(int B, const float* xi, const float* tgt, const int32_t* idx, const MlpWork& w,
-                       hipStream_t st) {
-  hipLaunchKernelGGL(k_mlp_input, dim3((B * kInPad + 255) / 256), dim3(256), 0, st, B, xi, tgt, idx, w.xb, w.xbt,
-                     w.tb);
+// Forward and backward pass of the batch, then its gradients (to grad) or
+// the Adam step on them.
+static void rows_pass(const float* p, int B, const float* xi, const float* tgt, const int32_t* idx, const MlpWork& w,
+                      float* out, hipStream_t st) {
+  hipLaunchKernelGGL(k_mlp_rows<true>, dim3(B / kRows), dim3(1024), 0, st, B, p, xi, tgt, idx, w, out);
 }
 
 static bool batch_ok(int B) { return B >= 32 && B <= 65536 && B % 32 == 0; }
@@ -376,9 +479,8 @@ ens_status ens_mlp_forward(const float* params, int32_t batch, const float* xi, 
   MlpWork w;
   mlp_layout(batch, &w, (char*)workspace);
   weights_bf16(params, w, stream);
-  load_batch(batch, xi, nullptr, nullptr, w, stream);
-  forward(params, batch, w, stream);
-  ENS_HIP_TRY(hipMemcpyAsync(out, w.y, (size_t)batch * kOut * sizeof(float), hipMemcpyDeviceToDevice, stream));
+  hipLaunchKernelGGL(k_mlp_rows<false>, dim3(batch / kRows), dim3(1024), 0, stream, batch, params, xi,
+                     (const float*)nullptr, (const int32_t*)nullptr, w, out);
   ENS_LAUNCH_CHECK();
   return ENS_OK;
 }
@@ -395,13 +497,9 @@ ens_status ens_mlp_grad(const float* params, int32_t batch, const float* xi, con
   MlpWork w;
   mlp_layout(batch, &w, (char*)workspace);
   weights_bf16(params, w, stream);
-  load_batch(batch, xi, target, nullptr, w, stream);
-  forward(params, batch, w, stream);
-  backward(batch, w, stream);
-  if (out)
-    ENS_HIP_TRY(hipMemcpyAsync(out, w.y, (size_t)batch * kOut * sizeof(float), hipMemcpyDeviceToDevice, stream));
-  ENS_HIP_TRY(hipMemcpyAsync(grad, w.grad, (size_t)kParams * sizeof(float), hipMemcpyDeviceToDevice, stream));
-  if (loss) ENS_HIP_TRY(hipMemcpyAsync(loss, w.loss, sizeof(float), hipMemcpyDeviceToDevice, stream));
+  rows_pass(params, batch, xi, target, nullptr, w, out, stream);
+  hipLaunchKernelGGL(k_mlp_update<false>, dim3(kUpdateBlocks), dim3(256), 0, stream, batch, w, (float*)nullptr,
+                     (float*)nullptr, (float*)nullptr, AdamStep{}, grad, loss);
   ENS_LAUNCH_CHECK();
   return ENS_OK;
 }
@@ -420,13 +518,13 @@ ens_status ens_mlp_train(float* params, float* adam_m, float* adam_v, int32_t st
   MlpWork w;
   mlp_layout(batch, &w, (char*)workspace);
   weights_bf16(params, w, stream);
+  AdamPowers pw;
+  pw.advance(step0);
   for (int s = 0; s < steps; ++s) {
-    load_batch(batch, xi, target, batch_idx + (int64_t)s * batch, w, stream);
-    forward(params, batch, w, stream);
-    backward(batch, w, stream);
-    if (loss) ENS_HIP_TRY(hipMemcpyAsync(loss + s, w.loss, sizeof(float), hipMemcpyDeviceToDevice, stream));
-    adam_launch(kParams, params, w.grad, adam_m, adam_v, step0 + s + 1, lr, stream);
-    weights_bf16(params, w, stream);
+    pw.advance(1);
+    rows_pass(params, batch, xi, target, batch_idx + (int64_t)s * batch, w, nullptr, stream);
+    hipLaunchKernelGGL(k_mlp_update<true>, dim3(kUpdateBlocks), dim3(256), 0, stream, batch, w, params, adam_m, adam_v,
+                       pw.step(lr), (float*)nullptr, loss ? loss + s : nullptr);
     ENS_LAUNCH_CHECK();
   }
   return ENS_OK;
@@ -439,7 +537,10 @@ ens_status ens_mlp_adam(float* params, const float* grad, float* adam_m, float* 
   ENS_ARG_CHECK(lr > 0.0f, "learning rate must be positive");
   ENS_ARG_CHECK(count <= INT32_MAX, "count must fit in int32");
   if (count == 0) return ENS_OK;
-  adam_launch(count, params, grad, adam_m, adam_v, step, lr, stream);
+  AdamPowers pw;
+  pw.advance(step);
+  hipLaunchKernelGGL(k_adam, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, stream, count, params, grad, adam_m,
+                     adam_v, pw.step(lr));
   ENS_LAUNCH_CHECK();
   return ENS_OK;
 }

@@ -42,3 +42,39 @@ def test_reconstruct(E, n, r, s, shift):
         bound = 2 * (r + 4) * EPS * (Phi.abs() @ (c.double().abs() * (1 if d is None else d.abs())
                                                   + (0 if m is None else m.abs())).t())
         assert bool(((x0 - Phi @ ch.t()).abs() <= bound).all())
+
+
+# batches at the edges of the weight gradients' chunks (eight of 32 rows in
+# flight) and of the bias sums' (sixteen of 16): one chunk, a partial group, a
+# whole one, one past it.  Tolerances as in the network's parity test: the
+# reference is FP64 on the same BF16 operands, and a pre-activation may round
+# to the neighbouring BF16 value.
+@pytest.mark.parametrize("B", [32, 96, 224, 256, 288, 544])
+def test_network_batches(E, B):
+    import numpy as np
+    from oracle import learned as L
+    rng = np.random.default_rng(B)
+    p = L.init_params(12).astype(np.float32)
+    X = rng.uniform(-1, 1, (B, L.IN)).astype(np.float32)
+    T = rng.standard_normal((B, L.OUT)).astype(np.float32)
+    dev = lambda a: torch.as_tensor(a, device=DEV)  # noqa: E731
+    y, g, loss = E.mlp_grad(dev(p), dev(X), dev(T))
+    yo, lo, go = L.forward_backward(p.astype(np.float64), X, T, bf16_points=True)
+    rel = lambda a, b: np.linalg.norm(a - b) / np.linalg.norm(b)  # noqa: E731
+    assert rel(y.cpu().numpy(), yo) <= 5e-3 and abs(float(loss.item()) - lo) <= 5e-3 * lo
+    off, gg = 0, g.cpu().numpy()
+    for name, shape in L.SIZES:
+        k = int(np.prod(shape))
+        assert rel(gg[off:off + k], go[off:off + k]) <= 2e-2, name
+        off += k
+    assert torch.equal(E.mlp_forward(dev(p), dev(X)), y)
+    # the training step takes Adam on those gradients, bit for bit, the rows
+    # in the order of its index list
+    perm = rng.permutation(B).astype(np.int32)
+    inv = np.argsort(perm)
+    a, am, av = dev(p), torch.zeros(L.P, device=DEV), torch.zeros(L.P, device=DEV)
+    lt = torch.zeros(1, device=DEV)
+    E.mlp_train(a, am, av, 0, dev(X[inv]), dev(T[inv]), B, dev(perm), 1e-3, loss=lt)
+    b, bm, bv = dev(p), torch.zeros(L.P, device=DEV), torch.zeros(L.P, device=DEV)
+    E.mlp_adam(b, g, bm, bv, 1, 1e-3)
+    assert torch.equal(a, b) and torch.equal(am, bm) and torch.equal(av, bv) and torch.equal(lt, loss)
