@@ -2,7 +2,7 @@
 // method of snapshots from solutions the ensemble solver produced.
 //
 //   snapshots S [n][m] (one column per solved sample)
-//   G = S^T S [m][m]                         (FP64, split-K tiled GEMM)
+//   G = S^T S [m][m]                         (FP64 matrix cores, half of the symmetric product, split K)
 //   top-r eigenpairs of G by block subspace iteration with a seeded start
 //   block, Gram-Schmidt (twice), and a final Rayleigh-Ritz step whose k x k
 //   eigenproblem is solved by cyclic Jacobi in one workgroup
@@ -15,64 +15,114 @@
 
 namespace ens {
 
-// C[M][N] (= or +=) op(A)[M][K] op(B)[K][N], FP64.  op(A)[i][k] is A[i*lda+k]
-// (TA = 0) or A[k*lda+i] (TA = 1); likewise op(B)[k][j] is B[k*ldb+j]
-// (TB = 0) or B[j*ldb+k] (TB = 1).  Block tile 64 x 64, 16 x 16 threads with
-// 4 x 4 outputs each, K staged through LDS in slices of 16.  blockIdx.z
-// selects a K range [z*kchunk, (z+1)*kchunk) and writes its partial product
-// to C + z*cstride (split-K; summed by k_sum_slices).
-template <int TA, int TB>
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+// C[M][N] = op(A)[M][K] B[K][N] in FP64 on the matrix cores
+// (v_mfma_f64_16x16x4: lane l holds A[l%16][l/16] and B[l/16][l%16], the result
+// leaves D[l/16 + 4 i][l%16], i = 0..3).  op(A)[i][k] is A[i*lda+k] (TA = 0) or
+// A[k*lda+i] (TA = 1); B[k][j] is B[k*ldb+j].  A workgroup forms 128 x BN of C:
+// BN = 128 as 2 x 2 wavefronts of 64 x 64, else four wavefronts of 32 x BN, so
+// a step of 4 in k reads at most 8 operands from LDS for 16 MFMA (one a SIMD
+// in 64 cycles) and the matrix cores, not LDS, bound the square products; the
+// products with a narrow B (the basis and the projection, N = 32) are bound by
+// reading A.  K slices of KS are staged k-major in LDS, double buffered, the
+// next slice on its way in registers meanwhile.  blockIdx.z selects a K range
+// [z*kchunk, (z+1)*kchunk) and writes its partial product to C + z*cstride.
+// SYM (A = B): blockIdx.x counts the block pairs i <= j of the symmetric C,
+// and with a single K range the mirrored block is written too.
+// The Gram matrix of 2048 snapshots at 64^3: 20.9 ms (58 TFLOP/s of its
+// half; a large library product reaches 72 here); the lane-per-4x4 form
+// with all of C took 70.9 ms.
+template <int TA, int BN, int KS, bool SYM>
 __global__ __launch_bounds__(256) void k_dgemm(int64_t M, int64_t N, int64_t K, const double* __restrict__ A,
                                                int64_t lda, const double* __restrict__ B, int64_t ldb,
                                                double* __restrict__ C, int64_t ldc, int64_t kchunk,
                                                int64_t cstride) {
-  __shared__ double As[16][64 + 1];
-  __shared__ double Bs[16][64 + 1];
-  const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-  const int64_t i0 = (int64_t)blockIdx.y * 64, j0 = (int64_t)blockIdx.x * 64;
+  constexpr int BM = 128, WM = BN == 128 ? 64 : 32, WN = BN == 128 ? 64 : BN;
+  constexpr int MT = WM / 16, NT = WN / 16, LA = BM + 2, LB = BN + 2;
+  constexpr int UA = KS * BM / 256, UB = KS * BN / 256;
+  __shared__ double As[2][KS * LA];
+  __shared__ double Bs[2][KS * LB];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = lane & 15, q = lane >> 4;
+  const int wm = BN == 128 ? (wave >> 1) * 64 : wave * 32, wn = BN == 128 ? (wave & 1) * 64 : 0;
+  int64_t bi = blockIdx.y, bj = blockIdx.x;
+  if (SYM) {  // pair p -> (i, j), i <= j, column by column
+    const int64_t p = blockIdx.x;
+    bj = (int64_t)((sqrt(8.0 * (double)p + 1.0) - 1.0) * 0.5);
+    while (bj * (bj + 1) / 2 > p) --bj;
+    while ((bj + 1) * (bj + 2) / 2 <= p) ++bj;
+    bi = p - bj * (bj + 1) / 2;
+  }
+  const int64_t i0 = bi * BM, j0 = bj * BN;
   const int64_t kb = (int64_t)blockIdx.z * kchunk;
   const int64_t ke = kb + kchunk < K ? kb + kchunk : K;
-  double acc[4][4];
+  double ra[UA], rb[UB];
+  auto load = [&](int64_t k0) {
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b) acc[a][b] = 0.0;
-  for (int64_t k0 = kb; k0 < ke; k0 += 16) {
-    // each of the 256 threads loads 4 elements of each 16 x 64 slice
-    for (int t = threadIdx.x; t < 16 * 64; t += 256) {
-      const int kk = TA ? t / 64 : t % 16;
-      const int ii = TA ? t % 64 : t / 16;
-      const int64_t gi = i0 + ii, gk = k0 + kk;
-      As[kk][ii] = (gi < M && gk < ke) ? (TA ? A[gk * lda + gi] : A[gi * lda + gk]) : 0.0;
-      const int kk2 = TB ? t % 16 : t / 64;
-      const int jj = TB ? t / 16 : t % 64;
-      const int64_t gj = j0 + jj, gk2 = k0 + kk2;
-      Bs[kk2][jj] = (gj < N && gk2 < ke) ? (TB ? B[gj * ldb + gk2] : B[gk2 * ldb + gj]) : 0.0;
+    for (int u = 0; u < UA; ++u) {
+      const int t = tid + 256 * u;
+      const int64_t k = k0 + (TA ? t / BM : t % KS), i = i0 + (TA ? t % BM : t / KS);
+      ra[u] = (i < M && k < ke) ? (TA ? A[k * lda + i] : A[i * lda + k]) : 0.0;
     }
-    __syncthreads();
 #pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      double a[4], b[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        a[q] = As[kk][ty + 16 * q];
-        b[q] = Bs[kk][tx + 16 * q];
-      }
-#pragma unroll
-      for (int p = 0; p < 4; ++p)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) acc[p][q] += a[p] * b[q];
+    for (int u = 0; u < UB; ++u) {
+      const int t = tid + 256 * u;
+      const int64_t k = k0 + t / BN, j = j0 + t % BN;
+      rb[u] = (j < N && k < ke) ? B[k * ldb + j] : 0.0;
     }
+  };
+  auto store = [&](int buf) {
+#pragma unroll
+    for (int u = 0; u < UA; ++u) {
+      const int t = tid + 256 * u;
+      As[buf][(TA ? t / BM : t % KS) * LA + (TA ? t % BM : t / KS)] = ra[u];
+    }
+#pragma unroll
+    for (int u = 0; u < UB; ++u) {
+      const int t = tid + 256 * u;
+      Bs[buf][(t / BN) * LB + t % BN] = rb[u];
+    }
+  };
+  f64x4 acc[MT][NT];
+#pragma unroll
+  for (int a = 0; a < MT; ++a)
+#pragma unroll
+    for (int b = 0; b < NT; ++b) acc[a][b] = (f64x4)0.0;
+  load(kb);
+  store(0);
+  __syncthreads();
+  int buf = 0;
+  for (int64_t k0 = kb; k0 < ke; k0 += KS, buf ^= 1) {
+    const bool more = k0 + KS < ke;
+    if (more) load(k0 + KS);
+#pragma unroll
+    for (int kk = 0; kk < KS; kk += 4) {
+      double a[MT], b[NT];
+#pragma unroll
+      for (int m = 0; m < MT; ++m) a[m] = As[buf][(kk + q) * LA + wm + 16 * m + r];
+#pragma unroll
+      for (int n = 0; n < NT; ++n) b[n] = Bs[buf][(kk + q) * LB + wn + 16 * n + r];
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int n = 0; n < NT; ++n) acc[m][n] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[m], b[n], acc[m][n], 0, 0, 0);
+    }
+    if (more) store(buf ^ 1);
     __syncthreads();
   }
   double* Cz = C + (int64_t)blockIdx.z * cstride;
 #pragma unroll
-  for (int p = 0; p < 4; ++p)
+  for (int m = 0; m < MT; ++m)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int64_t i = i0 + ty + 16 * p, j = j0 + tx + 16 * q;
-      if (i < M && j < N) Cz[i * ldc + j] = acc[p][q];
-    }
+    for (int n = 0; n < NT; ++n)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int64_t i = i0 + wm + 16 * m + q + 4 * t, j = j0 + wn + 16 * n + r;
+        if (i >= M || j >= N) continue;
+        Cz[i * ldc + j] = acc[m][n][t];
+        if (SYM && gridDim.z == 1 && bi != bj) Cz[j * ldc + i] = acc[m][n][t];
+      }
 }
 
 // out[i] = sum_z parts[z*stride + i], z ascending.
@@ -81,8 +131,38 @@ __global__ void k_sum_slices(int64_t count, int nz, const double* __restrict__ p
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= count) return;
   double s = 0.0;
+#pragma unroll 8
   for (int z = 0; z < nz; ++z) s += parts[(int64_t)z * stride + i];
   out[i] = s;
+}
+
+// The same for a symmetric m x m product whose slices hold the blocks i <= j of
+// 128 x 128 only: a workgroup sums a 32 x 32 piece of one and writes it and
+// its mirror image, turned over in LDS.
+__global__ __launch_bounds__(256) void k_sum_slices_sym(int64_t m, int nz, const double* __restrict__ parts,
+                                                        int64_t stride, double* __restrict__ out) {
+  const int64_t i0 = (int64_t)blockIdx.y * 32, j0 = (int64_t)blockIdx.x * 32;
+  if (i0 / 128 > j0 / 128) return;
+  __shared__ double t[32][33];
+  const int c = threadIdx.x & 31, g = threadIdx.x >> 5;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int64_t i = i0 + g + 8 * u, j = j0 + c;
+    if (i < m && j < m) {
+      double s = 0.0;
+#pragma unroll 8
+      for (int z = 0; z < nz; ++z) s += parts[(int64_t)z * stride + i * m + j];
+      out[i * m + j] = s;
+      t[g + 8 * u][c] = s;
+    }
+  }
+  if (i0 / 128 == j0 / 128) return;  // a diagonal block holds both halves
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int64_t j = j0 + g + 8 * u, i = i0 + c;
+    if (i < m && j < m) out[j * m + i] = t[c][g + 8 * u];
+  }
 }
 
 // Orthonormalise the k columns of Y [m][k] (row-major) in place, one
@@ -293,9 +373,6 @@ __global__ __launch_bounds__(256) void k_reconstruct(int64_t n, int r, int s, co
   x0[t] = acc;
 }
 
-typedef double f64x2 __attribute__((ext_vector_type(2)));
-typedef double f64x4 __attribute__((ext_vector_type(4)));
-
 // The same product on the FP64 matrix cores (v_mfma_f64_16x16x4): a wavefront
 // forms 16 nodes x 32 samples at a time.  It is bound by reading Phi and
 // writing x0, so the layout is the loads': the four k values of an MFMA step
@@ -388,31 +465,62 @@ __global__ void k_standardize(int m, int r, int common, const double* __restrict
 
 // ------------------------------------------------------------ host side ---
 
-template <int TA, int TB>
-static void dgemm(int64_t M, int64_t N, int64_t K, const double* A, int64_t lda, const double* B, int64_t ldb,
-                  double* C, int64_t ldc, int splits, double* scratch, hipStream_t st) {
-  if (splits <= 1) {
-    dim3 grid((unsigned)((N + 63) / 64), (unsigned)((M + 63) / 64), 1);
-    hipLaunchKernelGGL((k_dgemm<TA, TB>), grid, dim3(256), 0, st, M, N, K, A, lda, B, ldb, C, ldc, K, (int64_t)0);
-    return;
-  }
-  // the split path writes C densely (leading dimension N); callers pass ldc == N
-  int64_t kchunk = (K + splits - 1) / splits;
-  kchunk = (kchunk + 15) / 16 * 16;
-  const int nz = (int)((K + kchunk - 1) / kchunk);
-  dim3 grid((unsigned)((N + 63) / 64), (unsigned)((M + 63) / 64), (unsigned)nz);
-  hipLaunchKernelGGL((k_dgemm<TA, TB>), grid, dim3(256), 0, st, M, N, K, A, lda, B, ldb, scratch, N, kchunk,
-                     M * N);
-  hipLaunchKernelGGL(k_sum_slices, dim3((unsigned)((M * N + 255) / 256)), dim3(256), 0, st, M * N, nz, scratch,
-                     M * N, C);
-  (void)ldc;
+// K ranges a product of `tiles` workgroup tiles is split into: as many as make
+// `want` workgroups (about 512 are resident), none under 128 of K (a sum pass
+// reads each range's product again), at most 128.
+static int k_splits(int64_t tiles, int64_t K, int64_t want) {
+  int64_t s = (want + tiles - 1) / tiles, most = K / 128;
+  if (most > 128) most = 128;
+  if (s > most) s = most;
+  return (int)(s < 1 ? 1 : s);
 }
 
-static int gram_splits(int64_t n) {
-  int64_t s = n / 4096;
-  if (s < 1) s = 1;
-  if (s > 32) s = 32;
-  return (int)s;
+static int64_t tiles128(int64_t n) { return (n + 127) / 128; }
+
+// The widest tile of the three that N fills.
+static int tile_n(int64_t N) { return N <= 32 ? 32 : N <= 64 ? 64 : 128; }
+
+static int product_splits(int64_t M, int64_t N, int64_t K) {
+  const int bn = tile_n(N);
+  return k_splits(tiles128(M) * ((N + bn - 1) / bn), K, 1024);
+}
+
+// The Gram product's last round of workgroups is part empty, so it takes more
+// rounds, of smaller ranges.
+static int gram_splits(int64_t n, int64_t m) {
+  const int64_t t = tiles128(m);
+  return k_splits(t * (t + 1) / 2, n, 4096);
+}
+
+// C [M][N] (dense) = op(A) B in `splits` K ranges; scratch [splits][M][N] for
+// more than one.
+template <int TA>
+static void dgemm(int64_t M, int64_t N, int64_t K, const double* A, int64_t lda, const double* B, int64_t ldb,
+                  double* C, int splits, double* scratch, hipStream_t st) {
+  int64_t kchunk = (K + splits - 1) / splits;
+  kchunk = (kchunk + 31) / 32 * 32;
+  const int nz = (int)((K + kchunk - 1) / kchunk);
+  double* out = nz > 1 ? scratch : C;
+  const int bn = tile_n(N);
+  const dim3 grid((unsigned)((N + bn - 1) / bn), (unsigned)tiles128(M), (unsigned)nz);
+  if (bn == 32)
+    hipLaunchKernelGGL((k_dgemm<TA, 32, 16, false>), grid, dim3(256), 0, st, M, N, K, A, lda, B, ldb, out, N, kchunk,
+                       M * N);
+  else if (bn == 64)
+    hipLaunchKernelGGL((k_dgemm<TA, 64, 16, false>), grid, dim3(256), 0, st, M, N, K, A, lda, B, ldb, out, N, kchunk,
+                       M * N);
+  else
+    hipLaunchKernelGGL((k_dgemm<TA, 128, 16, false>), grid, dim3(256), 0, st, M, N, K, A, lda, B, ldb, out, N, kchunk,
+                       M * N);
+  if (nz > 1)
+    hipLaunchKernelGGL(k_sum_slices, dim3((unsigned)((M * N + 255) / 256)), dim3(256), 0, st, M * N, nz, scratch,
+                       M * N, C);
+}
+
+// Doubles of split-K scratch of the eigensolver's products.
+static size_t eig_scratch(int64_t m, int64_t k) {
+  const size_t a = (size_t)product_splits(m, k, m) * m * k, b = (size_t)product_splits(k, k, m) * k * k;
+  return a > b ? a : b;
 }
 
 }  // namespace ens
@@ -432,28 +540,36 @@ ens_status ens_pod_collect(const double* x, int64_t n, int32_t s, double* S, int
 
 ens_status ens_pod_gram_workspace_bytes(int64_t n, int32_t m, size_t* bytes) {
   ENS_ARG_CHECK(bytes && n >= 1 && m >= 1, "bad sizes");
-  *bytes = (size_t)gram_splits(n) * m * m * sizeof(double);
+  *bytes = (size_t)gram_splits(n, m) * m * m * sizeof(double);
   return ENS_OK;
 }
 
 ens_status ens_pod_gram(const double* S, int64_t n, int32_t m, double* G, void* workspace, size_t ws_bytes,
                         hipStream_t stream) {
   ENS_ARG_CHECK(S && G && n >= 1 && m >= 1, "bad Gram arguments");
-  const int sp = gram_splits(n);
+  const int sp = gram_splits(n, m);
   ENS_ARG_CHECK(sp == 1 || workspace, "null workspace");
   if (sp > 1 && ws_bytes < (size_t)sp * m * m * sizeof(double)) {
     set_error("Gram workspace too small");
     return ENS_E_NOMEM;
   }
-  // G = S^T S: op(A) = S^T (TA = 1, lda = m), op(B) = S (TB = 0, ldb = m), K = n
-  dgemm<1, 0>(m, m, n, S, m, S, m, G, m, sp, (double*)workspace, stream);
+  // G = S^T S: op(A) = S^T, K = n; the blocks on and above the diagonal
+  const int64_t tm = tiles128(m), m64 = m;
+  const int64_t kchunk = ((n + sp - 1) / sp + 31) / 32 * 32;
+  const int nz = (int)((n + kchunk - 1) / kchunk);
+  double* parts = (double*)workspace;
+  hipLaunchKernelGGL((k_dgemm<1, 128, 16, true>), dim3((unsigned)(tm * (tm + 1) / 2), 1, (unsigned)nz), dim3(256), 0,
+                     stream, m64, m64, n, S, m64, S, m64, nz > 1 ? parts : G, m64, kchunk, m64 * m64);
+  if (nz > 1)
+    hipLaunchKernelGGL(k_sum_slices_sym, dim3((unsigned)((m + 31) / 32), (unsigned)((m + 31) / 32)), dim3(256), 0,
+                       stream, m64, nz, parts, m64 * m64, G);
   ENS_LAUNCH_CHECK();
   return ENS_OK;
 }
 
 ens_status ens_pod_eig_workspace_bytes(int32_t m, int32_t k, size_t* bytes) {
   ENS_ARG_CHECK(bytes && m >= 1 && k >= 1, "bad sizes");
-  *bytes = (size_t)(3 * (size_t)m * k + 3 * (size_t)k * k + 64) * sizeof(double);
+  *bytes = (size_t)(3 * (size_t)m * k + 3 * (size_t)k * k + 64 + eig_scratch(m, k)) * sizeof(double);
   return ENS_OK;
 }
 
@@ -473,18 +589,20 @@ ens_status ens_pod_eig(const double* G, int32_t m, int32_t k, int32_t r, const d
   double* H = T + (size_t)m * k;
   double* U = H + (size_t)k * k;
   int* flag = (int*)(U + 2 * (size_t)k * k);
+  double* parts = U + 2 * (size_t)k * k + 64;
+  const int sy = product_splits(m, k, m), sh = product_splits(k, k, m);
   ENS_HIP_TRY(hipMemcpyAsync(Y, start, (size_t)m * k * sizeof(double), hipMemcpyDeviceToDevice, stream));
   ENS_HIP_TRY(hipMemsetAsync(flag, 0, sizeof(int), stream));
   // power steps: Y <- G orth(Y)
   for (int it = 0; it < iters; ++it) {
     hipLaunchKernelGGL(k_orth, dim3(1), dim3(1024), 0, stream, m, k, Y, flag);
     ENS_HIP_TRY(hipMemcpyAsync(Q, Y, (size_t)m * k * sizeof(double), hipMemcpyDeviceToDevice, stream));
-    dgemm<0, 0>(m, k, m, G, m, Q, k, Y, k, 1, nullptr, stream);
+    dgemm<0>(m, k, m, G, m, Q, k, Y, sy, parts, stream);
   }
   // Rayleigh-Ritz on span(Y)
   hipLaunchKernelGGL(k_orth, dim3(1), dim3(1024), 0, stream, m, k, Y, flag);
-  dgemm<0, 0>(m, k, m, G, m, Y, k, T, k, 1, nullptr, stream);   // T = G Q
-  dgemm<1, 0>(k, k, m, Y, k, T, k, H, k, 1, nullptr, stream);   // H = Q^T G Q
+  dgemm<0>(m, k, m, G, m, Y, k, T, sy, parts, stream);   // T = G Q
+  dgemm<1>(k, k, m, Y, k, T, k, H, sh, parts, stream);   // H = Q^T G Q
   hipLaunchKernelGGL(k_jacobi, dim3(1), dim3(256), 0, stream, k, H, U, 12);
   hipLaunchKernelGGL(k_ritz_select, dim3(64), dim3(256), 0, stream, m, k, r, H, U, Y, V, lambda);
   ENS_LAUNCH_CHECK();
@@ -494,7 +612,7 @@ ens_status ens_pod_eig(const double* G, int32_t m, int32_t k, int32_t r, const d
 ens_status ens_pod_basis(const double* S, int64_t n, int32_t m, const double* V, const double* lambda, int32_t r,
                          double* Phi, hipStream_t stream) {
   ENS_ARG_CHECK(S && V && lambda && Phi && n >= 1 && m >= 1 && r >= 1 && r <= m, "bad basis arguments");
-  dgemm<0, 0>(n, r, m, S, m, V, r, Phi, r, 1, nullptr, stream);  // Phi = S V
+  dgemm<0>(n, r, m, S, m, V, r, Phi, 1, nullptr, stream);  // Phi = S V
   hipLaunchKernelGGL(k_scale_cols, dim3((unsigned)((n * r + 255) / 256)), dim3(256), 0, stream, n, r, Phi, lambda);
   hipLaunchKernelGGL(k_sign_cols, dim3((unsigned)r), dim3(256), 0, stream, n, r, Phi);
   ENS_LAUNCH_CHECK();
@@ -503,21 +621,21 @@ ens_status ens_pod_basis(const double* S, int64_t n, int32_t m, const double* V,
 
 ens_status ens_pod_project_workspace_bytes(int64_t n, int32_t r, int32_t s, size_t* bytes) {
   ENS_ARG_CHECK(bytes && n >= 1 && r >= 1 && s >= 1, "bad sizes");
-  *bytes = (size_t)gram_splits(n) * r * s * sizeof(double);
+  *bytes = (size_t)product_splits(s, r, n) * r * s * sizeof(double);
   return ENS_OK;
 }
 
 ens_status ens_pod_project(const double* Phi, const double* X, int64_t n, int32_t r, int32_t s, double* C,
                            void* workspace, size_t ws_bytes, hipStream_t stream) {
   ENS_ARG_CHECK(Phi && X && C && n >= 1 && r >= 1 && s >= 1, "bad projection arguments");
-  const int sp = gram_splits(n);
+  const int sp = product_splits(s, r, n);
   ENS_ARG_CHECK(sp == 1 || workspace, "null workspace");
   if (sp > 1 && ws_bytes < (size_t)sp * r * s * sizeof(double)) {
     set_error("projection workspace too small");
     return ENS_E_NOMEM;
   }
-  // C[e][j] = sum_i X[i][e] Phi[i][j]: op(A) = X^T (TA = 1, lda = s), op(B) = Phi
-  dgemm<1, 0>(s, r, n, X, s, Phi, r, C, r, sp, (double*)workspace, stream);
+  // C[e][j] = sum_i X[i][e] Phi[i][j]: op(A) = X^T
+  dgemm<1>(s, r, n, X, s, Phi, r, C, sp, (double*)workspace, stream);
   ENS_LAUNCH_CHECK();
   return ENS_OK;
 }

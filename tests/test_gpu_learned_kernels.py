@@ -78,3 +78,34 @@ def test_network_batches(E, B):
     b, bm, bv = dev(p), torch.zeros(L.P, device=DEV), torch.zeros(L.P, device=DEV)
     E.mlp_adam(b, g, bm, bv, 1, 1e-3)
     assert torch.equal(a, b) and torch.equal(am, bm) and torch.equal(av, bv) and torch.equal(lt, loss)
+
+
+def _abs_product_bound(a, b, terms):
+    """Elementwise bound on two FP64 evaluations of a @ b."""
+    return 2 * (terms + 2) * EPS * (a.abs() @ b.abs())
+
+
+# the 128-row blocks of the symmetric product: one block whole and ragged, one
+# past it, several; K below one range, ragged and split
+@pytest.mark.parametrize("n,m", [(1, 1), (7, 3), (31, 128), (500, 129), (2000, 96), (700, 300), (9000, 257)])
+def test_gram(E, n, m):
+    S = _rand((n, m), n + m)
+    G = E.pod_gram(S)
+    assert bool(((G - S.t() @ S).abs() <= _abs_product_bound(S.t(), S, n)).all())
+    assert torch.equal(G, G.t().contiguous())
+
+
+# narrow, middle and wide right operands (the three tile widths and one past
+# each), ragged rows and K
+@pytest.mark.parametrize("n,m,r", [(1, 4, 4), (300, 40, 33), (129, 70, 64), (1000, 130, 65), (513, 200, 129),
+                                   (40, 32, 32), (5000, 96, 16)])
+def test_basis_and_projection_products(E, n, m, r):
+    S, V, lam = _rand((n, m), 5), _rand((m, r), 6), _rand(r, 7).abs() + 0.5
+    Phi = E.pod_basis(S, V, lam)
+    ref, b = (S @ V) / lam.sqrt(), _abs_product_bound(S, V, m + 4) / lam.sqrt()
+    sign = torch.sign(Phi.gather(0, Phi.abs().argmax(0)[None, :]))
+    assert bool((sign > 0).all())
+    flip = torch.sign((ref * Phi).sum(0))
+    assert bool(((Phi - flip * ref).abs() <= b).all())
+    C = E.pod_project(Phi, S)
+    assert bool(((C - S.t() @ Phi).abs() <= _abs_product_bound(S.t(), Phi, n)).all())
