@@ -165,172 +165,417 @@ __global__ __launch_bounds__(256) void k_sum_slices_sym(int64_t m, int nz, const
   }
 }
 
-// Orthonormalise the k columns of Y [m][k] (row-major) in place, one
-// workgroup: classical Gram-Schmidt applied twice per column (CGS2), the k
-// projections of a pass computed by the wavefronts in parallel and applied
-// in ascending column order.  A column whose norm falls below 1e-14 of the
-// first column's is reported through *rank_deficient.
-__global__ __launch_bounds__(1024) void k_orth(int m, int k, double* __restrict__ Y, int* __restrict__ rank_def) {
-  __shared__ double d[256];
-  __shared__ double red[16];
-  __shared__ double s_norm;
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6, nw = blockDim.x >> 6;
-  double first = 0.0;
-  for (int j = 0; j < k; ++j) {
-    for (int pass = 0; pass < 2; ++pass) {
-      for (int i = wave; i < j; i += nw) {
-        double sum = 0.0;
-        for (int r = lane; r < m; r += 64) sum += Y[(int64_t)r * k + i] * Y[(int64_t)r * k + j];
+// Orthonormalise the k columns of Y [m][k] (row-major) in place: block
+// Gram-Schmidt over panels of 16 columns, each panel taken twice through
+// "project out the panels before it, then orthonormalise it inside", which
+// leaves the columns orthonormal to rounding (the second round finds them so
+// to about 1e-11 and cleans up).  Between two power steps a basis that close
+// to orthonormal does as well, so there (`once`) the second round is left out
+// for a panel whose columns kept at least 1 % of their length in the first.  One workgroup of 16 wavefronts does it all:
+// the time is a chain of reductions over m, and Y (1 MB for 2048 x 64) stays
+// in L2.  Projections, panel Gram matrices and the updates are 16 x 16 tiles
+// on the FP64 matrix cores, whose reads of Y are whole 128-byte pieces of
+// rows; the columns one at a time, each product a strided pass, took 11.1 ms
+// for 2048 x 64, now 0.58 ms, and 0.30 ms with one round a panel.
+// Inside a panel: Y R^-1 from the Cholesky factor of its Gram matrix (columns
+// scaled to length one first) when every column keeps at least 1 % of its
+// length off the columns before it, so the factor is accurate; otherwise
+// column by column, classical Gram-Schmidt twice each, which also takes
+// columns that are dependent to rounding (a zero column stays zero).
+constexpr int kPanel = 16;
+constexpr int kOrthWaves = 8, kOrthThreads = 64 * kOrthWaves;
+constexpr double kCholeskyMin = 1e-4;  // least squared length off the columns before
+
+struct OrthLds {
+  double red[kOrthWaves][256];            // per-wavefront tiles or sums
+  double d[256 * kPanel];         // projections onto the columns before the panel
+  double w[kPanel * kPanel];      // the panel's Gram matrix
+  double rinv[kPanel * kPanel];
+  double col[kPanel];
+  int ok, clean;  // Cholesky is accurate; and the projection left every column most of its length
+};
+
+// Tiles t0 .. t0 + NT - 1 of X^T Yp, X the columns 16 t of Y (PANEL: Yp
+// itself), into out[16 (t - t0) + i][j].
+template <int NT, bool PANEL>
+__device__ inline void orth_dots(int m, int k, const double* Y, int t0, int j0, int b, OrthLds& s, double* out) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 15, q = lane >> 4;
+  f64x4 acc[NT];
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
-        if (lane == 0) d[i] = sum;
-      }
-      __syncthreads();
-      for (int r = t; r < m; r += blockDim.x) {
-        double v = Y[(int64_t)r * k + j];
-        for (int i = 0; i < j; ++i) v -= d[i] * Y[(int64_t)r * k + i];
-        Y[(int64_t)r * k + j] = v;
-      }
-      __syncthreads();
-    }
-    double sum = 0.0;
-    for (int r = t; r < m; r += blockDim.x) sum += Y[(int64_t)r * k + j] * Y[(int64_t)r * k + j];
+  for (int u = 0; u < NT; ++u) acc[u] = (f64x4)0.0;
+  for (int row0 = 4 * wave; row0 < m; row0 += 16 * kOrthWaves) {  // the operands of four steps in flight
+    double bv[4], av[4][NT];
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
-    if (lane == 0) red[wave] = sum;
-    __syncthreads();
-    if (t == 0) {
-      double tot = 0.0;
-      for (int w = 0; w < nw; ++w) tot += red[w];
-      s_norm = sqrt(tot);
+    for (int v = 0; v < 4; ++v) {
+      const int row = row0 + 4 * kOrthWaves * v + q;
+      const double* yr = Y + (int64_t)row * k;
+      bv[v] = (row < m && r < b) ? yr[j0 + r] : 0.0;
+#pragma unroll
+      for (int u = 0; u < NT; ++u) av[v][u] = PANEL ? bv[v] : (row < m ? yr[16 * (t0 + u) + r] : 0.0);
     }
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+      for (int u = 0; u < NT; ++u) acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[v][u], bv[v], acc[u], 0, 0, 0);
+  }
+#pragma unroll
+  for (int u = 0; u < NT; ++u) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s.red[wave][(q + 4 * i) * 16 + r] = acc[u][i];
     __syncthreads();
-    const double nrm = s_norm;
-    if (j == 0) first = nrm;
-    if (t == 0 && (!(nrm > 1e-300) || nrm < 1e-14 * first)) *rank_def = 1;
-    const double inv = nrm > 0.0 ? 1.0 / nrm : 0.0;
-    for (int r = t; r < m; r += blockDim.x) Y[(int64_t)r * k + j] *= inv;
+    if (threadIdx.x < 256) {
+      double v = 0.0;
+#pragma unroll
+      for (int w = 0; w < kOrthWaves; ++w) v += s.red[w][threadIdx.x];
+      out[u * 256 + threadIdx.x] = v;
+    }
     __syncthreads();
   }
 }
 
-// Cyclic Jacobi on a symmetric k x k matrix H (row-major, in place), one
-// workgroup; the rotation angles are computed by thread 0 and applied to
-// rows/columns in parallel.  On exit the diagonal of H holds the
-// eigenvalues and U [k][k] the eigenvectors (columns).
-__global__ __launch_bounds__(256) void k_jacobi(int k, double* __restrict__ H, double* __restrict__ U, int sweeps) {
-  __shared__ double s_c, s_s;
-  __shared__ int s_skip;
-  const int t = threadIdx.x;
-  for (int i = t; i < k * k; i += blockDim.x) U[i] = (i / k == i % k) ? 1.0 : 0.0;
+// R^-1 of the panel's Gram matrix by elimination on [W | 1] in the registers
+// of one wavefront: lane (row i = lane % 16, columns 8 (lane / 16) .. + 7).
+// Sets s.ok and s.clean (j0 columns were projected out).
+__device__ inline void orth_cholesky(int j0, int b, OrthLds& s) {
+  const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
+  // unit columns; columns past the panel count as unit vectors of their own
+  const double wii = i < b ? s.w[i * 17] : 1.0;
+  const double sc = 1.0 / sqrt(wii);
+  double a[8];
+#pragma unroll
+  for (int v = 0; v < 8; ++v) {
+    const int c = 8 * g + v;
+    const double sj = __shfl(sc, c & 15, 64);
+    a[v] = c >= 16 ? (c - 16 == i ? 1.0 : 0.0)
+                   : (i == c ? 1.0 : (i < b && c < b ? s.w[i * 16 + c] * sc * sj : 0.0));
+  }
+  bool ok = wii > 0.0 && wii < INFINITY;
+  double dii = 1.0;
+#pragma unroll
+  for (int p = 0; p < 16; ++p) {
+    const double piv = __shfl(a[p & 7], p + 16 * (p >> 3), 64);
+    const double f = __shfl(a[p & 7], i + 16 * (p >> 3), 64) / piv;
+    ok = ok && piv >= kCholeskyMin;
+    if (i == p) dii = piv;
+#pragma unroll
+    for (int v = 0; v < 8; ++v) {
+      const double pr = __shfl(a[v], p + 16 * g, 64);
+      if (i > p) a[v] -= f * pr;
+    }
+  }
+  const double rs = 1.0 / sqrt(dii);
+#pragma unroll
+  for (int v = 0; v < 8; ++v) {
+    const int l = (8 * g + v) & 15;
+    const double sl = __shfl(sc, l, 64);
+    if (g >= 2) s.rinv[l * 16 + i] = a[v] * rs * sl;
+  }
+  double off = 0.0;  // what the projection took off column i, squared
+  for (int row = g; row < j0; row += 4) off += s.d[row * 16 + i] * s.d[row * 16 + i];
+  off += __shfl_xor(off, 16, 64);
+  off += __shfl_xor(off, 32, 64);
+  const int all_ok = __all(ok), all_clean = __all(ok && wii >= kCholeskyMin * off);
+  if (lane == 0) {
+    s.ok = all_ok;
+    s.clean = all_clean;
+  }
+}
+
+// Block-wide sums of v[0 .. n-1] over the workgroup's lanes, to s.col.
+template <int NV>
+__device__ inline void orth_sums(const double (&v)[NV], int n, OrthLds& s) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int i = 0; i < NV; ++i)
+    if (i < n) {
+      double t = v[i];
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+      if (lane == 0) s.red[wave][i] = t;
+    }
+  __syncthreads();
+  if ((int)threadIdx.x < n) {
+    double t = 0.0;
+    for (int w = 0; w < kOrthWaves; ++w) t += s.red[w][threadIdx.x];
+    s.col[threadIdx.x] = t;
+  }
+  __syncthreads();
+}
+
+__global__ __launch_bounds__(kOrthThreads) void k_orth(int m, int k, double* Y, int once) {
+  __shared__ OrthLds s;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6, r = lane & 15, q = lane >> 4;
+  const int tiles = (m + 15) / 16;
+  for (int j0 = 0; j0 < k; j0 += kPanel) {
+    const int b = k - j0 < kPanel ? k - j0 : kPanel;
+    for (int round = 0; round < 2; ++round) {
+      if (j0 > 0) {
+        int t0 = 0;
+        for (; t0 + 2 <= j0 / 16; t0 += 2) orth_dots<2, false>(m, k, Y, t0, j0, b, s, s.d + t0 * 256);
+        for (; t0 < j0 / 16; ++t0) orth_dots<1, false>(m, k, Y, t0, j0, b, s, s.d + t0 * 256);
+        for (int tl = wave; tl < tiles; tl += kOrthWaves) {
+          const int ra = 16 * tl + r;
+          f64x4 acc;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int row = 16 * tl + q + 4 * i;
+            acc[i] = (row < m && r < b) ? Y[(int64_t)row * k + j0 + r] : 0.0;
+          }
+          for (int k0 = 0; k0 < j0; k0 += 16) {
+            double av[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) av[v] = ra < m ? -Y[(int64_t)ra * k + k0 + 4 * v + q] : 0.0;
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+              acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[v], s.d[(k0 + 4 * v + q) * 16 + r], acc, 0, 0, 0);
+          }
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int row = 16 * tl + q + 4 * i;
+            if (row < m && r < b) Y[(int64_t)row * k + j0 + r] = acc[i];
+          }
+        }
+        __syncthreads();
+      }
+      orth_dots<1, true>(m, k, Y, 0, j0, b, s, s.w);
+      if (wave == 0) orth_cholesky(j0, b, s);
+      __syncthreads();
+      if (s.ok) {
+        for (int tl = wave; tl < tiles; tl += kOrthWaves) {
+          const int ra = 16 * tl + r;
+          f64x4 acc = (f64x4)0.0;
+#pragma unroll
+          for (int kk = 0; kk < 16; kk += 4) {
+            const double av = (ra < m && kk + q < b) ? Y[(int64_t)ra * k + j0 + kk + q] : 0.0;
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, s.rinv[(kk + q) * 16 + r], acc, 0, 0, 0);
+          }
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int row = 16 * tl + q + 4 * i;
+            if (row < m && r < b) Y[(int64_t)row * k + j0 + r] = acc[i];
+          }
+        }
+      } else {
+        for (int j = 0; j < b; ++j) {
+          for (int pass = 0; pass < 2 && j > 0; ++pass) {
+            double acc[kPanel];
+#pragma unroll
+            for (int i = 0; i < kPanel; ++i) acc[i] = 0.0;
+#pragma unroll 1
+            for (int row = t; row < m; row += kOrthThreads) {
+              const double* yr = Y + (int64_t)row * k + j0;
+              const double yj = yr[j];
+#pragma unroll
+              for (int i = 0; i < kPanel; ++i)
+                if (i < j) acc[i] += yr[i] * yj;
+            }
+            orth_sums(acc, j, s);
+            for (int row = t; row < m; row += kOrthThreads) {
+              double* yr = Y + (int64_t)row * k + j0;
+              double v = yr[j];
+              for (int i = 0; i < j; ++i) v -= s.col[i] * yr[i];
+              yr[j] = v;
+            }
+          }
+          double sq[1] = {0.0};
+          for (int row = t; row < m; row += kOrthThreads) {
+            const double v = Y[(int64_t)row * k + j0 + j];
+            sq[0] += v * v;
+          }
+          orth_sums(sq, 1, s);
+          const double nrm = sqrt(s.col[0]), inv = nrm > 0.0 ? 1.0 / nrm : 0.0;
+          for (int row = t; row < m; row += kOrthThreads) Y[(int64_t)row * k + j0 + j] *= inv;
+          __syncthreads();
+        }
+      }
+      const int done = once && s.clean;
+      __syncthreads();
+      if (done) break;
+    }
+  }
+}
+
+// Jacobi on a symmetric k x k matrix H (row-major, in place), one workgroup;
+// on exit the diagonal of H holds the eigenvalues and U [k][k] the
+// eigenvectors (columns).  A sweep is k - 1 rounds (k even; an odd one has an
+// idle index) of k / 2 rotations of disjoint pairs, the round-robin order: the
+// angles of a round come from one lane each, then every 2 x 2 block of rows
+// of one pair and columns of another is rotated from both sides by one lane,
+// so a round is two barriers where the cyclic order takes three for each of
+// its rotations.  Sweeps end when one rotates nothing (entries at most 1e-18
+// of their diagonals' geometric mean), at most `sweeps`.  H and U lie in LDS
+// up to k = 96 (LDS: 2 k^2 doubles).  k = 64: 0.48 ms, against 11.6 ms for the
+// cyclic order's 12 sweeps in L2.
+constexpr int kJacobiLdsK = 96;
+
+template <bool LDS>
+__global__ __launch_bounds__(1024) void k_jacobi(int k, double* Hg, double* Ug, int sweeps) {
+  extern __shared__ double s_hu[];
+  __shared__ double s_c[128], s_s[128];
+  __shared__ short s_p[128], s_q[128];
+  __shared__ int s_any;
+  double* H = LDS ? s_hu : Hg;
+  double* U = LDS ? s_hu + k * k : Ug;
+  const int t = threadIdx.x, nt = blockDim.x;
+  const int k2 = k + (k & 1), pairs = k2 / 2;
+  for (int i = t; i < k * k; i += nt) {
+    if (LDS) H[i] = Hg[i];
+    U[i] = (i / k == i % k) ? 1.0 : 0.0;
+  }
   __syncthreads();
   for (int sw = 0; sw < sweeps; ++sw) {
-    for (int p = 0; p < k - 1; ++p)
-      for (int q = p + 1; q < k; ++q) {
-        if (t == 0) {
+    if (t == 0) s_any = 0;
+    for (int round = 0; round < k2 - 1; ++round) {
+      __syncthreads();
+      if (t < pairs) {
+        // round-robin: index k2 - 1 stays, the others move round by one
+        const int x = t == 0 ? k2 - 1 : (round + t) % (k2 - 1);
+        const int y = (round + (k2 - 1) - t) % (k2 - 1);
+        const int p = x < y ? x : y, q = x < y ? y : x;
+        double c = 1.0, s = 0.0;
+        if (q < k) {
           const double apq = H[p * k + q], app = H[p * k + p], aqq = H[q * k + q];
-          if (fabs(apq) <= 1e-300 || fabs(apq) <= 1e-18 * sqrt(fabs(app * aqq))) {
-            s_skip = 1;
-          } else {
+          if (!(fabs(apq) <= 1e-300 || fabs(apq) <= 1e-18 * sqrt(fabs(app * aqq)))) {
             const double tau = (aqq - app) / (2.0 * apq);
             const double tt = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-            s_c = 1.0 / sqrt(1.0 + tt * tt);
-            s_s = tt * s_c;
-            s_skip = 0;
+            c = 1.0 / sqrt(1.0 + tt * tt);
+            s = tt * c;
+            s_any = 1;
           }
         }
-        __syncthreads();
-        if (!s_skip) {
-          const double c = s_c, s = s_s;
-          // rows p, q of H
-          for (int j = t; j < k; j += blockDim.x) {
-            const double hp = H[p * k + j], hq = H[q * k + j];
-            H[p * k + j] = c * hp - s * hq;
-            H[q * k + j] = s * hp + c * hq;
-          }
-          __syncthreads();
-          // columns p, q of H and of U
-          for (int i = t; i < k; i += blockDim.x) {
-            const double hp = H[i * k + p], hq = H[i * k + q];
-            H[i * k + p] = c * hp - s * hq;
-            H[i * k + q] = s * hp + c * hq;
-            const double up = U[i * k + p], uq = U[i * k + q];
-            U[i * k + p] = c * up - s * uq;
-            U[i * k + q] = s * up + c * uq;
-          }
-        }
-        __syncthreads();
+        s_p[t] = (short)p;
+        s_q[t] = (short)q;
+        s_c[t] = c;
+        s_s[t] = s;
       }
-  }
-}
-
-// Sort the Jacobi result by eigenvalue descending; V[m][r] = Q U[:, top r],
-// lambda[r].
-__global__ void k_ritz_select(int m, int k, int r, const double* __restrict__ H, const double* __restrict__ U,
-                              const double* __restrict__ Q, double* __restrict__ V, double* __restrict__ lambda) {
-  __shared__ int order[256];
-  if (threadIdx.x == 0) {
-    for (int i = 0; i < k; ++i) order[i] = i;
-    for (int i = 0; i < k; ++i)  // selection sort, k <= 256
-      for (int j = i + 1; j < k; ++j)
-        if (H[order[j] * k + order[j]] > H[order[i] * k + order[i]]) {
-          const int tmp = order[i];
-          order[i] = order[j];
-          order[j] = tmp;
-        }
-    for (int j = 0; j < r; ++j) lambda[j] = H[order[j] * k + order[j]];
-  }
-  __syncthreads();
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < (int64_t)m * r;
-       t += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t i = t / r;
-    const int j = (int)(t % r), c = order[j];
-    double s = 0.0;
-    for (int l = 0; l < k; ++l) s += Q[i * k + l] * U[l * k + c];
-    V[t] = s;
-  }
-}
-
-// Phi columns scaled by lambda^(-1/2) (in place on the S V product).
-__global__ void k_scale_cols(int64_t n, int r, double* __restrict__ P, const double* __restrict__ lambda) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n * r) return;
-  P[t] *= 1.0 / sqrt(lambda[t % r]);
-}
-
-// Sign rule: the largest-magnitude entry of every column is positive (ties:
-// the lowest row).  One workgroup per column.
-__global__ __launch_bounds__(256) void k_sign_cols(int64_t n, int r, double* __restrict__ P) {
-  __shared__ double bv[256];
-  __shared__ int64_t bi[256];
-  const int j = blockIdx.x;
-  double best = -1.0;
-  int64_t besti = 0;
-  for (int64_t i = threadIdx.x; i < n; i += blockDim.x) {
-    const double a = fabs(P[i * r + j]);
-    if (a > best) {
-      best = a;
-      besti = i;
-    }
-  }
-  bv[threadIdx.x] = best;
-  bi[threadIdx.x] = besti;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) {
-      const double o = bv[threadIdx.x + s];
-      const int64_t oi = bi[threadIdx.x + s];
-      if (o > bv[threadIdx.x] || (o == bv[threadIdx.x] && oi < bi[threadIdx.x])) {
-        bv[threadIdx.x] = o;
-        bi[threadIdx.x] = oi;
+      __syncthreads();
+      for (int i = t; i < pairs * pairs; i += nt) {
+        const int a = i / pairs, b = i % pairs;
+        const double ca = s_c[a], sa = s_s[a], cb = s_c[b], sb = s_s[b];
+        if (sa == 0.0 && sb == 0.0) continue;
+        const int p = s_p[a], q = s_q[a], u = s_p[b], v = s_q[b];
+        const bool qk = q < k, vk = v < k;
+        // rows p, q by the pair a's rotation, then columns u, v by b's
+        const double hpu = H[p * k + u], hpv = vk ? H[p * k + v] : 0.0;
+        const double hqu = qk ? H[q * k + u] : 0.0, hqv = qk && vk ? H[q * k + v] : 0.0;
+        const double rpu = ca * hpu - sa * hqu, rpv = ca * hpv - sa * hqv;
+        const double rqu = sa * hpu + ca * hqu, rqv = sa * hpv + ca * hqv;
+        const bool own = a == b;  // its off-diagonal entries are what the rotation removes
+        H[p * k + u] = cb * rpu - sb * rpv;
+        if (vk) H[p * k + v] = own && sa != 0.0 ? 0.0 : sb * rpu + cb * rpv;
+        if (qk) H[q * k + u] = own && sa != 0.0 ? 0.0 : cb * rqu - sb * rqv;
+        if (qk && vk) H[q * k + v] = sb * rqu + cb * rqv;
+      }
+      for (int i = t; i < k * pairs; i += nt) {
+        const int row = i / pairs, b = i % pairs;
+        const double cb = s_c[b], sb = s_s[b];
+        if (sb == 0.0) continue;
+        const int u = s_p[b], v = s_q[b];
+        const double up = U[row * k + u], uq = U[row * k + v];
+        U[row * k + u] = cb * up - sb * uq;
+        U[row * k + v] = sb * up + cb * uq;
       }
     }
     __syncthreads();
+    const int any = s_any;
+    __syncthreads();
+    if (!any) break;
   }
-  const bool flip = P[bi[0] * r + j] < 0.0;
+  if (LDS)
+    for (int i = t; i < k * k; i += nt) {
+      Hg[i] = H[i];
+      Ug[i] = U[i];
+    }
+}
+
+// Sort the Jacobi result by eigenvalue descending (equal ones by index);
+// V[m][r] = Q U[:, top r], lambda[r].
+__global__ __launch_bounds__(256) void k_ritz_select(int m, int k, int r, const double* __restrict__ H,
+                                                     const double* __restrict__ U, const double* __restrict__ Q,
+                                                     double* __restrict__ V, double* __restrict__ lambda) {
+  __shared__ double diag[256];
+  __shared__ int order[256];
+  const int t = threadIdx.x;  // k <= 256
+  order[t] = 0;               // (a NaN ranks nowhere)
+  if (t < k) diag[t] = H[t * k + t];
   __syncthreads();
-  if (flip)
-    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) P[i * r + j] = -P[i * r + j];
+  if (t < k) {
+    int rank = 0;
+    for (int j = 0; j < k; ++j) rank += diag[j] > diag[t] || (diag[j] == diag[t] && j < t);
+    order[rank] = t;
+  }
+  __syncthreads();
+  if (blockIdx.x == 0 && t < r) lambda[t] = diag[order[t]];
+  for (int64_t x = (int64_t)blockIdx.x * blockDim.x + t; x < (int64_t)m * r; x += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t i = x / r;
+    const int c = order[x % r];
+    double s = 0.0;
+    for (int l = 0; l < k; ++l) s += Q[i * k + l] * U[l * k + c];
+    V[x] = s;
+  }
+}
+
+// Phi columns scaled by lambda^(-1/2), in place on the S V product, with the
+// sign rule: the largest-magnitude entry of every column is positive (ties: the
+// lowest row).  One workgroup per column; each of its loads touches as many
+// lines as it has lanes, and the rate at which one CU takes such misses bounds
+// it (1.05 ms at 64^3 for reading twice and writing once; 1.18 ms for the sign
+// alone with one load in flight a lane, and a pass of its own for the scale).
+__global__ __launch_bounds__(1024) void k_scale_sign_cols(int64_t n, int r, double* __restrict__ P,
+                                                          const double* __restrict__ lambda) {
+  constexpr int NT = 1024, D = 8;
+  __shared__ double bv[NT / 64], bs[NT / 64];
+  __shared__ int64_t bi[NT / 64];
+  const int j = blockIdx.x, t = threadIdx.x;
+  const double inv = 1.0 / sqrt(lambda[j]);
+  double best = -1.0, bval = 0.0;
+  int64_t besti = 0;
+  for (int64_t i0 = t; i0 < n; i0 += NT * D) {
+    double v[D];
+#pragma unroll
+    for (int d = 0; d < D; ++d) v[d] = i0 + NT * d < n ? P[(i0 + NT * d) * r + j] : 0.0;
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      const double a = v[d] * inv;
+      if (i0 + NT * d < n && fabs(a) > best) {
+        best = fabs(a);
+        bval = a;
+        besti = i0 + NT * d;
+      }
+    }
+  }
+  auto take = [&](double o, double ov, int64_t oi) {
+    if (o > best || (o == best && oi < besti)) {
+      best = o;
+      bval = ov;
+      besti = oi;
+    }
+  };
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    const double o = __shfl_xor(best, off, 64), ov = __shfl_xor(bval, off, 64);
+    const int64_t oi = __shfl_xor((long long)besti, off, 64);
+    take(o, ov, oi);
+  }
+  if ((t & 63) == 0) {
+    bv[t >> 6] = best;
+    bs[t >> 6] = bval;
+    bi[t >> 6] = besti;
+  }
+  __syncthreads();
+  best = bv[0];
+  bval = bs[0];
+  besti = bi[0];
+  for (int w = 1; w < NT / 64; ++w) take(bv[w], bs[w], bi[w]);
+  const bool flip = bval < 0.0;
+  for (int64_t i0 = t; i0 < n; i0 += NT * D) {
+    double v[D];
+#pragma unroll
+    for (int d = 0; d < D; ++d) v[d] = i0 + NT * d < n ? P[(i0 + NT * d) * r + j] : 0.0;
+#pragma unroll
+    for (int d = 0; d < D; ++d)
+      if (i0 + NT * d < n) P[(i0 + NT * d) * r + j] = flip ? -(v[d] * inv) : v[d] * inv;
+  }
 }
 
 // S[i][col0 + e] = x[i][e]
@@ -425,42 +670,60 @@ __global__ __launch_bounds__(256) void k_reconstruct_mfma(int64_t n, int r, int 
   }
 }
 
-// Per-column mean and standard deviation of C [m][r] (one thread per
-// column, rows in order) and the standardised targets T = (C - mu) / sd.
-// Mean and standard deviation of each coefficient over the m snapshots
-// (one lane per coefficient, one workgroup), the scale of each coefficient
-// its own deviation or (common) the largest of them, and the network
-// targets T = (C - mu) / scale.  With one common scale the targets keep the
-// coefficients' relative sizes, so the network's squared error is the
-// squared error of the lifted guess in the orthonormal basis.
-__global__ void k_standardize(int m, int r, int common, const double* __restrict__ C, double* __restrict__ mu,
-                              double* __restrict__ sd, float* __restrict__ T) {
-  __shared__ double s_dev[1024];
-  const int j = threadIdx.x;
-  double mean = 0.0, dev = 0.0;
-  if (j < r) {
-    double s1 = 0.0;
-    for (int i = 0; i < m; ++i) s1 += C[(int64_t)i * r + j];
-    mean = s1 / m;
-    double s2 = 0.0;
-    for (int i = 0; i < m; ++i) {
-      const double d = C[(int64_t)i * r + j] - mean;
-      s2 += d * d;
+// Mean and standard deviation of each coefficient over the m snapshots, the
+// scale of each coefficient its own deviation or (common) the largest of them,
+// and the network targets T = (C - mu) / scale.  With one common scale the
+// targets keep the coefficients' relative sizes, so the network's squared
+// error is the squared error of the lifted guess in the orthonormal basis.
+// One workgroup: 1024 / r lanes a coefficient, each on a stride of the rows,
+// their sums added in lane order (one lane a coefficient: 980 us for 2048 x 32,
+// now 33 us).
+__global__ __launch_bounds__(1024) void k_standardize(int m, int r, int common, const double* __restrict__ C,
+                                                      double* __restrict__ mu, double* __restrict__ sd,
+                                                      float* __restrict__ T) {
+  __shared__ double s_part[1024];
+  __shared__ double s_mean[1024], s_dev[1024];
+  const int t = threadIdx.x, G = 1024 / r, j = t % r, g = t / r;
+  const bool live = g < G;
+  auto column_sum = [&](auto term) -> double {  // the column's sum, for the lanes t < r
+    double s = 0.0;
+    if (live) {
+      int i = g;
+      for (; i + 3 * G < m; i += 4 * G) {
+        const double v0 = C[(int64_t)i * r + j], v1 = C[(int64_t)(i + G) * r + j];
+        const double v2 = C[(int64_t)(i + 2 * G) * r + j], v3 = C[(int64_t)(i + 3 * G) * r + j];
+        s += (term(v0) + term(v1)) + (term(v2) + term(v3));
+      }
+      for (; i < m; i += G) s += term(C[(int64_t)i * r + j]);
     }
-    dev = sqrt(s2 / m);
-  }
-  s_dev[j] = dev;
+    s_part[t] = s;
+    __syncthreads();
+    double tot = 0.0;
+    if (t < r)
+      for (int h = 0; h < G; ++h) tot += s_part[h * r + t];
+    __syncthreads();
+    return tot;
+  };
+  const double s1 = column_sum([](double v) { return v; });
+  if (t < r) s_mean[t] = s1 / m;
   __syncthreads();
+  const double mean = s_mean[j];
+  const double s2 = column_sum([&](double v) { return (v - mean) * (v - mean); });
+  if (t < r) s_dev[t] = sqrt(s2 / m);
+  __syncthreads();
+  double dev = s_dev[j];
   if (common) {
     double mx = 0.0;
-    for (int k = 0; k < r; ++k) mx = s_dev[k] > mx ? s_dev[k] : mx;
+    for (int i = 0; i < r; ++i) mx = s_dev[i] > mx ? s_dev[i] : mx;
     dev = mx;
   }
   if (!(dev > 0.0)) dev = 1.0;
-  if (j >= r) return;
-  mu[j] = mean;
-  sd[j] = dev;
-  for (int i = 0; i < m; ++i) T[(int64_t)i * r + j] = (float)((C[(int64_t)i * r + j] - mean) / dev);
+  if (t < r) {
+    mu[t] = mean;
+    sd[t] = dev;
+  }
+  if (live)
+    for (int i = g; i < m; i += G) T[(int64_t)i * r + j] = (float)((C[(int64_t)i * r + j] - mean) / dev);
 }
 
 // ------------------------------------------------------------ host side ---
@@ -588,22 +851,25 @@ ens_status ens_pod_eig(const double* G, int32_t m, int32_t k, int32_t r, const d
   double* T = Q + (size_t)m * k;
   double* H = T + (size_t)m * k;
   double* U = H + (size_t)k * k;
-  int* flag = (int*)(U + 2 * (size_t)k * k);
   double* parts = U + 2 * (size_t)k * k + 64;
   const int sy = product_splits(m, k, m), sh = product_splits(k, k, m);
   ENS_HIP_TRY(hipMemcpyAsync(Y, start, (size_t)m * k * sizeof(double), hipMemcpyDeviceToDevice, stream));
-  ENS_HIP_TRY(hipMemsetAsync(flag, 0, sizeof(int), stream));
-  // power steps: Y <- G orth(Y)
+  // power steps: Y <- G orth(Y), between two buffers
   for (int it = 0; it < iters; ++it) {
-    hipLaunchKernelGGL(k_orth, dim3(1), dim3(1024), 0, stream, m, k, Y, flag);
-    ENS_HIP_TRY(hipMemcpyAsync(Q, Y, (size_t)m * k * sizeof(double), hipMemcpyDeviceToDevice, stream));
-    dgemm<0>(m, k, m, G, m, Q, k, Y, sy, parts, stream);
+    hipLaunchKernelGGL(k_orth, dim3(1), dim3(kOrthThreads), 0, stream, m, k, Y, 1);
+    dgemm<0>(m, k, m, G, m, Y, k, Q, sy, parts, stream);
+    double* const tmp = Y;
+    Y = Q;
+    Q = tmp;
   }
   // Rayleigh-Ritz on span(Y)
-  hipLaunchKernelGGL(k_orth, dim3(1), dim3(1024), 0, stream, m, k, Y, flag);
+  hipLaunchKernelGGL(k_orth, dim3(1), dim3(kOrthThreads), 0, stream, m, k, Y, 0);
   dgemm<0>(m, k, m, G, m, Y, k, T, sy, parts, stream);   // T = G Q
   dgemm<1>(k, k, m, Y, k, T, k, H, sh, parts, stream);   // H = Q^T G Q
-  hipLaunchKernelGGL(k_jacobi, dim3(1), dim3(256), 0, stream, k, H, U, 12);
+  if (k <= kJacobiLdsK)
+    hipLaunchKernelGGL(k_jacobi<true>, dim3(1), dim3(1024), 2 * (size_t)k * k * sizeof(double), stream, k, H, U, 12);
+  else
+    hipLaunchKernelGGL(k_jacobi<false>, dim3(1), dim3(1024), 0, stream, k, H, U, 12);
   hipLaunchKernelGGL(k_ritz_select, dim3(64), dim3(256), 0, stream, m, k, r, H, U, Y, V, lambda);
   ENS_LAUNCH_CHECK();
   return ENS_OK;
@@ -613,8 +879,7 @@ ens_status ens_pod_basis(const double* S, int64_t n, int32_t m, const double* V,
                          double* Phi, hipStream_t stream) {
   ENS_ARG_CHECK(S && V && lambda && Phi && n >= 1 && m >= 1 && r >= 1 && r <= m, "bad basis arguments");
   dgemm<0>(n, r, m, S, m, V, r, Phi, 1, nullptr, stream);  // Phi = S V
-  hipLaunchKernelGGL(k_scale_cols, dim3((unsigned)((n * r + 255) / 256)), dim3(256), 0, stream, n, r, Phi, lambda);
-  hipLaunchKernelGGL(k_sign_cols, dim3((unsigned)r), dim3(256), 0, stream, n, r, Phi);
+  hipLaunchKernelGGL(k_scale_sign_cols, dim3((unsigned)r), dim3(1024), 0, stream, n, r, Phi, lambda);
   ENS_LAUNCH_CHECK();
   return ENS_OK;
 }
@@ -662,8 +927,7 @@ ens_status ens_pod_reconstruct(const double* Phi, int64_t n, int32_t r, const fl
 ens_status ens_pod_standardize(const double* C, int32_t m, int32_t r, int32_t common, double* mu, double* sd,
                                float* T, hipStream_t stream) {
   ENS_ARG_CHECK(C && mu && sd && T && m >= 1 && r >= 1 && r <= 1024, "bad standardize arguments");
-  hipLaunchKernelGGL(k_standardize, dim3(1), dim3((unsigned)((r + 63) / 64 * 64)), 0, stream, m, r, common, C, mu,
-                     sd, T);
+  hipLaunchKernelGGL(k_standardize, dim3(1), dim3(1024), 0, stream, m, r, common, C, mu, sd, T);
   ENS_LAUNCH_CHECK();
   return ENS_OK;
 }

@@ -109,3 +109,41 @@ def test_basis_and_projection_products(E, n, m, r):
     assert bool(((Phi - flip * ref).abs() <= b).all())
     C = E.pod_project(Phi, S)
     assert bool(((C - S.t() @ Phi).abs() <= _abs_product_bound(S.t(), Phi, n)).all())
+
+
+# panels of 16 columns whole and ragged, one panel and many, few rows, rows past
+# a workgroup's; spectra that fall slowly, fast enough that the first power
+# step's columns are dependent to 1e-2 of their length or to rounding, and with
+# exact zeros; k on both sides of what the rotations keep in LDS, and odd.
+# Columns orthonormal to 64 k roundings; eigenpair residuals and eigenvalues
+# to m k roundings of the largest eigenvalue where the iteration has converged.
+@pytest.mark.parametrize("m,k,r,ratio,rank", [
+    (1, 1, 1, 2.0, 1), (5, 3, 2, 30.0, 5), (96, 48, 16, 2.25, 96), (300, 64, 32, 3.0, 300), (200, 97, 40, 1.3, 200),
+    (300, 64, 32, 1.5, 20), (700, 33, 20, 1.6, 700), (40, 16, 16, 1e3, 40), (300, 256, 64, 1.2, 300),
+    (16, 16, 16, 10.0, 1)])
+def test_eigenpairs(E, m, k, r, ratio, rank):
+    Q, _ = torch.linalg.qr(_rand((m, m), m + k).cpu())
+    lam = ratio ** -torch.arange(m, dtype=torch.float64)
+    lam[rank:] = 0.0
+    G = (Q * lam) @ Q.t()
+    G = ((G + G.t()) / 2).to(DEV)
+    V, l = E.pod_eig(G, r, _rand((m, k), 9), 12)
+    eye = torch.eye(r, dtype=torch.float64, device=DEV)
+    assert float((V.t() @ V - eye).abs().max()) <= 64 * k * EPS
+    assert float((G @ V - V * l).norm()) <= 8 * m * k * EPS
+    assert float((l.cpu() - lam[:r]).abs().max()) <= 8 * m * k * EPS
+    assert bool((l[:-1] >= l[1:]).all())
+
+
+@pytest.mark.parametrize("m,r", [(1, 1), (7, 5), (130, 32), (100, 1024), (2049, 33)])
+def test_standardize(E, m, r):
+    C = _rand((m, r), 3) * torch.arange(1, r + 1, device=DEV)
+    mag = C.abs().mean(0) + C.abs().amax(0)
+    for common in (False, True):
+        mu, sd, T = E.pod_standardize(C, common=common)
+        mean, dev = C.mean(0), C.std(0, unbiased=False)
+        assert bool(((mu - mean).abs() <= 2 * (m + 2) * EPS * mag).all())
+        want = dev.max().expand(r) if common else dev
+        want = torch.where(want > 0, want, torch.ones_like(want))
+        assert bool(((sd - want).abs() <= 4 * (m + 4) * EPS * mag.max()).all())
+        assert bool(((T.double() - (C - mu) / sd).abs() <= 2.0 ** -24 * ((C - mu) / sd).abs() + 1e-300).all())
