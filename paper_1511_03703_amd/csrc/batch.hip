@@ -56,18 +56,25 @@ struct BatchDev {
 };
 
 template <int S, int NW>
+struct Plan {
+  static constexpr int KS = row_groups<double, S, true, false>();
+  static constexpr int RB = RowPlace<double, S, KS, NW>::R;  // rows per row tile
+  static constexpr int VB = kBlock * kU;                  // chunks per vector block
+};
+
+template <int S, int NW>
 __global__ __launch_bounds__(NW * 64) void kb_spmv_dot(BatchDev bd) {
   const int64_t blk = blockIdx.x;
   const GroupDev& g = bd.groups[bd.row_grp[blk]];
   if (g.ctl->n_active == 0) return;
-  spmv_dot_body<double, S, NW>(g.n, g.rp, g.ci, g.vals, g.p, g.q, blk - g.row0, bd.part + blk * S);
+  spmv_dot_body<double, S, Plan<S, NW>::KS, NW>(g.n, g.rp, g.ci, g.vals, g.p, g.q, blk - g.row0, bd.part + blk * S);
 }
 
 template <int S, int NW>
 __global__ __launch_bounds__(NW * 64) void kb_residual(BatchDev bd, int store_r) {
   const int64_t blk = blockIdx.x;
   const GroupDev& g = bd.groups[bd.row_grp[blk]];
-  residual_body<S, double, NW>(g.n, g.rp, g.ci, g.vals, g.x, g.b, store_r ? g.r : (double*)nullptr, blk - g.row0,
+  residual_body<S, double, Plan<S, NW>::KS, NW>(g.n, g.rp, g.ci, g.vals, g.x, g.b, store_r ? g.r : (double*)nullptr, blk - g.row0,
                                bd.part + blk * 2 * S);
 }
 
@@ -190,12 +197,6 @@ static __global__ void kb_ctl_init(BatchDev bd, int ngroups, double rtol, int ma
 // ------------------------------------------------------------ host side ---
 
 static size_t r256(size_t b) { return (b + 255) & ~(size_t)255; }
-
-template <int S, int NW>
-struct Plan {
-  static constexpr int RB = NW * EnsMap<double, S>::RPW;  // rows per row tile
-  static constexpr int VB = kBlock * kU;                  // chunks per vector block
-};
 
 struct Layout {
   std::vector<GroupDev> g;

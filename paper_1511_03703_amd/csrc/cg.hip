@@ -27,6 +27,7 @@
 // the active count is zero, and the host reads the count once per chunk of
 // iterations, so the loop ends on the device.
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "cgcore.hpp"
@@ -71,23 +72,28 @@ __global__ __launch_bounds__(256) void k_diag_inv(int n, const int32_t* __restri
   diag_inv_body<T, S>(n, rp, ci, vals, dinv, blockIdx.x);
 }
 
-// Wavefronts per workgroup of the CG product and the FP64 residual: 8
-// (a row tile twice as deep as the cycle's row passes) measured 1.2 % (FP32)
-// and 1.9 % (FP64) faster than 4 at 128^3, s = 32; the cycle's passes gain
-// under 1 % in FP32 and lose 2.7 % in FP64 from it, and keep 4.
-constexpr int kProdWaves = 8;
+// Wavefronts of a row tile of the CG product and the FP64 residual: 8 where a
+// row has one lane group (at 128^3, s = 32 1.2 % (FP32) and 1.9 % (FP64) faster
+// than 4; the cycle's passes gain under 1 % from it in FP32, lose 2.7 % in FP64,
+// and keep 4), 4 where lane groups share rows (64^3, s = 16 in FP64: 160 us,
+// 182 with 8).
+template <int KS>
+constexpr int kProdWaves = KS == 1 ? 8 : 4;
+// Lane groups of the residual of a refinement, whose 2 S partials a tile have
+// to fit 2 S for every 512 / S rows.
+template <int S>
+constexpr int kMixedResGroups = S >= 16 ? 1 : 2;
 
-// One row tile per block (kProdWaves wavefronts).
-template <int S, typename TR>
-__global__ __launch_bounds__(64 * kProdWaves) void k_residual(int n, const int32_t* __restrict__ rp,
+// One row tile per block.
+template <int S, typename TR, int KS, int NW>
+__global__ __launch_bounds__(64 * NW) void k_residual(int n, const int32_t* __restrict__ rp,
                                                   const int32_t* __restrict__ ci, const double* __restrict__ vals,
                                                   const double* __restrict__ x, const double* __restrict__ b,
                                                   TR* __restrict__ rout, double* __restrict__ part,
                                                   const Ctl* xflag) {
   // a zero initial guess (xflag->xnz == 0) makes r = b without the product
   const bool x_zero = xflag && xflag->xnz == 0;
-  residual_body<S, TR, kProdWaves>(n, rp, ci, vals, x, b, rout, blockIdx.x, part + (int64_t)blockIdx.x * 2 * S,
-                                   x_zero);
+  residual_body<S, TR, KS, NW>(n, rp, ci, vals, x, b, rout, blockIdx.x, part + (int64_t)blockIdx.x * 2 * S, x_zero);
 }
 
 static __global__ __launch_bounds__(256) void k_x_nonzero(int64_t total, const double* __restrict__ x, Ctl* c) {
@@ -101,13 +107,13 @@ __global__ __launch_bounds__(256) void k_cg_start(int64_t nchunks, const T* __re
   cg_start_body<T, S>(nchunks, r, dinv, p, xzero, blockIdx.x, part + (int64_t)blockIdx.x * 2 * S);
 }
 
-template <typename T, int S>
-__global__ __launch_bounds__(64 * kProdWaves) void k_cg_spmv_dot(int n, const int32_t* __restrict__ rp,
+template <typename T, int S, int KS>
+__global__ __launch_bounds__(64 * kProdWaves<KS>) void k_cg_spmv_dot(int n, const int32_t* __restrict__ rp,
                                                      const int32_t* __restrict__ ci, const T* __restrict__ vals,
                                                      const T* __restrict__ p, T* __restrict__ q, const Ctl* c,
                                                      double* __restrict__ part) {
   if (c->n_active == 0) return;
-  spmv_dot_body<T, S, kProdWaves>(n, rp, ci, vals, p, q, blockIdx.x, part + (int64_t)blockIdx.x * S);
+  spmv_dot_body<T, S, KS, kProdWaves<KS>>(n, rp, ci, vals, p, q, blockIdx.x, part + (int64_t)blockIdx.x * S);
 }
 
 template <typename T, int S>
@@ -258,6 +264,8 @@ static void launch_residual_scalar(const ens_graph* g, const double* vals, const
 struct Work {
   Ctl* ctl;
   double* part;   // block partials, [blocks][2 s]
+  double* rpart;  // those of the row tiles: an FP64 solve keeps them in the fifth
+                  // vector, which it does not use otherwise
   double* part1;  // first-stage sums, [kRedBlocks][2 s]
   void* vec[5];
   // polls copy into a stack word instead of the device context's pinned one
@@ -295,6 +303,8 @@ static size_t ws_layout(int64_t n, int s, bool mixed, Work* w, char* base) {
     w->part = part;
     w->part1 = part1;
     for (int i = 0; i < 5; ++i) w->vec[i] = v[i];
+    // (2 S for every 4 rows at most: only a single row's do not fit)
+    w->rpart = mixed || s == 1 || n < 2 ? part : (double*)v[4];
   }
   return off;
 }
@@ -307,15 +317,15 @@ static unsigned grid_for(int64_t items, int64_t per_block) {
 // Sum `nrows` block partials of NQ*S doubles and run the finalize step.
 // Small grids go straight to the one-block final stage.
 template <int S, int NQ>
-static void reduce(const Work& w, int64_t nrows, int op, int arg, int gate, hipStream_t st) {
+static void reduce(const Work& w, const double* part, int64_t nrows, int op, int arg, int gate, hipStream_t st) {
   constexpr int P = NQ * S;
   if (nrows <= 512) {
-    hipLaunchKernelGGL((k_reduce_final<S, NQ>), dim3(1), dim3(kBlock), 0, st, w.part, nrows, w.ctl, op, arg, gate);
+    hipLaunchKernelGGL((k_reduce_final<S, NQ>), dim3(1), dim3(kBlock), 0, st, part, nrows, w.ctl, op, arg, gate);
     return;
   }
   int64_t r = nrows / 64;
   if (r > kRedBlocks) r = kRedBlocks;
-  hipLaunchKernelGGL((k_reduce_stage1<P>), dim3((unsigned)r), dim3(kBlock), 0, st, w.part, nrows, w.part1, w.ctl,
+  hipLaunchKernelGGL((k_reduce_stage1<P>), dim3((unsigned)r), dim3(kBlock), 0, st, part, nrows, w.part1, w.ctl,
                      gate);
   hipLaunchKernelGGL((k_reduce_final<S, NQ>), dim3(1), dim3(kBlock), 0, st, w.part1, r, w.ctl, op, arg, gate);
 }
@@ -344,25 +354,34 @@ static ens_status poll_active(const Work& w, bool outer, hipStream_t st, int32_t
   return ENS_OK;
 }
 
+// q = A p, the partials of p.q (w.rpart) and their reduction into alpha.
+template <typename T, int S, int KS>
+static void product_launch(const ens_graph* g, const T* vals, const T* p, T* q, const Work& w, hipStream_t st) {
+  const unsigned sb = grid_for(g->n, RowPlace<T, S, KS, kProdWaves<KS>>::R);
+  const int kid = sizeof(T) == 8 ? ENS_K_SPMV_F64 : ENS_K_SPMV_F32;
+  const double wv = sizeof(T);
+  prof_begin(kid, st);
+  hipLaunchKernelGGL((k_cg_spmv_dot<T, S, KS>), dim3(sb), dim3(64 * kProdWaves<KS>), 0, st, g->n, g->row_ptr,
+                     g->col_idx, vals, p, q, w.ctl, w.rpart);
+  prof_end(kid, st, (double)g->nnz * (S * wv + 4.0) + 4.0 * (g->n + 1) + 2.0 * g->n * S * wv);
+  reduce<S, 1>(w, w.rpart, sb, OP_ALPHA, 0, 1, st);
+}
+
+template <typename T, int S>
+static void product(const ens_graph* g, const T* vals, const T* p, T* q, const Work& w, hipStream_t st) {
+  if (cached_matrix<T, S>(g->nnz)) product_launch<T, S, row_groups<T, S, true, true>()>(g, vals, p, q, w, st);
+  else product_launch<T, S, row_groups<T, S, true, false>()>(g, vals, p, q, w, st);
+}
+
 // Launches of one CG iteration (A, reductions, B, reductions, C).
 template <typename T, int S>
 static void cg_iteration(const ens_graph* g, const T* vals, T* x, T* r, T* p, T* q, T* dinv, const Work& w, int k,
                          hipStream_t st) {
-  using M = EnsMap<T, S>;
-  using VM = VecMap<T, S>;
-  const int64_t nchunks = (int64_t)g->n * S / VM::V;
-  const unsigned sb = grid_for(g->n, kProdWaves * M::RPW);
+  const int64_t nchunks = (int64_t)g->n * S / VecMap<T, S>::V;
   const unsigned vb = grid_for(nchunks, (int64_t)kBlock * kU);
-  const int kid = sizeof(T) == 8 ? ENS_K_SPMV_F64 : ENS_K_SPMV_F32;
-  const double wv = sizeof(T);
-  const double spmv_bytes = (double)g->nnz * (S * wv + 4.0) + 4.0 * (g->n + 1) + 2.0 * g->n * S * wv;
-  prof_begin(kid, st);
-  hipLaunchKernelGGL((k_cg_spmv_dot<T, S>), dim3(sb), dim3(64 * kProdWaves), 0, st, g->n, g->row_ptr, g->col_idx, vals, p, q,
-                     w.ctl, w.part);
-  prof_end(kid, st, spmv_bytes);
-  reduce<S, 1>(w, sb, OP_ALPHA, 0, 1, st);
+  product<T, S>(g, vals, p, q, w, st);
   hipLaunchKernelGGL((k_cg_update<T, S>), dim3(vb), dim3(kBlock), 0, st, nchunks, x, p, q, r, dinv, w.ctl, w.part);
-  reduce<S, 2>(w, vb, OP_UPDATE, k, 1, st);
+  reduce<S, 2>(w, w.part, vb, OP_UPDATE, k, 1, st);
   hipLaunchKernelGGL((k_cg_pupdate<T, S>), dim3(vb), dim3(kBlock), 0, st, nchunks, r, dinv, p, w.ctl);
 }
 
@@ -412,16 +431,27 @@ static ens_status read_stats(Ctl* ctl, int s, ens_cg_stat* stats, hipStream_t st
 template <int S, typename TR>
 static void residual(const ens_graph* g, const double* vals, const double* x, const double* b, TR* rout,
                      const Work& w, int op, int arg, hipStream_t st, bool initial = false) {
-  using M = EnsMap<double, S>;
-  const unsigned sb = grid_for(g->n, kProdWaves * M::RPW);
   if (initial) {
     const int64_t total = (int64_t)g->n * S;
     const unsigned xb = grid_for(total / 2, 256 * 4);
     hipLaunchKernelGGL(k_x_nonzero, dim3(xb < 2048 ? xb : 2048), dim3(256), 0, st, total, x, w.ctl);
   }
-  hipLaunchKernelGGL((k_residual<S, TR>), dim3(sb), dim3(64 * kProdWaves), 0, st, g->n, g->row_ptr, g->col_idx, vals, x, b,
-                     rout, w.part, initial ? (const Ctl*)w.ctl : (const Ctl*)nullptr);
-  reduce<S, 2>(w, sb, op, arg, 0, st);
+  auto launch = [&](auto groups, auto waves) {
+    constexpr int KS = groups, NW = waves;
+    const unsigned sb = grid_for(g->n, RowPlace<double, S, KS, NW>::R);
+    hipLaunchKernelGGL((k_residual<S, TR, KS, NW>), dim3(sb), dim3(64 * NW), 0, st, g->n, g->row_ptr, g->col_idx,
+                       vals, x, b, rout, w.rpart, initial ? (const Ctl*)w.ctl : (const Ctl*)nullptr);
+    reduce<S, 2>(w, w.rpart, sb, op, arg, 0, st);
+  };
+  if constexpr (sizeof(TR) == 4) {
+    launch(std::integral_constant<int, kMixedResGroups<S>>(), std::integral_constant<int, 8>());
+  } else if (cached_matrix<double, S>(g->nnz)) {
+    constexpr int KS = row_groups<double, S, true, true>();
+    launch(std::integral_constant<int, KS>(), std::integral_constant<int, kProdWaves<KS>>());
+  } else {
+    constexpr int KS = row_groups<double, S, true, false>();
+    launch(std::integral_constant<int, KS>(), std::integral_constant<int, kProdWaves<KS>>());
+  }
 }
 
 template <typename T, int S>
@@ -429,7 +459,7 @@ static void cg_start(int64_t n, const T* r, const T* dinv, T* p, T* xzero, const
   const int64_t nchunks = n * S / VecMap<T, S>::V;
   const unsigned vb = grid_for(nchunks, (int64_t)kBlock * kU);
   hipLaunchKernelGGL((k_cg_start<T, S>), dim3(vb), dim3(kBlock), 0, st, nchunks, r, dinv, p, xzero, w.part);
-  reduce<S, 2>(w, vb, OP_RHO, 0, 0, st);
+  reduce<S, 2>(w, w.part, vb, OP_RHO, 0, 0, st);
 }
 
 // ------------------------------------------------------------ compaction --
@@ -664,7 +694,7 @@ static void scalar_setup(const ens_graph* g, const double* vals, const double* b
   hipLaunchKernelGGL((k_diag_inv<double, 1>), dim3(grid_for(n, 256)), dim3(256), 0, st, g->n, g->row_ptr,
                      g->col_idx, vals, dinv);
   launch_residual_scalar<G>(g, vals, x, b, r, w.part, rb, st);
-  reduce<1, 2>(w, rb, OP_START, 0, 0, st);
+  reduce<1, 2>(w, w.part, rb, OP_START, 0, 0, st);
   hipLaunchKernelGGL(k_zero_where<1>, dim3(grid_for(n, 256 * 8)), dim3(kBlock), 0, st, n, x, w.ctl);
   cg_start<double, 1>(n, r, dinv, p, (double*)nullptr, w, st);
 }
@@ -688,9 +718,9 @@ static void scalar_iters(const ens_graph* g, const double* vals, double* x, cons
       hipLaunchKernelGGL(k_cg_spmv_dot_scalar<G>, dim3(rb), dim3(kBlock), 0, st, g->n, g->row_ptr, g->col_idx, vals,
                          p, q, w.ctl, w.part);
     prof_end(ENS_K_SCALAR_SPMV, st, (double)g->nnz * 12.0 + 4.0 * (n + 1) + 16.0 * n);
-    reduce<1, 1>(w, rb, OP_ALPHA, 0, 1, st);
+    reduce<1, 1>(w, w.part, rb, OP_ALPHA, 0, 1, st);
     hipLaunchKernelGGL((k_cg_update<double, 1>), dim3(vb), dim3(kBlock), 0, st, n, x, p, q, r, dinv, w.ctl, w.part);
-    reduce<1, 2>(w, vb, OP_UPDATE, k, 1, st);
+    reduce<1, 2>(w, w.part, vb, OP_UPDATE, k, 1, st);
     hipLaunchKernelGGL((k_cg_pupdate<double, 1>), dim3(vb), dim3(kBlock), 0, st, n, r, dinv, p, w.ctl);
   }
 }
@@ -700,7 +730,7 @@ static void scalar_finish(const ens_graph* g, const double* vals, const double* 
                           hipStream_t st) {
   const unsigned rb = grid_for(g->n, sc_rows_per_block<G>());
   launch_residual_scalar<G>(g, vals, x, b, (double*)nullptr, w.part, rb, st);
-  reduce<1, 2>(w, rb, OP_TRUE, 0, 0, st);
+  reduce<1, 2>(w, w.part, rb, OP_TRUE, 0, 0, st);
 }
 
 template <int G>
@@ -820,23 +850,16 @@ static void mg_iterations(const ens_graph* g, const T* vals, const MgPlan& plan,
                           const Work& w, int k0, int k1, hipStream_t st) {
   const int64_t n = g->n;
   const int64_t nchunks = n * S / VecMap<T, S>::V;
-  const unsigned sb = grid_for(n, kProdWaves * EnsMap<T, S>::RPW);
-  const unsigned db = grid_for(n, 4 * EnsMap<T, S>::RPW);  // row tiles of the cycle's passes
+  const unsigned db = grid_for(n, mg_dot_rows<T, S>(g->nnz));  // row tiles of the cycle's last pass
   const unsigned vb = grid_for(nchunks, (int64_t)kBlock * kU);
-  const int kid = sizeof(T) == 8 ? ENS_K_SPMV_F64 : ENS_K_SPMV_F32;
-  const double spmv_bytes = (double)g->nnz * (S * (double)sizeof(T) + 4.0) + 4.0 * (n + 1) + 2.0 * n * S * sizeof(T);
   for (int k = k0 + 1; k <= k1; ++k) {
-    prof_begin(kid, st);
-    hipLaunchKernelGGL((k_cg_spmv_dot<T, S>), dim3(sb), dim3(64 * kProdWaves), 0, st, g->n, g->row_ptr, g->col_idx, vals, p, q,
-                       w.ctl, w.part);
-    prof_end(kid, st, spmv_bytes);
-    reduce<S, 1>(w, sb, OP_ALPHA, 0, 1, st);
+    product<T, S>(g, vals, p, q, w, st);
     hipLaunchKernelGGL((k_mg_update_r<T, S>), dim3(vb), dim3(kBlock), 0, st, nchunks, x, p, q, r, w.ctl, w.part);
-    reduce<S, 2>(w, vb, OP_UPDATE_R, k, 1, st);
+    reduce<S, 2>(w, w.part, vb, OP_UPDATE_R, k, 1, st);
     // the cycle's last fine-level pass also writes the r . z partials, one
     // row per row tile of that pass (db rows)
-    mg_vcycle<T, S>(plan, r, z, w.ctl, st, w.part);
-    reduce<S, 1>(w, db, OP_BETA, 0, 1, st);
+    mg_vcycle<T, S>(plan, r, z, w.ctl, st, w.rpart);
+    reduce<S, 1>(w, w.rpart, db, OP_BETA, 0, 1, st);
     hipLaunchKernelGGL((k_mg_pz<T, S>), dim3(vb), dim3(kBlock), 0, st, nchunks, z, p, w.ctl);
   }
 }
@@ -848,7 +871,7 @@ static void mg_start(int64_t n, const MgPlan& plan, T* r, T* z, T* p, const Work
   const unsigned vb = grid_for(nchunks, (int64_t)kBlock * kU);
   mg_vcycle<T, S>(plan, r, z, w.ctl, st);
   hipLaunchKernelGGL((k_mg_rz<T, S>), dim3(vb), dim3(kBlock), 0, st, nchunks, r, z, p, w.ctl, 0, w.part);
-  reduce<S, 2>(w, vb, OP_RHO, 0, 0, st);
+  reduce<S, 2>(w, w.part, vb, OP_RHO, 0, 0, st);
 }
 
 // FP64 CG with z = M r from the FP64 multigrid cycle.

@@ -24,6 +24,7 @@
 
 #include <cmath>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "cgcore.hpp"
@@ -341,7 +342,10 @@ enum MgRowMode { MG_RES = 0, MG_CHEB1 = 1, MG_CHEB2 = 2 };
 // DOT (the cycle's very last pass, on the finest level, inside CG): the
 // block's per-sample partials of B . xout, i.e. r . z with z = M r, go to
 // dot[blockIdx.x][S], so CG needs no separate pass over r and z.
-template <typename T, int S, int MODE, bool DOT = false>
+// EARLY: the row's vectors are on their way while the product is formed; else
+// they are read after it (64^3, FP64 s = 16 with 2 lane groups: 177 us, 179
+// early; 128^3, FP32 s = 32 with one: 1526 us early, 1546 after).
+template <typename T, int S, int KS, int MODE, bool DOT = false>
 __global__ __launch_bounds__(256) void k_mg_row(int n, const int32_t* __restrict__ rp, const int32_t* __restrict__ ci,
                                                 const T* __restrict__ vals, const T* __restrict__ x,
                                                 const T* __restrict__ b, const T* __restrict__ dinv,
@@ -349,44 +353,53 @@ __global__ __launch_bounds__(256) void k_mg_row(int n, const int32_t* __restrict
                                                 T* __restrict__ out, const Ctl* gate, double* __restrict__ dot) {
   static_assert(!DOT || MODE == MG_CHEB2, "the dot is formed in the smoother's last step");
   if (mg_idle(gate)) return;
-  using M = EnsMap<T, S>;
+  using M = EnsMap<T, S, KS>;
   using vt = typename M::vt;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int sub = lane % M::L;
-  const int64_t row = ((int64_t)blockIdx.x * 4 + wave) * M::RPW + lane / M::L;
-  constexpr int R = 4 * M::RPW;
+  constexpr bool EARLY = KS == 1 || (KS == 4 && M::L >= 8);
+  const RowPlace<T, S, KS, 4> at;
+  constexpr int R = at.R;
   __shared__ RowTileLds<R> tile;
-  const bool staged = stage_row_tile(tile, n, rp, ci, (int64_t)blockIdx.x * R);
+  const int64_t r0 = (int64_t)blockIdx.x * R, row = r0 + at.lr;
+  const bool staged = stage_row_tile(tile, n, rp, ci, r0);
   double acc[1][M::V];
 #pragma unroll
   for (int v = 0; v < M::V; ++v) acc[0][v] = 0.0;
   if (row < n) {
-    const vt ax =
-        tile_row_product<T, S>(tile, staged, (int)(row - (int64_t)blockIdx.x * R), ci, vals, x, sub);
-    const int64_t i = row * M::L + sub;
-    const vt bv = load_stream((const vt*)b + i);
-    const vt res = bv - ax;
-    if (MODE == MG_RES) {
-      store_stream((vt*)out + i, res);
-      return;
-    }
-    vt k1, k2;
+    const int64_t i = row * M::L + at.sub;
+    vt bv = (vt)0, dv = (vt)0, dp = (vt)0, xv = (vt)0;
+    auto vectors = [&]() {
+      bv = load_stream((const vt*)b + i);
+      if (MODE != MG_RES) dv = load_stream((const vt*)dinv + i);
+      if (MODE == MG_CHEB2) dp = load_stream((const vt*)d + i);
+      if (MODE != MG_RES) xv = ((const vt*)x)[i];
+    };
+    if (EARLY && at.g == 0) vectors();
+    const vt ax = tile_row_product<T>(at, tile, staged, ci, vals, x);
+    if (at.g == 0) {
+      if (!EARLY) vectors();
+      const vt res = bv - ax;
+      if (MODE == MG_RES) {
+        store_stream((vt*)out + i, res);
+      } else {
+        vt k1, k2;
 #pragma unroll
-    for (int v = 0; v < M::V; ++v) {
-      const ChebK c = cheb_consts(lmax[sub * M::V + v]);
-      k1[v] = (T)(MODE == MG_CHEB1 ? 0.0 : c.c1);
-      k2[v] = (T)(MODE == MG_CHEB1 ? c.inv_theta : c.c2);
-    }
-    const vt dv = load_stream((const vt*)dinv + i) * res;
-    vt dn;
-    if (MODE == MG_CHEB1) dn = k2 * dv;
-    else dn = k1 * load_stream((const vt*)d + i) + k2 * dv;
-    if (MODE == MG_CHEB1) store_stream((vt*)d + i, dn);
-    const vt xn = ((const vt*)x)[i] + dn;
-    store_stream((vt*)out + i, xn);
-    if (DOT) {
+        for (int v = 0; v < M::V; ++v) {
+          const ChebK c = cheb_consts(lmax[at.sub * M::V + v]);
+          k1[v] = (T)(MODE == MG_CHEB1 ? 0.0 : c.c1);
+          k2[v] = (T)(MODE == MG_CHEB1 ? c.inv_theta : c.c2);
+        }
+        const vt dr = dv * res;
+        vt dn;
+        if (MODE == MG_CHEB1) dn = k2 * dr;
+        else dn = k1 * dp + k2 * dr;
+        if (MODE == MG_CHEB1) store_stream((vt*)d + i, dn);
+        const vt xn = xv + dn;
+        store_stream((vt*)out + i, xn);
+        if (DOT) {
 #pragma unroll
-      for (int v = 0; v < M::V; ++v) acc[0][v] = (double)bv[v] * (double)xn[v];
+          for (int v = 0; v < M::V; ++v) acc[0][v] = (double)bv[v] * (double)xn[v];
+        }
+      }
     }
   }
   if (DOT) block_partials<S, M::V, 1, 4>(acc, dot + (int64_t)blockIdx.x * S);
@@ -612,13 +625,25 @@ static unsigned blocks_for(int64_t items, int64_t per) {
   return (unsigned)(b < 1 ? 1 : b);
 }
 
+// One row pass of level l: KS lane groups a row as the size of its matrix asks.
+template <typename T, int S, int MODE, bool DOT = false>
+static void row_pass(const MgLevel& l, const T* x, const T* b, T* out, const Ctl* gate, hipStream_t st,
+                     double* dot = nullptr) {
+  const T* vals = sizeof(T) == 4 ? (const T*)l.vals32 : (const T*)l.vals;
+  auto launch = [&](auto groups) {
+    constexpr int KS = groups;
+    hipLaunchKernelGGL((k_mg_row<T, S, KS, MODE, DOT>), dim3(blocks_for(l.n, RowPlace<T, S, KS, 4>::R)), dim3(256), 0,
+                       st, (int)l.n, l.rp, l.ci, vals, x, b, (const T*)l.dinv, l.lmax, (T*)l.d, out, gate, dot);
+  };
+  if (cached_matrix<T, S>(l.nnz)) launch(std::integral_constant<int, row_groups<T, S, DOT, true>()>());
+  else launch(std::integral_constant<int, row_groups<T, S, DOT, false>()>());
+}
+
 template <typename T, int S>
 static void cycle(const MgPlan& P, int k, const T* B, T* OUT, const Ctl* gate, hipStream_t st,
                   double* dot = nullptr) {
-  using EM = EnsMap<T, S>;
   using VM = VecMap<T, S>;
   const MgLevel& l = P.lv[k];
-  const T* vals = sizeof(T) == 4 ? (const T*)l.vals32 : (const T*)l.vals;
   const T* dinv = (const T*)l.dinv;
   T *xa = (T*)l.xa, *xb = (T*)l.xb, *r = (T*)l.r, *d = (T*)l.d;
   if (k == P.levels - 1) {
@@ -630,7 +655,6 @@ static void cycle(const MgPlan& P, int k, const T* B, T* OUT, const Ctl* gate, h
   T* cb = (T*)c.b;
   T* cx = (T*)c.xb;
   const int64_t nchunks = l.n * S / VM::V;
-  const unsigned rb = blocks_for(l.n, 4 * EM::RPW);
   // algorithmic bytes of the fine row passes: the matrix and the gathered
   // x once, plus (vectors read + written) x n x S x sizeof(T)
   const double mat = (double)l.nnz * (S * (double)sizeof(T) + 4.0) + 4.0 * (l.n + 1);
@@ -639,27 +663,20 @@ static void cycle(const MgPlan& P, int k, const T* B, T* OUT, const Ctl* gate, h
   hipLaunchKernelGGL((k_mg_cheb0<T, S>), dim3(blocks_for(nchunks, (int64_t)kBlock * kU)), dim3(kBlock), 0, st,
                      nchunks, B, dinv, l.lmax, d, gate);
   if (fine) prof_begin(ENS_K_MG_ROW, st);
-  hipLaunchKernelGGL((k_mg_row<T, S, MG_CHEB2>), dim3(rb), dim3(256), 0, st, (int)l.n, l.rp, l.ci, vals, d, B, dinv,
-                     l.lmax, d, xb, gate, (double*)nullptr);
+  row_pass<T, S, MG_CHEB2>(l, d, B, xb, gate, st);
   if (fine) prof_end(ENS_K_MG_ROW, st, mat + 4.0 * vec);  // x is d: one vector read less
   if (fine) prof_begin(ENS_K_MG_ROW, st);
-  hipLaunchKernelGGL((k_mg_row<T, S, MG_RES>), dim3(rb), dim3(256), 0, st, (int)l.n, l.rp, l.ci, vals, xb, B, dinv,
-                     l.lmax, d, r, gate, (double*)nullptr);
+  row_pass<T, S, MG_RES>(l, xb, B, r, gate, st);
   if (fine) prof_end(ENS_K_MG_ROW, st, mat + 3.0 * vec);
   hipLaunchKernelGGL((k_mg_restrict<T, S>), dim3(blocks_for(c.n * VM::L, 256)), dim3(256), 0, st, c.N, r, cb, gate);
   cycle<T, S>(P, k + 1, cb, cx, gate, st);
   hipLaunchKernelGGL((k_mg_prolong<T, S>), dim3(blocks_for(l.n * VM::L, 256)), dim3(256), 0, st, c.N, cx, xb, gate);
   if (fine) prof_begin(ENS_K_MG_ROW, st);
-  hipLaunchKernelGGL((k_mg_row<T, S, MG_CHEB1>), dim3(rb), dim3(256), 0, st, (int)l.n, l.rp, l.ci, vals, xb, B, dinv,
-                     l.lmax, d, xa, gate, (double*)nullptr);
+  row_pass<T, S, MG_CHEB1>(l, xb, B, xa, gate, st);
   if (fine) prof_end(ENS_K_MG_ROW, st, mat + 5.0 * vec);
   if (fine) prof_begin(ENS_K_MG_ROW, st);
-  if (dot && fine)
-    hipLaunchKernelGGL((k_mg_row<T, S, MG_CHEB2, true>), dim3(rb), dim3(256), 0, st, (int)l.n, l.rp, l.ci, vals, xa,
-                       B, dinv, l.lmax, d, OUT, gate, dot);
-  else
-    hipLaunchKernelGGL((k_mg_row<T, S, MG_CHEB2>), dim3(rb), dim3(256), 0, st, (int)l.n, l.rp, l.ci, vals, xa, B,
-                       dinv, l.lmax, d, OUT, gate, (double*)nullptr);
+  if (dot && fine) row_pass<T, S, MG_CHEB2, true>(l, xa, B, OUT, gate, st, dot);
+  else row_pass<T, S, MG_CHEB2>(l, xa, B, OUT, gate, st);
   if (fine) prof_end(ENS_K_MG_ROW, st, mat + 5.0 * vec);
 }
 

@@ -269,127 +269,61 @@ static __global__ void k_gm_accept(GmCtl* c) {
 
 // --------------------------------------------------------- vector kernels ---
 
-// sum_k vals[k] z[col k] for the two samples of lane `sub`, the values (TV)
-// and z (TZ) widened to FP64 as they are read; entries in ascending order.
-template <int S, typename TV, typename TZ>
-__device__ inline typename EnsMap<double, S>::vt gm_row_product(const int32_t* __restrict__ ci,
-                                                                const TV* __restrict__ vals,
-                                                                const TZ* __restrict__ z, int64_t k0, int64_t k1,
-                                                                int sub) {
-  using M = EnsMap<double, S>;
-  using vt = typename M::vt;
-  typedef typename vec_t<TV, M::V>::type at;
-  typedef typename vec_t<TZ, M::V>::type zt;
-  const at* vv = (const at*)vals + sub;
-  const zt* zv = (const zt*)z + sub;
-  vt acc = (vt)0.0;
-  int64_t k = k0;
-  for (; k + 2 < k1; k += 3) {
-    int32_t c3[3];
-    at a[3];
-    zt b[3];
-#pragma unroll
-    for (int j = 0; j < 3; ++j) c3[j] = ci[k + j];
-#pragma unroll
-    for (int j = 0; j < 3; ++j) a[j] = load_stream(vv + (k + j) * M::L);
-#pragma unroll
-    for (int j = 0; j < 3; ++j) b[j] = zv[(int64_t)c3[j] * M::L];
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-#pragma unroll
-      for (int v = 0; v < M::V; ++v) acc[v] += (double)a[j][v] * (double)b[j][v];
-  }
-  for (; k < k1; ++k) {
-    const at a = load_stream(vv + k * M::L);
-    const zt b = zv[(int64_t)ci[k] * M::L];
-#pragma unroll
-    for (int v = 0; v < M::V; ++v) acc[v] += (double)a[v] * (double)b[v];
-  }
-  return acc;
-}
-
 // w = A z: the matrix in FP64 or FP32 (TV), z in FP64 or, from an FP32
 // cycle, FP32 (TZ); products and sums in FP64.
-template <int S, typename TV, typename TZ>
+template <int S, int KS, typename TV, typename TZ>
 static __global__ __launch_bounds__(kBlock) void k_gm_spmv(int n, const int32_t* __restrict__ rp,
                                                            const int32_t* __restrict__ ci,
                                                            const TV* __restrict__ vals, const TZ* __restrict__ z,
                                                            double* __restrict__ w) {
-  using M = EnsMap<double, S>;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int sub = lane % M::L;
-  const int64_t row = ((int64_t)blockIdx.x * (kBlock / 64) + wave) * M::RPW + lane / M::L;
-  constexpr int R = (kBlock / 64) * M::RPW;
+  using M = EnsMap<double, S, KS>;
+  const RowPlace<double, S, KS, kBlock / 64> at;
+  constexpr int R = at.R;
   __shared__ RowTileLds<R> tile;  // the row tile's offsets and indices, as in the CG product
-  const bool staged = stage_row_tile(tile, n, rp, ci, (int64_t)blockIdx.x * R);
+  const int64_t r0 = (int64_t)blockIdx.x * R, row = r0 + at.lr;
+  const bool staged = stage_row_tile(tile, n, rp, ci, r0);
   if (row >= n) return;
-  const int lr = (int)(row - (int64_t)blockIdx.x * R);
-  const typename M::vt y = staged
-                               ? gm_row_product<S, TV, TZ>(tile.ci - tile.rp[0], vals, z, tile.rp[lr], tile.rp[lr + 1], sub)
-                               : gm_row_product<S, TV, TZ>(ci, vals, z, tile.rp[lr], tile.rp[lr + 1], sub);
-  store_stream((typename M::vt*)w + row * M::L + sub, y);
-}
-
-// One row of the FP32-mapped product: entries k0..k1 of the row, column
-// indices from ci (global memory or a staged LDS tile).
-template <int S, typename TZ>
-__device__ inline typename vec_t<double, 4>::type gm_v32_row(const int32_t* ci, const float* __restrict__ vals,
-                                                             const TZ* __restrict__ z, int64_t k0, int64_t k1,
-                                                             int sub) {
-  using M = EnsMap<float, S>;
-  typedef typename vec_t<float, 4>::type f4;
-  typedef typename vec_t<TZ, 4>::type z4;
-  typedef typename vec_t<double, 4>::type d4;
-  const f4* vv = (const f4*)vals + sub;
-  const TZ* zs = z + sub * 4;
-  d4 acc = (d4)0.0;
-  int64_t k = k0;
-  for (; k + 2 < k1; k += 3) {
-    int32_t c3[3];
-    f4 a[3];
-    z4 b[3];
-#pragma unroll
-    for (int j = 0; j < 3; ++j) c3[j] = ci[k + j];
-#pragma unroll
-    for (int j = 0; j < 3; ++j) a[j] = load_stream(vv + (k + j) * M::L);
-#pragma unroll
-    for (int j = 0; j < 3; ++j) b[j] = *(const z4*)(zs + (int64_t)c3[j] * S);
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) acc[v] += (double)a[j][v] * (double)b[j][v];
-  }
-  for (; k < k1; ++k) {
-    const f4 a = load_stream(vv + k * M::L);
-    const z4 b = *(const z4*)(zs + (int64_t)ci[k] * S);
-#pragma unroll
-    for (int v = 0; v < 4; ++v) acc[v] += (double)a[v] * (double)b[v];
-  }
-  return acc;
+  const typename M::vt y = tile_row_product<double>(at, tile, staged, ci, vals, z);
+  if (at.g == 0) store_stream((typename M::vt*)w + row * M::L + at.sub, y);
 }
 
 // w = A z for an FP32 matrix with the FP32 row mapping: each lane reads 16
 // bytes (4 samples) of the value stream, gathers those samples of z (FP64
 // or FP32) and accumulates in FP64.
-template <int S, typename TZ>
+template <int S, int KS, typename TZ>
 static __global__ __launch_bounds__(kBlock) void k_gm_spmv_v32(int n, const int32_t* __restrict__ rp,
                                                                const int32_t* __restrict__ ci,
                                                                const float* __restrict__ vals,
                                                                const TZ* __restrict__ z, double* __restrict__ w) {
-  using M = EnsMap<float, S>;  // V = 4 samples per lane
   typedef typename vec_t<double, 4>::type d4;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int sub = lane % M::L;
-  const int64_t row = ((int64_t)blockIdx.x * (kBlock / 64) + wave) * M::RPW + lane / M::L;
-  constexpr int R = (kBlock / 64) * M::RPW;
+  const RowPlace<float, S, KS, kBlock / 64> at;  // V = 4 samples per lane
+  constexpr int R = at.R;
   __shared__ RowTileLds<R> tile;  // the row tile's offsets and indices, as in the CG product
-  const bool staged = stage_row_tile(tile, n, rp, ci, (int64_t)blockIdx.x * R);
+  const int64_t r0 = (int64_t)blockIdx.x * R, row = r0 + at.lr;
+  const bool staged = stage_row_tile(tile, n, rp, ci, r0);
   if (row >= n) return;
-  const int lr = (int)(row - (int64_t)blockIdx.x * R);
-  const int64_t k0 = tile.rp[lr], k1 = tile.rp[lr + 1];
-  const d4 acc = staged ? gm_v32_row<S, TZ>(tile.ci - tile.rp[0], vals, z, k0, k1, sub)
-                        : gm_v32_row<S, TZ>(ci, vals, z, k0, k1, sub);
-  store_stream((d4*)(w + row * S + sub * 4), acc);
+  const d4 acc = tile_row_product<double>(at, tile, staged, ci, vals, z);
+  if (at.g == 0) store_stream((d4*)(w + row * S + at.sub * 4), acc);
+}
+
+// The product with the lane groups its matrix's size asks for.
+template <int S, typename TV, typename TZ>
+static void gm_product(const ens_graph* g, const TV* vals, const TZ* z, double* w, hipStream_t st) {
+  auto launch = [&](auto groups) {
+    constexpr int KS = groups;
+    if constexpr (sizeof(TV) == 4)
+      hipLaunchKernelGGL((k_gm_spmv_v32<S, KS, TZ>),
+                         dim3((unsigned)((g->n + RowPlace<float, S, KS, kBlock / 64>::R - 1) /
+                                         RowPlace<float, S, KS, kBlock / 64>::R)),
+                         dim3(kBlock), 0, st, g->n, g->row_ptr, g->col_idx, vals, z, w);
+    else
+      hipLaunchKernelGGL((k_gm_spmv<S, KS, TV, TZ>),
+                         dim3((unsigned)((g->n + RowPlace<double, S, KS, kBlock / 64>::R - 1) /
+                                         RowPlace<double, S, KS, kBlock / 64>::R)),
+                         dim3(kBlock), 0, st, g->n, g->row_ptr, g->col_idx, vals, z, w);
+  };
+  if (cached_matrix<TV, S>(g->nnz)) launch(std::integral_constant<int, row_groups<TV, S, false, true>()>());
+  else launch(std::integral_constant<int, row_groups<TV, S, false, false>()>());
 }
 
 // part[blk][i*S + e] = sum over the block's chunks of V_i . w, i = 0..j.
@@ -622,18 +556,17 @@ static __global__ __launch_bounds__(kBlock) void k_gm_residual(int n, const int3
                                                                double* __restrict__ part) {
   using M = EnsMap<double, S>;
   using vt = typename M::vt;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int sub = lane % M::L;
+  const RowPlace<double, S, 1, kBlock / 64> at;
   double acc[2][M::V];
 #pragma unroll
   for (int v = 0; v < M::V; ++v) acc[0][v] = acc[1][v] = 0.0;
-  const int64_t row = ((int64_t)blockIdx.x * (kBlock / 64) + wave) * M::RPW + lane / M::L;
+  const int64_t row = (int64_t)blockIdx.x * at.R + at.lr;
   if (row < n) {
     // XZ: x = 0 is known, so r = b without the product
-    const vt ax = XZ ? (vt)0.0 : gm_row_product<S, TV, double>(ci, vals, x, rp[row], rp[row + 1], sub);
-    const vt bv = ((const vt*)b)[row * M::L + sub];
+    const vt ax = XZ ? (vt)0.0 : row_sum<S, M::V, 1, double>(ci, vals, x, rp[row], rp[row + 1], at.sub, 0);
+    const vt bv = ((const vt*)b)[row * M::L + at.sub];
     const vt rv = bv - ax;
-    ((vt*)r)[row * M::L + sub] = rv;
+    ((vt*)r)[row * M::L + at.sub] = rv;
 #pragma unroll
     for (int v = 0; v < M::V; ++v) {
       acc[0][v] = rv[v] * rv[v];
@@ -757,7 +690,6 @@ static ens_status gmres(const ens_graph* g, const TV* vals, const double* b, dou
   const int64_t vstride = (int64_t)n * S;
   const unsigned sg = stream_grid(nchunks), eg = grid_of(nchunks, kBlock);
   const unsigned rb = (unsigned)row_blocks(n, S);
-  const unsigned sb = grid_of(n, (kBlock / 64) * EnsMap<double, S>::RPW);
   const bool jac = plan == nullptr;
   const bool f32 = plan != nullptr && plan->fp32;
   const double spmv_bytes = (double)g->nnz * (S * (double)sizeof(TV) + 4.0) + 4.0 * (n + 1) + 2.0 * n * S * 8.0;
@@ -800,22 +732,8 @@ static ens_status gmres(const ens_graph* g, const TV* vals, const double* b, dou
       if (f32) mg_vcycle<float, S>(*plan, w.r32, zj32, nullptr, st);
       else if (!jac) mg_vcycle<double, S>(*plan, vj, zj, nullptr, st);
       prof_begin(ENS_K_GM_SPMV, st);
-      if (sizeof(TV) == 4) {
-        const unsigned sb32 = grid_of(n, (kBlock / 64) * EnsMap<float, S>::RPW);
-        if (f32)
-          hipLaunchKernelGGL((k_gm_spmv_v32<S, float>), dim3(sb32), dim3(kBlock), 0, st, n, g->row_ptr, g->col_idx,
-                             (const float*)vals, (const float*)zj32, w.w);
-        else
-          hipLaunchKernelGGL((k_gm_spmv_v32<S, double>), dim3(sb32), dim3(kBlock), 0, st, n, g->row_ptr,
-                             g->col_idx, (const float*)vals, (const double*)zj, w.w);
-      } else {
-        if (f32)
-          hipLaunchKernelGGL((k_gm_spmv<S, TV, float>), dim3(sb), dim3(kBlock), 0, st, n, g->row_ptr, g->col_idx,
-                             vals, (const float*)zj32, w.w);
-        else
-          hipLaunchKernelGGL((k_gm_spmv<S, TV, double>), dim3(sb), dim3(kBlock), 0, st, n, g->row_ptr, g->col_idx,
-                             vals, (const double*)zj, w.w);
-      }
+      if (f32) gm_product<S>(g, vals, (const float*)zj32, w.w, st);
+      else gm_product<S>(g, vals, (const double*)zj, w.w, st);
       prof_end(ENS_K_GM_SPMV, st, spmv_bytes - (f32 ? 4.0 * n * S : 0.0));
       // classical Gram-Schmidt twice: h1 = V^T w, w -= V h1, h2 = V^T w,
       // w -= V h2 and |w|^2; for j < 16 the middle two passes are one kernel

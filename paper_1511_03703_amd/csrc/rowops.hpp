@@ -4,26 +4,58 @@
 // the column index is read once and the s-long ensembles of the value and of
 // x[col] are contiguous.  On a 64-wide wavefront we map that inner loop onto
 // lanes: one 16-byte load holds V = 16/sizeof(T) samples, L = s/V lanes
-// cover one entry's ensemble, and a wavefront works on 64/L rows at once.
-// Every lane walks its row's entries in ascending order, so each sample's
-// sum is formed in the order of the listing (with fused multiply-adds).
-//   s=32 FP32: L=8, 8 rows/wave     s=32 FP64: L=16, 4 rows/wave
-//   s=16 FP64: L=8, 8 rows/wave     s=4  FP64: L=2, 32 rows/wave
-// Loads of the matrix values and of x are 128-256 contiguous bytes per row
-// and entry (coalesced); the values stream is read with non-temporal loads
-// so it does not evict the reused x entries from the caches.
+// cover one entry's ensemble, and KS such lane groups share a row, taking
+// every KS-th entry; the groups' sums are added by a butterfly.  With one
+// group a row, a narrow ensemble is read in pieces of L * 16 bytes a row and
+// the 27 entries are nine dependent rounds of three loads; KS groups read KS
+// entries of a row side by side in as many fewer rounds, at the price of the
+// butterfly and of vector work on only 1/KS of the lanes (row_groups below
+// says when it pays).  The values stream is read with non-temporal loads so
+// it does not evict the reused x entries from the caches.
 #pragma once
 
 #include "common.hpp"
 
 namespace ens {
 
+// Lane groups per row.  Ensembles of 64 bytes or less (L <= 4) always gain
+// from several groups; wider ones gain with 4 while the matrix fits the 256 MB
+// last-level cache (SMALL: latency counts), and beyond that, where HBM bounds
+// the pass, a little with 2, or not at all where the pass also forms sums of
+// its rows for a reduction (DOT: the shorter tiles write more partials).
+// Measured, one group -> this many (us):
+//   product        64^3: FP64 s = 4 107 -> 54, 8 123 -> 90, 16 165 -> 158, 32 327
+//                  -> 318; FP32 s = 4 110 -> 35, 8 106 -> 54, 16 120 -> 90;
+//                  128^3: FP32 s = 32 1375 -> 1354
+//   smoother pass  8^3, 16^3, 32^3: FP32 s = 32 7.9 -> 4.4, 8.3 -> 5.7, 29.0 ->
+//                  24.6; FP64 s = 16 the same; 64^3: FP64 s = 16 184 -> 177, s = 8
+//                  130 -> 100; 128^3: FP32 s = 32 1510 -> 1475
+//   with DOT       32^3: FP64 s = 16 28.6 -> 25.8; 64^3: s = 8 131 -> 105; s = 16
+//                  186 with one, 183 to 188 with 2 and 4; 128^3: FP32 s = 32 1526
+//                  with one, 1554 with 2
+// (FP32 sums take at most 4: the workspace of a refinement holds 2 S partials
+// for every 512 / S rows.)
+template <typename T, int S, bool DOT, bool SMALL>
+constexpr int row_groups() {
+  constexpr int L = S * (int)sizeof(T) / 16;
+  if (L <= 4) return L == 4 || (DOT && sizeof(T) == 4) ? 4 : 8;
+  return SMALL ? 4 : DOT ? 1 : 2;
+}
+
+// Whether an ensemble matrix of nnz entries fits the last-level cache.
 template <typename T, int S>
+inline bool cached_matrix(int64_t nnz) {
+  return nnz * (int64_t)(S * sizeof(T)) <= ((int64_t)256 << 20);
+}
+
+template <typename T, int S, int KSv = 1>
 struct EnsMap {
   static constexpr int V = pack<T>::V;  // samples per 16-byte load
   static_assert(S % V == 0, "ensemble size must fill a 16-byte load");
-  static constexpr int L = S / V;       // lanes per row
-  static constexpr int RPW = 64 / L;    // rows per wavefront
+  static constexpr int L = S / V;       // lanes per entry
+  static constexpr int KS = KSv;        // lane groups per row
+  static constexpr int W = L * KS;      // lanes per row
+  static constexpr int RPW = 64 / W;    // rows per wavefront
   typedef typename pack<T>::type vt;
 };
 
@@ -38,37 +70,6 @@ __device__ inline VT load_stream(const VT* p) {
 template <typename VT>
 __device__ inline void store_stream(VT* p, VT v) {
   __builtin_nontemporal_store(v, p);
-}
-
-// y_row = sum_k values[k] * x[col[k]] for the V samples of lane `sub`.
-template <typename T, int S>
-__device__ inline typename EnsMap<T, S>::vt ens_row_product(const int32_t* __restrict__ ci,
-                                                            const T* __restrict__ vals,
-                                                            const T* __restrict__ x, int64_t k0,
-                                                            int64_t k1, int sub) {
-  using M = EnsMap<T, S>;
-  using vt = typename M::vt;
-  const vt* vv = (const vt*)vals + sub;
-  const vt* xv = (const vt*)x + sub;
-  vt acc = (vt)0;
-  int64_t k = k0;
-  for (; k + 2 < k1; k += 3) {
-    int32_t c[3];
-    vt a[3], b[3];
-#pragma unroll
-    for (int j = 0; j < 3; ++j) c[j] = ci[k + j];
-#pragma unroll
-    for (int j = 0; j < 3; ++j) a[j] = load_stream(vv + (k + j) * M::L);
-#pragma unroll
-    for (int j = 0; j < 3; ++j) b[j] = xv[(int64_t)c[j] * M::L];
-#pragma unroll
-    for (int j = 0; j < 3; ++j) acc += a[j] * b[j];
-  }
-  for (; k < k1; ++k) {
-    int32_t c = ci[k];
-    acc += load_stream(vv + k * M::L) * xv[(int64_t)c * M::L];
-  }
-  return acc;
 }
 
 // A workgroup's row tile staged in LDS: the row offsets of rows r0..r0+R
@@ -104,44 +105,98 @@ __device__ inline bool stage_row_tile(RowTileLds<R, CAP>& t, int n, const int32_
   return true;
 }
 
-// ens_row_product with the column indices from a staged tile (sci =
-// t.ci - t.rp[0], so sci[k] is entry k's index).
-template <typename T, int S>
-__device__ inline typename EnsMap<T, S>::vt ens_row_product_lds(const int32_t* sci, const T* __restrict__ vals,
-                                                                const T* __restrict__ x, int64_t k0, int64_t k1,
-                                                                int sub) {
-  using M = EnsMap<T, S>;
-  using vt = typename M::vt;
-  const vt* vv = (const vt*)vals + sub;
-  const vt* xv = (const vt*)x + sub;
-  vt acc = (vt)0;
-  int64_t k = k0;
-  for (; k + 2 < k1; k += 3) {
-    int32_t c[3];
-    vt a[3], b[3];
+// sum_k vals[k] x[ci[k]] over the entries k0 .. k1 of a row for the V samples
+// of lane `sub`, in precision TA (TV and TX widened as they are read): lane
+// group g of KS takes the entries k0 + g, k0 + g + KS, ..., and the butterfly
+// over the groups leaves the sum in every one.  The loads of a split row are
+// predicated one by one, U in flight; with the row unrolled whole and every
+// load issued at once the same products ran 6 to 10 % slower.
+template <int S, int V, int KS, typename TA, typename TV, typename TX>
+__device__ inline typename vec_t<TA, V>::type row_sum(const int32_t* ci, const TV* __restrict__ vals,
+                                                      const TX* __restrict__ x, int64_t k0, int64_t k1, int sub,
+                                                      int g) {
+  constexpr int L = S / V;
+  typedef typename vec_t<TV, V>::type av;
+  typedef typename vec_t<TX, V>::type xv;
+  typename vec_t<TA, V>::type acc = (typename vec_t<TA, V>::type)0;
+  const av* vv = (const av*)vals + sub;
+  const xv* xx = (const xv*)x + sub;
+  if constexpr (KS == 1) {
+    int64_t k = k0;
+    for (; k + 2 < k1; k += 3) {
+      int32_t c[3];
+      av a[3];
+      xv b[3];
 #pragma unroll
-    for (int j = 0; j < 3; ++j) c[j] = sci[k + j];
+      for (int j = 0; j < 3; ++j) c[j] = ci[k + j];
 #pragma unroll
-    for (int j = 0; j < 3; ++j) a[j] = load_stream(vv + (k + j) * M::L);
+      for (int j = 0; j < 3; ++j) a[j] = load_stream(vv + (k + j) * L);
 #pragma unroll
-    for (int j = 0; j < 3; ++j) b[j] = xv[(int64_t)c[j] * M::L];
+      for (int j = 0; j < 3; ++j) b[j] = xx[(int64_t)c[j] * L];
 #pragma unroll
-    for (int j = 0; j < 3; ++j) acc += a[j] * b[j];
+      for (int j = 0; j < 3; ++j)
+#pragma unroll
+        for (int v = 0; v < V; ++v) acc[v] += (TA)a[j][v] * (TA)b[j][v];
+    }
+    for (; k < k1; ++k) {
+      const av a = load_stream(vv + k * L);
+      const xv b = xx[(int64_t)ci[k] * L];
+#pragma unroll
+      for (int v = 0; v < V; ++v) acc[v] += (TA)a[v] * (TA)b[v];
+    }
+  } else {
+    constexpr int U = KS == 2 ? 9 : 4;
+    for (int64_t k = k0 + g; k < k1; k += KS * U) {
+      av a[U];
+      xv b[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (k + u * KS < k1) a[u] = load_stream(vv + (k + u * KS) * L);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (k + u * KS < k1) b[u] = xx[(int64_t)ci[k + u * KS] * L];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (k + u * KS < k1)
+#pragma unroll
+          for (int v = 0; v < V; ++v) acc[v] += (TA)a[u][v] * (TA)b[u][v];
+    }
+#pragma unroll
+    for (int off = L; off < L * KS; off <<= 1)
+#pragma unroll
+      for (int v = 0; v < V; ++v) acc[v] += __shfl_xor(acc[v], off, 64);
   }
-  for (; k < k1; ++k) acc += load_stream(vv + k * M::L) * xv[(int64_t)sci[k] * M::L];
   return acc;
 }
 
-// Row product of row `row` (local index lr in the tile) through the staged
-// tile when it was staged, else from global memory.
-template <typename T, int S, int R, int CAP>
-__device__ inline typename EnsMap<T, S>::vt tile_row_product(const RowTileLds<R, CAP>& t, bool staged, int lr,
-                                                             const int32_t* __restrict__ ci,
-                                                             const T* __restrict__ vals, const T* __restrict__ x,
-                                                             int sub) {
-  const int64_t k0 = t.rp[lr], k1 = t.rp[lr + 1];
-  if (staged) return ens_row_product_lds<T, S>(t.ci - t.rp[0], vals, x, k0, k1, sub);
-  return ens_row_product<T, S>(ci, vals, x, k0, k1, sub);
+// A lane's place in a row tile of NW wavefronts: its samples sub*V .., lane
+// group g (the one with g = 0 does the row's vector work) and row.
+template <typename T, int S, int KS, int NW>
+struct RowPlace {
+  using M = EnsMap<T, S, KS>;
+  static constexpr int R = NW * M::RPW;  // rows per tile
+  int sub, g, lr;
+  __device__ inline RowPlace() {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    sub = lane % M::L;
+    g = (lane / M::L) % KS;
+    lr = wave * M::RPW + lane / M::W;
+  }
+};
+
+// Row product of a lane's row of the tile through the staged indices when
+// they were staged, else from global memory.  (t.ci - t.rp[0])[k] is entry k's
+// index.
+template <typename TA, typename T, int S, int KS, int NW, typename TV, typename TX, int R, int CAP>
+__device__ inline typename vec_t<TA, EnsMap<T, S>::V>::type tile_row_product(const RowPlace<T, S, KS, NW>& at,
+                                                                             const RowTileLds<R, CAP>& t, bool staged,
+                                                                             const int32_t* __restrict__ ci,
+                                                                             const TV* __restrict__ vals,
+                                                                             const TX* __restrict__ x) {
+  constexpr int V = EnsMap<T, S>::V;
+  const int64_t k0 = t.rp[at.lr], k1 = t.rp[at.lr + 1];
+  if (staged) return row_sum<S, V, KS, TA>(t.ci - t.rp[0], vals, x, k0, k1, at.sub, at.g);
+  return row_sum<S, V, KS, TA>(ci, vals, x, k0, k1, at.sub, at.g);
 }
 
 // Block-wide per-sample reduction of NQ quantities over NW wavefronts.
@@ -180,20 +235,20 @@ __device__ inline void sum_rows(const double* __restrict__ src, int64_t rows, do
   __shared__ double stripe[G][P];
   const int t = threadIdx.x;
   const int g = t / P, qe = t % P;
-  double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
+  constexpr int D = 8;  // loads in flight a lane
+  double a[D];
+#pragma unroll
+  for (int d = 0; d < D; ++d) a[d] = 0.0;
   int64_t r = g;
-  for (; r + 3 * G < rows; r += 4 * G) {
-    const double v0 = src[r * P + qe];
-    const double v1 = src[(r + G) * P + qe];
-    const double v2 = src[(r + 2 * G) * P + qe];
-    const double v3 = src[(r + 3 * G) * P + qe];
-    a0 += v0;
-    a1 += v1;
-    a2 += v2;
-    a3 += v3;
+  for (; r + (D - 1) * G < rows; r += D * G) {
+    double v[D];
+#pragma unroll
+    for (int d = 0; d < D; ++d) v[d] = src[(r + d * G) * P + qe];
+#pragma unroll
+    for (int d = 0; d < D; ++d) a[d] += v[d];
   }
-  for (; r < rows; r += G) a0 += src[r * P + qe];
-  stripe[g][qe] = (a0 + a1) + (a2 + a3);
+  for (; r < rows; r += G) a[0] += src[r * P + qe];
+  stripe[g][qe] = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
   __syncthreads();
   if (t < P) {
     double acc = 0.0;

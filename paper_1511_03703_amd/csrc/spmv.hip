@@ -7,20 +7,19 @@ namespace ens {
 
 // One workgroup of 256 lanes = 4 wavefronts, each on RPW consecutive rows;
 // the tile's row offsets and column indices staged in LDS.
-template <typename T, int S>
+template <typename T, int S, int KS>
 __global__ __launch_bounds__(256) void k_ens_spmv(int n, const int32_t* __restrict__ rp,
                                                   const int32_t* __restrict__ ci, const T* __restrict__ vals,
                                                   const T* __restrict__ x, T* __restrict__ y) {
-  using M = EnsMap<T, S>;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int sub = lane % M::L;
-  const int64_t row = ((int64_t)blockIdx.x * 4 + wave) * M::RPW + lane / M::L;
-  constexpr int R = 4 * M::RPW;
+  using M = EnsMap<T, S, KS>;
+  const RowPlace<T, S, KS, 4> at;
+  constexpr int R = at.R;
   __shared__ RowTileLds<R> tile;
-  const bool staged = stage_row_tile(tile, n, rp, ci, (int64_t)blockIdx.x * R);
+  const int64_t r0 = (int64_t)blockIdx.x * R, row = r0 + at.lr;
+  const bool staged = stage_row_tile(tile, n, rp, ci, r0);
   if (row >= n) return;
-  typename M::vt acc = tile_row_product<T, S>(tile, staged, (int)(row - (int64_t)blockIdx.x * R), ci, vals, x, sub);
-  store_stream((typename M::vt*)y + row * M::L + sub, acc);
+  const typename M::vt acc = tile_row_product<T>(at, tile, staged, ci, vals, x);
+  if (at.g == 0) store_stream((typename M::vt*)y + row * M::L + at.sub, acc);
 }
 
 // Scalar CRS (Fig. "crs") with G lanes per row: lane g sums entries
@@ -71,17 +70,20 @@ __global__ __launch_bounds__(256) void k_relayout(const double* __restrict__ src
   }
 }
 
-template <typename T, int S>
-static ens_status launch_ens_spmv(const ens_graph* g, const void* vals, const void* x, void* y,
-                                  hipStream_t st) {
-  using M = EnsMap<T, S>;
-  const int64_t rows_per_block = 4 * M::RPW;
-  const int64_t blocks = (g->n + rows_per_block - 1) / rows_per_block;
+template <typename T, int S, int KS>
+static ens_status launch_ens_spmv(const ens_graph* g, const void* vals, const void* x, void* y, hipStream_t st) {
+  const int64_t R = RowPlace<T, S, KS, 4>::R, blocks = (g->n + R - 1) / R;
   if (blocks == 0) return ENS_OK;
-  hipLaunchKernelGGL((k_ens_spmv<T, S>), dim3((unsigned)blocks), dim3(256), 0, st, g->n, g->row_ptr, g->col_idx,
+  hipLaunchKernelGGL((k_ens_spmv<T, S, KS>), dim3((unsigned)blocks), dim3(256), 0, st, g->n, g->row_ptr, g->col_idx,
                      (const T*)vals, (const T*)x, (T*)y);
   ENS_LAUNCH_CHECK();
   return ENS_OK;
+}
+
+template <typename T, int S>
+static ens_status launch_ens_spmv(const ens_graph* g, const void* vals, const void* x, void* y, hipStream_t st) {
+  if (cached_matrix<T, S>(g->nnz)) return launch_ens_spmv<T, S, row_groups<T, S, false, true>()>(g, vals, x, y, st);
+  return launch_ens_spmv<T, S, row_groups<T, S, false, false>()>(g, vals, x, y, st);
 }
 
 template <typename T>
