@@ -235,8 +235,9 @@ typedef struct {
   double inner_rtol;      /* mixed: inner stop |r_in| <= inner_rtol |r_out|   */
   int32_t inner_max_iter; /* mixed: cap per inner solve (<=0: 10000)          */
   int32_t max_outer;      /* mixed: cap on refinement steps (<=0: 10)         */
-  int32_t check_every;    /* iterations between polls of the device done flag
-                             (<=0: 16)                                       */
+  int32_t check_every;    /* most iterations between polls of the device done
+                             flag (<=0: 16); fewer where the residuals' rate
+                             promises an earlier end                         */
   int32_t coupled;        /* 0: per-sample scalars and masks (default);
                              1: the coupled solve of the whole commuted
                              system (Sec. 3.4, Sec. 3.7): inner products are

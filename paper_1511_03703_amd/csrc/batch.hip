@@ -84,7 +84,9 @@ __global__ __launch_bounds__(256) void kb_update(BatchDev bd) {
   const GroupDev& g = bd.groups[bd.vec_grp[blk]];
   if (g.ctl->n_active == 0) return;
   const int64_t nchunks = (int64_t)g.n * S / VecMap<double, S>::V;
-  update_body<double, S>(nchunks, g.x, g.p, g.q, g.r, g.dinv, g.ctl, blk - g.vec0, bd.part + blk * 2 * S);
+  const Ctl* c = g.ctl;
+  update_body<double, S>(nchunks, g.x, g.p, g.q, g.r, g.dinv, [=]() { return c; }, blk - g.vec0,
+                         bd.part + blk * 2 * S);
 }
 
 template <int S>
@@ -93,7 +95,8 @@ __global__ __launch_bounds__(256) void kb_pupdate(BatchDev bd) {
   const GroupDev& g = bd.groups[bd.vec_grp[blk]];
   if (g.ctl->n_active == 0) return;
   const int64_t nchunks = (int64_t)g.n * S / VecMap<double, S>::V;
-  pupdate_body<double, S>(nchunks, g.r, g.dinv, g.p, g.ctl, blk - g.vec0);
+  const Ctl* c = g.ctl;
+  pupdate_body<double, S>(nchunks, g.r, g.dinv, g.p, [=]() { return c; }, blk - g.vec0);
 }
 
 template <int S>
@@ -179,9 +182,11 @@ static __global__ void kb_ctl_init(BatchDev bd, int ngroups, double rtol, int ma
       c->xnz = 1;
       c->n_active = 0;
       c->n_oactive = 0;
+      c->progress0 = c->progress = 0.0;
     }
     if (threadIdx.x < kMaxS) {
       const int e = threadIdx.x;
+      c->ratio[e] = 0.0;
       c->active[e] = 0;
       c->oactive[e] = 0;
       c->iters[e] = 0;

@@ -26,6 +26,10 @@
 // launch it saves).  Every kernel of the iteration returns immediately when
 // the active count is zero, and the host reads the count once per chunk of
 // iterations, so the loop ends on the device.
+#include <stddef.h>
+#include <string.h>
+
+#include <cmath>
 #include <mutex>
 #include <type_traits>
 #include <vector>
@@ -122,14 +126,71 @@ __global__ __launch_bounds__(256) void k_cg_update(int64_t nchunks, T* __restric
                                                    const T* __restrict__ dinv, const Ctl* c,
                                                    double* __restrict__ part) {
   if (c->n_active == 0) return;
-  update_body<T, S>(nchunks, x, p, q, r, dinv, c, blockIdx.x, part + (int64_t)blockIdx.x * 2 * S);
+  update_body<T, S>(nchunks, x, p, q, r, dinv, [=]() { return c; }, blockIdx.x,
+                    part + (int64_t)blockIdx.x * 2 * S);
 }
 
 template <typename T, int S>
 __global__ __launch_bounds__(256) void k_cg_pupdate(int64_t nchunks, const T* __restrict__ r,
                                                     const T* __restrict__ dinv, T* __restrict__ p, const Ctl* c) {
   if (c->n_active == 0) return;
-  pupdate_body<T, S>(nchunks, r, dinv, p, c, blockIdx.x);
+  pupdate_body<T, S>(nchunks, r, dinv, p, [=]() { return c; }, blockIdx.x);
+}
+
+// The update and the new direction of a small system, each with the reduction
+// before it inside: every workgroup sums the partial rows itself, in the order
+// of k_reduce_final, and steps its own copy of the control block (in LDS);
+// workgroup 0 writes the new state to `cout`, another block than `cin`, which
+// the others still read.  A small solve is bound by its launches (about 3 us
+// of the host's time each, and 3 to 5 us on the device whatever they do): 3 or
+// 4 an iteration instead of 5 to 7.
+template <int S, int NQ>
+__device__ inline const Ctl* fused_state(Ctl& sc, const Ctl* cin, Ctl* cout, const double* __restrict__ rows,
+                                         int nrows, int op) {
+  __shared__ double tot[2 * kMaxS];
+  static_assert(sizeof(Ctl) % 8 == 0 && sizeof(Ctl) / 8 <= 4 * kBlock, "copied in words, at most four a lane");
+  constexpr int W = sizeof(Ctl) / 8;
+  uint64_t word[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    if (threadIdx.x + i * kBlock < W) word[i] = ((const uint64_t*)cin)[threadIdx.x + i * kBlock];
+  sum_rows<NQ * S>(rows, nrows, tot);
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    if (threadIdx.x + i * kBlock < W) ((uint64_t*)&sc)[threadIdx.x + i * kBlock] = word[i];
+  __syncthreads();
+  const bool live = sc.n_active != 0;
+  if (live) {
+    if (threadIdx.x < 2 * S) sc.tot[threadIdx.x] = threadIdx.x < NQ * S ? tot[threadIdx.x] : 0.0;
+    __syncthreads();
+    finalize<S>(&sc, op, 0);
+    __syncthreads();
+  }
+  if (blockIdx.x == 0)
+    for (int i = threadIdx.x; i < W; i += kBlock) ((uint64_t*)cout)[i] = ((const uint64_t*)&sc)[i];
+  return live && (op == OP_ALPHA || sc.n_active != 0) ? &sc : nullptr;
+}
+
+template <int S>
+__global__ __launch_bounds__(256) void k_cg_update_fused(int64_t nchunks, double* __restrict__ x,
+                                                         const double* __restrict__ p, const double* __restrict__ q,
+                                                         double* __restrict__ r, const double* __restrict__ dinv,
+                                                         const Ctl* cin, Ctl* cout, const double* __restrict__ rows,
+                                                         int nrows, double* __restrict__ part) {
+  __shared__ Ctl sc;
+  update_body<double, S>(nchunks, x, p, q, r, dinv,
+                         [&]() { return fused_state<S, 1>(sc, cin, cout, rows, nrows, OP_ALPHA); }, blockIdx.x,
+                         part + (int64_t)blockIdx.x * 2 * S);
+}
+
+template <int S>
+__global__ __launch_bounds__(256) void k_cg_pupdate_fused(int64_t nchunks, const double* __restrict__ r,
+                                                          const double* __restrict__ dinv, double* __restrict__ p,
+                                                          const Ctl* cin, Ctl* cout, const double* __restrict__ rows,
+                                                          int nrows) {
+  __shared__ Ctl sc;
+  pupdate_body<double, S>(nchunks, r, dinv, p,
+                          [&]() { return fused_state<S, 2>(sc, cin, cout, rows, nrows, OP_UPDATE); }, blockIdx.x);
 }
 
 // x += d for the samples still in refinement (FP64 += FP32 correction).
@@ -267,6 +328,7 @@ struct Work {
   double* rpart;  // those of the row tiles: an FP64 solve keeps them in the fifth
                   // vector, which it does not use otherwise
   double* part1;  // first-stage sums, [kRedBlocks][2 s]
+  Ctl* ctl2 = nullptr;  // second control block of the fused iteration (null: not fused)
   void* vec[5];
   // polls copy into a stack word instead of the device context's pinned one
   // (for the entry point that must not allocate, even the context)
@@ -274,6 +336,16 @@ struct Work {
 };
 
 static size_t round256(size_t b) { return (b + 255) & ~(size_t)255; }
+
+// Values (nodes x samples) of the largest system whose iteration sums its
+// reductions in every workgroup: 1024 vector workgroups, each reading up to
+// kFusedBytes of partials where a launch of one workgroup read them once.
+// Jacobi solves, separate -> fused (us): 16^3 s = 4 855 -> 769 (0.02 M values),
+// 37^3 s = 8 4250 -> 3980 (0.4 M), 32^3 s = 32 7310 -> 6640 (1.1 M), 48^3
+// s = 16 14730 -> 14190 (1.9 M), 64^3 s = 8 22550 -> 22500 (2.2 M), 96^3 s = 4
+// 59100 -> 59000 (3.7 M).
+constexpr int64_t kFusedValues = 1 << 21;
+constexpr int64_t kFusedBytes = 32 << 10;
 
 // Largest grid of any kernel that writes block partials for this problem.
 static int64_t max_partial_blocks(int64_t n, int s) {
@@ -305,6 +377,11 @@ static size_t ws_layout(int64_t n, int s, bool mixed, Work* w, char* base) {
     for (int i = 0; i < 5; ++i) w->vec[i] = v[i];
     // (2 S for every 4 rows at most: only a single row's do not fit)
     w->rpart = mixed || s == 1 || n < 2 ? part : (double*)v[4];
+    // the fused iteration: vectors of at most kFusedValues, and room for its
+    // second control block in the half of the fifth vector that partials never
+    // reach
+    if (!mixed && s > 1 && n * s <= kFusedValues && n * s * sizeof(double) >= 8 * sizeof(Ctl))
+      w->ctl2 = (Ctl*)((char*)v[4] + vb - round256(sizeof(Ctl)));
   }
   return off;
 }
@@ -330,33 +407,48 @@ static void reduce(const Work& w, const double* part, int64_t nrows, int op, int
   hipLaunchKernelGGL((k_reduce_final<S, NQ>), dim3(1), dim3(kBlock), 0, st, w.part1, r, w.ctl, op, arg, gate);
 }
 
-static ens_status poll_active(const Work& w, bool outer, hipStream_t st, int32_t* out) {
-  Ctl* ctl = w.ctl;
-  if (w.pageable_poll) {
-    int32_t h = 0;
-    ENS_HIP_TRY(hipMemcpyAsync(&h, outer ? &ctl->n_oactive : &ctl->n_active, sizeof(int32_t),
-                               hipMemcpyDeviceToHost, st));
-    ENS_HIP_TRY(hipStreamSynchronize(st));
-    prof_collect();
-    *out = h;
-    return ENS_OK;
+// The words of the control block a poll reads, in one copy.
+struct PollWords {
+  double progress0, progress;
+  int32_t n_active, n_oactive;
+};
+static_assert(offsetof(Ctl, progress) == offsetof(Ctl, progress0) + 8 &&
+                  offsetof(Ctl, n_active) == offsetof(Ctl, progress0) + 16 &&
+                  offsetof(Ctl, n_oactive) == offsetof(Ctl, progress0) + 20 && sizeof(PollWords) == 24,
+              "polled words lie side by side");
+
+static ens_status poll(const Work& w, hipStream_t st, PollWords* out) {
+  void* to = out;
+  if (!w.pageable_poll) {
+    DeviceCtx* cx = device_ctx();
+    if (!cx) {
+      set_error("device context unavailable");
+      return ENS_E_HIP;
+    }
+    to = cx->host_flag;
   }
-  DeviceCtx* cx = device_ctx();
-  if (!cx) {
-    set_error("device context unavailable");
-    return ENS_E_HIP;
-  }
-  ENS_HIP_TRY(hipMemcpyAsync(cx->host_flag, outer ? &ctl->n_oactive : &ctl->n_active, sizeof(int32_t),
-                             hipMemcpyDeviceToHost, st));
+  ENS_HIP_TRY(hipMemcpyAsync(to, &w.ctl->progress0, sizeof(PollWords), hipMemcpyDeviceToHost, st));
   ENS_HIP_TRY(hipStreamSynchronize(st));
   prof_collect();
-  *out = *cx->host_flag;
+  if (to != out) memcpy(out, to, sizeof(PollWords));
   return ENS_OK;
 }
 
-// q = A p, the partials of p.q (w.rpart) and their reduction into alpha.
+// Iterations until the next poll, at most `every`: fewer when the residuals,
+// falling at the rate since the last poll (prev at iteration kp; the start at
+// 0), will meet the tolerance sooner.  Iterations launched past that are empty,
+// but launched all the same: a solve of 35 polled every 16 launched 48.
+static int until_poll(int every, const PollWords& pw, double prev, int kp, int k) {
+  if (!(pw.progress > 1.0) || !(prev > pw.progress) || !std::isfinite(prev) || k <= kp) return every;
+  const double left = std::log(pw.progress) * (k - kp) / std::log(prev / pw.progress);
+  if (!(left < every)) return every;
+  const int c = (int)std::ceil(0.9 * left);
+  return c < 1 ? 1 : c;
+}
+
+// q = A p and the partials of p.q (w.rpart); returns their number.
 template <typename T, int S, int KS>
-static void product_launch(const ens_graph* g, const T* vals, const T* p, T* q, const Work& w, hipStream_t st) {
+static unsigned product_launch(const ens_graph* g, const T* vals, const T* p, T* q, const Work& w, hipStream_t st) {
   const unsigned sb = grid_for(g->n, RowPlace<T, S, KS, kProdWaves<KS>>::R);
   const int kid = sizeof(T) == 8 ? ENS_K_SPMV_F64 : ENS_K_SPMV_F32;
   const double wv = sizeof(T);
@@ -364,22 +456,56 @@ static void product_launch(const ens_graph* g, const T* vals, const T* p, T* q, 
   hipLaunchKernelGGL((k_cg_spmv_dot<T, S, KS>), dim3(sb), dim3(64 * kProdWaves<KS>), 0, st, g->n, g->row_ptr,
                      g->col_idx, vals, p, q, w.ctl, w.rpart);
   prof_end(kid, st, (double)g->nnz * (S * wv + 4.0) + 4.0 * (g->n + 1) + 2.0 * g->n * S * wv);
-  reduce<S, 1>(w, w.rpart, sb, OP_ALPHA, 0, 1, st);
+  return sb;
 }
 
 template <typename T, int S>
-static void product(const ens_graph* g, const T* vals, const T* p, T* q, const Work& w, hipStream_t st) {
-  if (cached_matrix<T, S>(g->nnz)) product_launch<T, S, row_groups<T, S, true, true>()>(g, vals, p, q, w, st);
-  else product_launch<T, S, row_groups<T, S, true, false>()>(g, vals, p, q, w, st);
+static unsigned product(const ens_graph* g, const T* vals, const T* p, T* q, const Work& w, hipStream_t st) {
+  if (cached_matrix<T, S>(g->nnz)) return product_launch<T, S, row_groups<T, S, true, true>()>(g, vals, p, q, w, st);
+  return product_launch<T, S, row_groups<T, S, true, false>()>(g, vals, p, q, w, st);
+}
+
+// The iteration of a small FP64 system (Work::ctl2): the state passes from
+// ctl to ctl2 with alpha and back with beta.
+template <int S>
+static void cg_iteration_fused(const ens_graph* g, const double* vals, double* x, double* r, double* p, double* q,
+                               double* dinv, const Work& w, hipStream_t st) {
+  const int64_t nchunks = (int64_t)g->n * S / VecMap<double, S>::V;
+  const unsigned vb = grid_for(nchunks, (int64_t)kBlock * kU);
+  const unsigned sb = product<double, S>(g, vals, p, q, w, st);
+  // few enough partial rows to sum in every workgroup, after a stage if not
+  auto rows = [&](const double* part, int64_t n, auto quantities, int* count) -> const double* {
+    constexpr int P = quantities * S;
+    if (n * P * (int64_t)sizeof(double) <= kFusedBytes) {
+      *count = (int)n;
+      return part;
+    }
+    const int64_t most = kFusedBytes / (P * (int64_t)sizeof(double));
+    int64_t b = n / 64;
+    if (b > most) b = most;
+    if (b > kRedBlocks) b = kRedBlocks;
+    hipLaunchKernelGGL((k_reduce_stage1<P>), dim3((unsigned)b), dim3(kBlock), 0, st, part, n, w.part1, w.ctl, 1);
+    *count = (int)b;
+    return w.part1;
+  };
+  int nr = 0;
+  const double* pr = rows(w.rpart, sb, std::integral_constant<int, 1>(), &nr);
+  hipLaunchKernelGGL(k_cg_update_fused<S>, dim3(vb), dim3(kBlock), 0, st, nchunks, x, p, q, r, dinv, w.ctl, w.ctl2, pr,
+                     nr, w.part);
+  pr = rows(w.part, vb, std::integral_constant<int, 2>(), &nr);
+  hipLaunchKernelGGL(k_cg_pupdate_fused<S>, dim3(vb), dim3(kBlock), 0, st, nchunks, r, dinv, p, w.ctl2, w.ctl, pr, nr);
 }
 
 // Launches of one CG iteration (A, reductions, B, reductions, C).
 template <typename T, int S>
 static void cg_iteration(const ens_graph* g, const T* vals, T* x, T* r, T* p, T* q, T* dinv, const Work& w, int k,
                          hipStream_t st) {
+  if constexpr (sizeof(T) == 8)
+    if (w.ctl2) return cg_iteration_fused<S>(g, vals, x, r, p, q, dinv, w, st);
   const int64_t nchunks = (int64_t)g->n * S / VecMap<T, S>::V;
   const unsigned vb = grid_for(nchunks, (int64_t)kBlock * kU);
-  product<T, S>(g, vals, p, q, w, st);
+  const unsigned sb = product<T, S>(g, vals, p, q, w, st);
+  reduce<S, 1>(w, w.rpart, sb, OP_ALPHA, 0, 1, st);
   hipLaunchKernelGGL((k_cg_update<T, S>), dim3(vb), dim3(kBlock), 0, st, nchunks, x, p, q, r, dinv, w.ctl, w.part);
   reduce<S, 2>(w, w.part, vb, OP_UPDATE, k, 1, st);
   hipLaunchKernelGGL((k_cg_pupdate<T, S>), dim3(vb), dim3(kBlock), 0, st, nchunks, r, dinv, p, w.ctl);
@@ -393,18 +519,23 @@ template <typename T, int S>
 static ens_status cg_loop(const ens_graph* g, const T* vals, T* x, T* r, T* p, T* q, T* dinv, Work& w,
                           int max_iter, int check_every, hipStream_t st, int pause_at = 0,
                           int* paused_after = nullptr) {
-  for (int k0 = 0; k0 < max_iter; k0 += check_every) {
-    const int k1 = k0 + check_every < max_iter ? k0 + check_every : max_iter;
+  double prev = INFINITY;
+  for (int k0 = 0, kp = 0, step = check_every; k0 < max_iter;) {
+    const int k1 = step < max_iter - k0 ? k0 + step : max_iter;
     for (int k = k0 + 1; k <= k1; ++k) cg_iteration<T, S>(g, vals, x, r, p, q, dinv, w, k, st);
     ENS_LAUNCH_CHECK();
-    int32_t act = 0;
-    ens_status s2 = poll_active(w, false, st, &act);
+    PollWords pw;
+    ens_status s2 = poll(w, st, &pw);
     if (s2 != ENS_OK) return s2;
-    if (act == 0) break;
-    if (pause_at > 0 && act <= pause_at && k1 < max_iter) {
+    if (pw.n_active == 0) break;
+    if (pause_at > 0 && pw.n_active <= pause_at && k1 < max_iter) {
       *paused_after = k1;
       return ENS_OK;
     }
+    step = until_poll(check_every, pw, k0 == 0 ? pw.progress0 : prev, kp, k1);
+    prev = pw.progress;
+    kp = k1;
+    k0 = k1;
   }
   return ENS_OK;
 }
@@ -513,6 +644,8 @@ __global__ void k_ctl_compact(const Ctl* __restrict__ src, Ctl* __restrict__ dst
     dst->xnz = src->xnz;
     dst->n_active = m;
     dst->n_oactive = 0;
+    dst->progress0 = src->progress0;
+    dst->progress = src->progress;
   }
   if (j < kMaxS) {
     const bool live = j < H && j < m;
@@ -524,6 +657,7 @@ __global__ void k_ctl_compact(const Ctl* __restrict__ src, Ctl* __restrict__ dst
     dst->bnorm2[j] = src->bnorm2[e];
     dst->rel_res[j] = src->rel_res[e];
     dst->orr_prev[j] = src->orr_prev[e];
+    dst->ratio[j] = src->ratio[e];
     dst->active[j] = live ? src->active[e] : 0;
     dst->oactive[j] = 0;
     dst->iters[j] = src->iters[e];
@@ -664,10 +798,10 @@ static ens_status cg_mixed(const ens_graph* g, const double* vals, const float* 
     if (outer == 0)
       hipLaunchKernelGGL(k_zero_where<S>, dim3(grid_for(total, 256 * 8)), dim3(kBlock), 0, st, total, x, w.ctl);
     ENS_LAUNCH_CHECK();
-    int32_t act = 0;
-    ens_status rc = poll_active(w, true, st, &act);
+    PollWords pw;
+    ens_status rc = poll(w, st, &pw);
     if (rc != ENS_OK) return rc;
-    if (act == 0) break;
+    if (pw.n_oactive == 0) break;
     cg_start<float, S>(n, r, dinv, p, d, w, st);
     ENS_LAUNCH_CHECK();
     rc = cg_loop<float, S>(g, vals32, d, r, p, q, dinv, w, o.inner_max_iter, o.check_every, st);
@@ -742,10 +876,10 @@ static ens_status cg_scalar_one(const ens_graph* g, const double* vals, const do
     const int k1 = k0 + o.check_every < o.max_iter ? k0 + o.check_every : o.max_iter;
     scalar_iters<G>(g, vals, x, w, k0, k1, st);
     ENS_LAUNCH_CHECK();
-    int32_t act = 0;
-    ens_status rc = poll_active(w, false, st, &act);
+    PollWords pw;
+    ens_status rc = poll(w, st, &pw);
     if (rc != ENS_OK) return rc;
-    if (act == 0) break;
+    if (pw.n_active == 0) break;
   }
   scalar_finish<G>(g, vals, b, x, w, st);
   ENS_LAUNCH_CHECK();
@@ -853,7 +987,8 @@ static void mg_iterations(const ens_graph* g, const T* vals, const MgPlan& plan,
   const unsigned db = grid_for(n, mg_dot_rows<T, S>(g->nnz));  // row tiles of the cycle's last pass
   const unsigned vb = grid_for(nchunks, (int64_t)kBlock * kU);
   for (int k = k0 + 1; k <= k1; ++k) {
-    product<T, S>(g, vals, p, q, w, st);
+    const unsigned sb = product<T, S>(g, vals, p, q, w, st);
+    reduce<S, 1>(w, w.rpart, sb, OP_ALPHA, 0, 1, st);
     hipLaunchKernelGGL((k_mg_update_r<T, S>), dim3(vb), dim3(kBlock), 0, st, nchunks, x, p, q, r, w.ctl, w.part);
     reduce<S, 2>(w, w.part, vb, OP_UPDATE_R, k, 1, st);
     // the cycle's last fine-level pass also writes the r . z partials, one
@@ -862,6 +997,27 @@ static void mg_iterations(const ens_graph* g, const T* vals, const MgPlan& plan,
     reduce<S, 1>(w, w.rpart, db, OP_BETA, 0, 1, st);
     hipLaunchKernelGGL((k_mg_pz<T, S>), dim3(vb), dim3(kBlock), 0, st, nchunks, z, p, w.ctl);
   }
+}
+
+// Iterations until every sample has stopped or max_iter, polled as in cg_loop.
+template <typename T, int S>
+static ens_status mg_loop(const ens_graph* g, const T* vals, const MgPlan& plan, T* x, T* r, T* p, T* q, T* z,
+                          const Work& w, int max_iter, int check_every, hipStream_t st) {
+  double prev = INFINITY;
+  for (int k0 = 0, kp = 0, step = check_every; k0 < max_iter;) {
+    const int k1 = step < max_iter - k0 ? k0 + step : max_iter;
+    mg_iterations<T, S>(g, vals, plan, x, r, p, q, z, w, k0, k1, st);
+    ENS_LAUNCH_CHECK();
+    PollWords pw;
+    ens_status rc = poll(w, st, &pw);
+    if (rc != ENS_OK) return rc;
+    if (pw.n_active == 0) break;
+    step = until_poll(check_every, pw, k0 == 0 ? pw.progress0 : prev, kp, k1);
+    prev = pw.progress;
+    kp = k1;
+    k0 = k1;
+  }
+  return ENS_OK;
 }
 
 // z = M r, p = z and rho = r.z for the active samples.
@@ -888,15 +1044,8 @@ static ens_status cg_mg(const ens_graph* g, const double* vals, const double* b,
   hipLaunchKernelGGL(k_zero_where<S>, dim3(grid_for(total, 256 * 8)), dim3(kBlock), 0, st, total, x, w.ctl);
   mg_start<double, S>(n, plan, r, z, p, w, st);
   ENS_LAUNCH_CHECK();
-  for (int k0 = 0; k0 < o.max_iter; k0 += o.check_every) {
-    const int k1 = k0 + o.check_every < o.max_iter ? k0 + o.check_every : o.max_iter;
-    mg_iterations<double, S>(g, vals, plan, x, r, p, q, z, w, k0, k1, st);
-    ENS_LAUNCH_CHECK();
-    int32_t act = 0;
-    ens_status rc = poll_active(w, false, st, &act);
-    if (rc != ENS_OK) return rc;
-    if (act == 0) break;
-  }
+  ens_status rc = mg_loop<double, S>(g, vals, plan, x, r, p, q, z, w, o.max_iter, o.check_every, st);
+  if (rc != ENS_OK) return rc;
   residual<S, double>(g, vals, x, b, (double*)nullptr, w, OP_TRUE, 0, st);
   ENS_LAUNCH_CHECK();
   return ENS_OK;
@@ -920,21 +1069,15 @@ static ens_status cg_mixed_mg(const ens_graph* g, const double* vals, const floa
     if (outer == 0)
       hipLaunchKernelGGL(k_zero_where<S>, dim3(grid_for(total, 256 * 8)), dim3(kBlock), 0, st, total, x, w.ctl);
     ENS_LAUNCH_CHECK();
-    int32_t act = 0;
-    ens_status rc = poll_active(w, true, st, &act);
+    PollWords pw;
+    ens_status rc = poll(w, st, &pw);
     if (rc != ENS_OK) return rc;
-    if (act == 0) break;
+    if (pw.n_oactive == 0) break;
     hipLaunchKernelGGL(k_fill_zero<float>, dim3(grid_for(total, 256)), dim3(256), 0, st, total, d);
     mg_start<float, S>(n, plan, r, z, p, w, st);
     ENS_LAUNCH_CHECK();
-    for (int k0 = 0; k0 < o.inner_max_iter; k0 += o.check_every) {
-      const int k1 = k0 + o.check_every < o.inner_max_iter ? k0 + o.check_every : o.inner_max_iter;
-      mg_iterations<float, S>(g, vals32, plan, d, r, p, q, z, w, k0, k1, st);
-      ENS_LAUNCH_CHECK();
-      rc = poll_active(w, false, st, &act);
-      if (rc != ENS_OK) return rc;
-      if (act == 0) break;
-    }
+    rc = mg_loop<float, S>(g, vals32, plan, d, r, p, q, z, w, o.inner_max_iter, o.check_every, st);
+    if (rc != ENS_OK) return rc;
     hipLaunchKernelGGL(k_ir_update<S>, dim3(grid_for(total, 256 * 8)), dim3(kBlock), 0, st, total, x, d, w.ctl);
     ENS_LAUNCH_CHECK();
   }

@@ -20,11 +20,15 @@ struct Ctl {
   int32_t active[kMaxS], oactive[kMaxS], iters[kMaxS], oiters[kMaxS], kiter[kMaxS], status[kMaxS];
   int32_t zero_b[kMaxS];
   int32_t compacted[kMaxS];  // the sample finished in the compacted ensemble
+  // what a poll reads: the largest |r|^2 / tol^2 of the samples that iterate, at
+  // the start and now, and their number
+  double progress0, progress;
   int32_t n_active, n_oactive;
   double rtol, inner_rtol;
   int32_t max_iter, inner_max_iter, max_outer, mixed;
   int32_t coupled;
   int32_t xnz;  // set when the initial guess has a nonzero entry
+  double ratio[kMaxS];  // |r|^2 / tol^2
   double tot[2 * kMaxS];
 };
 
@@ -66,6 +70,7 @@ __device__ void finalize(Ctl* c, int op, int arg) {
           c->status[e] = ENS_SAMPLE_MAXITER;
           c->active[e] = 1;
         }
+        c->ratio[e] = t0 / c->tol2[e];
         break;
       }
       case OP_RHO: {  // t0 = r.z
@@ -103,6 +108,7 @@ __device__ void finalize(Ctl* c, int op, int arg) {
           c->iters[e] += 1;
           c->kiter[e] += 1;
           const int cap = c->mixed ? c->inner_max_iter : c->max_iter;
+          c->ratio[e] = t1 / c->tol2[e];
           if (!isfinite(t0) || !isfinite(t1)) {
             c->status[e] = ENS_SAMPLE_NONFINITE;
             c->active[e] = 0;
@@ -125,6 +131,7 @@ __device__ void finalize(Ctl* c, int op, int arg) {
           c->iters[e] += 1;
           c->kiter[e] += 1;
           const int cap = c->mixed ? c->inner_max_iter : c->max_iter;
+          c->ratio[e] = t1 / c->tol2[e];
           if (!isfinite(t1)) {
             c->status[e] = ENS_SAMPLE_NONFINITE;
             c->active[e] = 0;
@@ -187,6 +194,7 @@ __device__ void finalize(Ctl* c, int op, int arg) {
             const double it = c->inner_rtol * c->inner_rtol * t0;
             const double fl = 0.09 * rt * rt * t1;
             c->tol2[e] = it > fl ? it : fl;
+            c->ratio[e] = t0 / c->tol2[e];
             c->active[e] = 1;
             c->oiters[e] += 1;
           }
@@ -199,12 +207,16 @@ __device__ void finalize(Ctl* c, int op, int arg) {
   __syncthreads();
   if (threadIdx.x == 0) {
     int na = 0, no = 0;
+    double most = 0.0;
     for (int j = 0; j < S; ++j) {
       na += c->active[j];
       no += c->oactive[j];
+      if (c->active[j] && c->ratio[j] > most) most = c->ratio[j];
     }
     c->n_active = na;
     c->n_oactive = no;
+    c->progress = most;
+    if (op == OP_START || op == OP_OUTER) c->progress0 = most;
   }
 }
 
@@ -245,9 +257,11 @@ static __global__ void k_ctl_init(Ctl* c, double rtol, double inner_rtol, int ma
     c->xnz = 0;
     c->n_active = 0;
     c->n_oactive = 0;
+    c->progress0 = c->progress = 0.0;
   }
   if (threadIdx.x < kMaxS) {
     const int e = threadIdx.x;
+    c->ratio[e] = 0.0;
     c->active[e] = 0;
     c->oactive[e] = 0;
     c->iters[e] = 0;
@@ -379,22 +393,16 @@ __device__ inline void spmv_dot_body(int n, const int32_t* __restrict__ rp, cons
 }
 
 // B: x += alpha p; r -= alpha q; z = D^-1 r for chunk block `blk`; partials
-// r.z, r.r to dst[2][S].  Samples that are not active stay frozen.
-template <typename T, int S>
+// r.z, r.r to dst[2][S].  Samples that are not active stay frozen.  state()
+// gives the control block (null: nothing is to be done), called by every lane
+// while the vectors are on their way.
+template <typename T, int S, typename State>
 __device__ inline void update_body(int64_t nchunks, T* __restrict__ x, const T* __restrict__ p,
                                    const T* __restrict__ q, T* __restrict__ r, const T* __restrict__ dinv,
-                                   const Ctl* c, int64_t blk, double* __restrict__ dst) {
+                                   State state, int64_t blk, double* __restrict__ dst) {
   using M = VecMap<T, S>;
   using vt = typename M::vt;
   const int sub = (threadIdx.x & 63) % M::L;
-  vt al;
-  int act[M::V];
-#pragma unroll
-  for (int v = 0; v < M::V; ++v) {
-    const int e = M::sample(sub, v);
-    act[v] = c->active[e];
-    al[v] = act[v] ? (T)c->alpha[e] : (T)0;
-  }
   double acc[2][M::VS];
 #pragma unroll
   for (int j = 0; j < M::VS; ++j) acc[0][j] = acc[1][j] = 0.0;
@@ -410,6 +418,16 @@ __device__ inline void update_body(int64_t nchunks, T* __restrict__ x, const T* 
       xv[u] = load_stream((const vt*)x + i);
       dv[u] = load_stream((const vt*)dinv + i);
     }
+  }
+  const Ctl* c = state();
+  if (!c) return;
+  vt al;
+  int act[M::V];
+#pragma unroll
+  for (int v = 0; v < M::V; ++v) {
+    const int e = M::sample(sub, v);
+    act[v] = c->active[e];
+    al[v] = act[v] ? (T)c->alpha[e] : (T)0;
   }
 #pragma unroll
   for (int u = 0; u < kU; ++u) {
@@ -445,24 +463,14 @@ __device__ inline void update_body(int64_t nchunks, T* __restrict__ x, const T* 
   block_partials<S, M::VS, 2, kBlock / 64>(acc, dst);
 }
 
-// C: p = D^-1 r + beta p for the samples still active, chunk block `blk`.
-template <typename T, int S>
+// C: p = D^-1 r + beta p for the samples still active, chunk block `blk`;
+// state() as in update_body.
+template <typename T, int S, typename State>
 __device__ inline void pupdate_body(int64_t nchunks, const T* __restrict__ r, const T* __restrict__ dinv,
-                                    T* __restrict__ p, const Ctl* c, int64_t blk) {
+                                    T* __restrict__ p, State state, int64_t blk) {
   using M = VecMap<T, S>;
   using vt = typename M::vt;
   const int sub = (threadIdx.x & 63) % M::L;
-  vt be;
-  int act[M::V];
-  bool any = false;
-#pragma unroll
-  for (int v = 0; v < M::V; ++v) {
-    const int e = M::sample(sub, v);
-    act[v] = c->active[e];
-    be[v] = act[v] ? (T)c->beta[e] : (T)0;
-    any |= act[v] != 0;
-  }
-  if (!any) return;
   const int64_t base = blk * kBlock * kU + threadIdx.x;
   vt pv[kU], rv[kU], dv[kU];
 #pragma unroll
@@ -474,6 +482,19 @@ __device__ inline void pupdate_body(int64_t nchunks, const T* __restrict__ r, co
       dv[u] = load_stream((const vt*)dinv + i);
     }
   }
+  const Ctl* c = state();
+  if (!c) return;
+  vt be;
+  int act[M::V];
+  bool any = false;
+#pragma unroll
+  for (int v = 0; v < M::V; ++v) {
+    const int e = M::sample(sub, v);
+    act[v] = c->active[e];
+    be[v] = act[v] ? (T)c->beta[e] : (T)0;
+    any |= act[v] != 0;
+  }
+  if (!any) return;
 #pragma unroll
   for (int u = 0; u < kU; ++u) {
     const int64_t i = base + u * kBlock;

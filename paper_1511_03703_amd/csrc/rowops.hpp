@@ -239,15 +239,13 @@ __device__ inline void sum_rows(const double* __restrict__ src, int64_t rows, do
   double a[D];
 #pragma unroll
   for (int d = 0; d < D; ++d) a[d] = 0.0;
-  int64_t r = g;
-  for (; r + (D - 1) * G < rows; r += D * G) {
+  for (int64_t r = g; r < rows; r += D * G) {
     double v[D];
 #pragma unroll
-    for (int d = 0; d < D; ++d) v[d] = src[(r + d * G) * P + qe];
+    for (int d = 0; d < D; ++d) v[d] = r + d * G < rows ? src[(r + d * G) * P + qe] : 0.0;
 #pragma unroll
     for (int d = 0; d < D; ++d) a[d] += v[d];
   }
-  for (; r < rows; r += G) a[0] += src[r * P + qe];
   stripe[g][qe] = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
   __syncthreads();
   if (t < P) {
