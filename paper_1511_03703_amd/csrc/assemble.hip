@@ -2,12 +2,13 @@
 //
 // Alg. "assembly" (Sec. 4) loops over cells and scatters each element matrix
 // into the global matrix with atomic adds.  Here the loop is turned inside
-// out: a lane owns one matrix row (one node) of one sample, visits the (up
-// to 8) elements around the node in ascending element id and adds the
-// element row K_e[a_i][.] into a 27-entry register row.  No atomics are
-// needed, each entry is 0 + K_e1 + K_e2 + ... in ascending element order,
-// and since every K_e is formed from a symmetric table with the same
-// operations for (a,b) and (b,a) the assembled matrix is bitwise symmetric.
+// out: a lane owns one matrix row (one node) of one sample, visits the 8
+// elements around an interior node in ascending element id and adds the
+// element row K_e[a_i][.] into a 27-entry register row (a boundary row is an
+// identity row and needs none).  No atomics are needed, each entry sums its
+// elements in ascending order, and since every K_e is formed from a symmetric
+// table with the same operations for (a,b) and (b,a) the assembled matrix is
+// bitwise symmetric.
 // The coefficient at each element's Gauss points is evaluated once per
 // workgroup tile into LDS (k_assemble_tile).  The writes of a row are
 // sample-contiguous ([nnz][s]).
@@ -32,9 +33,7 @@ constexpr int kAsmMaxM = 16;
 // loading (and spilling) a table per element.
 struct Q1Tables {
   double G[8][8][8];   // [q][a][b]: grad N_a . grad N_b (reference), symmetric in (a,b)
-  double N[8][8];      // [q][a]: N_a at Gauss point q
   double dN[8][8][3];  // [q][a][d]: reference derivative of N_a along axis d
-  double NN[8][8][8];  // [q][a][b]: N_a N_b at Gauss point q
 };
 
 constexpr Q1Tables q1_tables() {
@@ -50,7 +49,6 @@ constexpr Q1Tables q1_tables() {
         l[k] = ax[k] ? s3[k] : 1.0 - s3[k];
         d[k] = ax[k] ? 1.0 : -1.0;
       }
-      t.N[q][a] = l[0] * l[1] * l[2];
       t.dN[q][a][0] = d[0] * l[1] * l[2];
       t.dN[q][a][1] = l[0] * d[1] * l[2];
       t.dN[q][a][2] = l[0] * l[1] * d[2];
@@ -62,20 +60,11 @@ constexpr Q1Tables q1_tables() {
         t.G[q][a][b] = dot;
         t.G[q][b][a] = dot;
       }
-    for (int a = 0; a < 8; ++a)
-      for (int b = 0; b < 8; ++b) t.NN[q][a][b] = t.N[q][a] * t.N[q][b];
   }
   return t;
 }
 
 __device__ constexpr Q1Tables kQ1 = q1_tables();
-
-// 1D factors of the Q1 shape functions at the two Gauss points of an axis:
-// kL1[q][b] = l_b(g_q), l_0 = 1 - t, l_1 = t, g_q = (1 -+ 1/sqrt 3)/2 (the
-// same values the tables above are products of).
-__device__ constexpr double kL1[2][2] = {
-    {1.0 - 0.5 * (1.0 - 0.57735026918962576451), 0.5 * (1.0 - 0.57735026918962576451)},
-    {1.0 - 0.5 * (1.0 + 0.57735026918962576451), 0.5 * (1.0 + 0.57735026918962576451)}};
 
 // Node tiles of the assemblies: a workgroup owns R = TX x TY x TZ nodes
 // (one lane per row and sample); the elements touching the tile form an
@@ -88,111 +77,130 @@ struct AsmTile {
   static_assert(TX * TY * TZ == R, "tile shape");
 };
 
-// LDS slot of Gauss point q of tile element le for sample sb: the 8 points
-// of an element are stored in the order q ^ (le & 7), so that the lanes of a
-// wavefront, which read the same q of consecutive elements, hit different
-// banks without padding the rows.
-template <int SB>
+// LDS slot of Gauss point q of tile element le (of NE) for sample sb: point by
+// point, so that the lanes of a wavefront, which read the same q of consecutive
+// elements, hit different banks and all points lie at fixed offsets of one.
+template <int NE, int SB>
 __device__ inline int kslot(int le, int q, int sb) {
-  return ((le * 8 + (q ^ (le & 7))) * SB) + sb;
+  return (q * NE + le) * SB + sb;
 }
 
-// LDS doubles of a tile's KL factors: for each of the M modes its 1D
-// eigenfunction at the 2 Gauss abscissae of each element column along x,
-// and the products Y(qy) Z(qz) for each (y, z) element pair of the tile's
-// element block.
+// LDS doubles of a tile's KL factors: the 1D eigenfunctions of the M modes at
+// the 2 Gauss abscissae of each element column along x (by their x index), y
+// and z (by mode).
 template <int EX, int EY, int EZ>
-__host__ __device__ constexpr int tab_doubles(int M) { return M * (2 * EX + 4 * EY * EZ); }
+__host__ __device__ constexpr int tab_doubles(int M) { return M * 2 * (EX + EY + EZ); }
 
 // Phase 1 of the tiled assemblies: the coefficient at the 8 Gauss points of
 // every element of the tile's EX x EY x EZ element block (origin ex0, ey0,
 // ez0) for the SB samples e0.., times `scale`, into s_k[kslot(le, q, sb)].
-// The sample-independent factors are staged in s_tab first (the x factors
-// and the y-z products, read from the KL table once per workgroup), and
-// each lane keeps the coefficients c_m = sigma sqrt(lambda_m) y_m of its one
-// sample in registers (the NT lanes are a multiple of SB, so a lane's items
-// all have the same sample).  An item is one element and sample, its PTS =
-// 8 Gauss points (PTS = 4: half an element, the lanes then a multiple of
-// 2 SB with a fixed z half each); whole elements read 3 instead of 4 LDS
-// factor pairs per 8 points and mode, which made the linear assembly 3.6 %
-// faster (5.10 -> 4.92 ms in alternating runs).  The sum of a
-// point is kappa0 + sum_m X (c_m (Y Z)) in mode order whatever PTS.  Ends with
-// a barrier.
-template <int NT, int SB, int EX, int EY, int EZ, bool SCALED, int PTS = 4>
-__device__ inline void tile_coefficients(int N, const double* __restrict__ kl_sqrt_lam,
+// The 1D factors are staged in s_tab first, and each lane keeps the
+// coefficients c_m = scale sigma sqrt(lambda_m) y_m of its one sample in registers
+// (the NT lanes are a multiple of SB, so a lane's items all have the same
+// sample).  An item is one sample's half column of elements along x: the modes
+// with the same x factor X_i collapse into one weight for each of the column's
+// 4 (y, z) Gauss lines,
+//   W_i = sum over the modes m with x index i of c_m Y_m Z_m,
+// scale kappa = scale kappa0 + sum_i X_i W_i, kColSlots x indices at a time (the 10 leading
+// modes have 3).  Half columns of 3 and 2 elements: 30 items a sample for the 32
+// lanes; with an element an item every mode cost its multiply-adds at every
+// point, 120 operations instead of about 37 an element at 10 modes, and three
+// times the LDS reads.  Ends with a barrier.
+constexpr int kColSlots = 3;
+
+template <int NT, int SB, int EX, int EY, int EZ>
+__device__ __forceinline__ void tile_coefficients(int N, const double* __restrict__ kl_sqrt_lam,
                                          const int32_t* __restrict__ kl_triple, const double* __restrict__ kl_phi,
                                          int M, double kappa0, double sigma, const double* __restrict__ xi, int e0,
                                          int ex0, int ey0, int ez0, double scale, double* s_tab, double* s_k) {
-  static_assert(PTS == 4 || PTS == 8, "an item is half an element or a whole one");
-  constexpr int HALVES = 8 / PTS;  // z halves of an element held by different lanes
-  static_assert(NT % (HALVES * SB) == 0, "a lane's items must share one sample and z half");
-  constexpr int NE = EX * EY * EZ;
+  constexpr int HX = (EX + 1) / 2;  // elements of a half column (the second may hold one less)
+  static_assert(NT % SB == 0 && 2 * EY * EZ <= NT / SB, "an item a lane, all of a lane's of one sample");
   const int64_t two_n = 2 * (int64_t)N;
-  double* s_x = s_tab;               // [M][EX][2]
-  double* s_yz = s_tab + M * 2 * EX;  // [M][EY][EZ][4], index qy + 2 qz
-  for (int t = threadIdx.x; t < M * 2 * EX; t += NT) {
-    const int m = t / (2 * EX), l = (t / 2) % EX, q = t & 1;
-    const int el = ex0 + l;
-    s_x[t] = (el >= 0 && el < N) ? kl_phi[kl_triple[3 * m] * two_n + 2 * el + q] : 0.0;
+  double* s_x = s_tab;             // [x index][EX][2]
+  double* s_y = s_x + M * 2 * EX;  // [M][EY][2]
+  double* s_z = s_y + M * 2 * EY;  // [M][EZ][2]
+  for (int t = threadIdx.x; t < M * 2 * (EX + EY + EZ); t += NT) {
+    int64_t k, at;
+    if (t < M * 2 * EX) {
+      k = t / (2 * EX);
+      at = 2 * (int64_t)ex0 + t % (2 * EX);
+    } else if (t < M * 2 * (EX + EY)) {
+      const int r = t - M * 2 * EX;
+      k = kl_triple[3 * (r / (2 * EY)) + 1];
+      at = 2 * (int64_t)ey0 + r % (2 * EY);
+    } else {
+      const int r = t - M * 2 * (EX + EY);
+      k = kl_triple[3 * (r / (2 * EZ)) + 2];
+      at = 2 * (int64_t)ez0 + r % (2 * EZ);
+    }
+    s_tab[t] = at >= 0 && at < two_n ? kl_phi[k * two_n + at] : 0.0;
   }
-  for (int t = threadIdx.x; t < M * 4 * EY * EZ; t += NT) {
-    const int m = t / (4 * EY * EZ), r = t % (4 * EY * EZ);
-    const int ly = r / (4 * EZ), lz = (r / 4) % EZ, qy = r & 1, qz = (r >> 1) & 1;
-    const int ey = ey0 + ly, ez = ez0 + lz;
-    double v = 0.0;
-    if (ey >= 0 && ey < N && ez >= 0 && ez < N)
-      v = kl_phi[kl_triple[3 * m + 1] * two_n + 2 * ey + qy] * kl_phi[kl_triple[3 * m + 2] * two_n + 2 * ez + qz];
-    s_yz[t] = v;
-  }
-  const int sb = threadIdx.x % SB, hz = HALVES == 2 ? (threadIdx.x / SB) & 1 : 0;
+  const int sb = threadIdx.x % SB;
   double c[kAsmMaxM];
 #pragma unroll
-  for (int m = 0; m < kAsmMaxM; ++m) c[m] = m < M ? sigma * kl_sqrt_lam[m] * xi[(int64_t)(e0 + sb) * M + m] : 0.0;
+  for (int m = 0; m < kAsmMaxM; ++m) c[m] = m < M ? scale * sigma * kl_sqrt_lam[m] * xi[(int64_t)(e0 + sb) * M + m] : 0.0;
+  int nx = 0;  // x indices in use: 0 .. nx - 1
+  for (int m = 0; m < M; ++m) nx = kl_triple[3 * m] >= nx ? kl_triple[3 * m] + 1 : nx;
   __syncthreads();
-  // a lane's items are elements le0, le0 + D, le0 + 2 D, ... (D = NT / 2 SB):
-  // their block coordinates advance by D's digits with carries instead of
-  // being divided out per item
-  constexpr int D = NT / (HALVES * SB);
-  constexpr int DX = D % EX, DY = (D / EX) % EY, DZ = D / (EX * EY);
-  int le = threadIdx.x / (HALVES * SB);
-  int lx = le % EX, ly = (le / EX) % EY, lz = le / (EX * EY);
-  for (; le < NE; le += D) {
-    const int ex = ex0 + lx, ey = ey0 + ly, ez = ez0 + lz;
-    if (ex >= 0 && ey >= 0 && ez >= 0 && ex < N && ey < N && ez < N) {
-      double kq[PTS];  // Gauss points qx + 2 qy + 4 (hz or qz)
+  const int col = (threadIdx.x / SB) >> 1, lx0 = (threadIdx.x / SB) & 1 ? HX : 0;
+  const int ly = col % EY, lz = col / EY;
+  const int ey = ey0 + ly, ez = ez0 + lz;
+  if (lz < EZ && ey >= 0 && ez >= 0 && ey < N && ez < N) {
+    double kq[HX][8];  // Gauss points qx + 2 (qy + 2 qz)
 #pragma unroll
-      for (int q = 0; q < PTS; ++q) kq[q] = 0.0;
-      const double* px = s_x + lx * 2;
-      const double* pyz = s_yz + (ly * EZ + lz) * 4 + 2 * hz;
+    for (int l = 0; l < HX; ++l)
+#pragma unroll
+      for (int q = 0; q < 8; ++q) kq[l][q] = kappa0 * scale;
+    for (int i0 = 0; i0 < nx; i0 += kColSlots) {
+      double w[kColSlots][4];
+#pragma unroll
+      for (int i = 0; i < kColSlots; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) w[i][j] = 0.0;
       // every mode up to the largest M, each skipped by a uniform branch
       // when absent: the coefficients stay in fixed registers
 #pragma unroll
       for (int m = 0; m < kAsmMaxM; ++m) {
         if (m < M) {
-          const double fx[2] = {px[m * 2 * EX], px[m * 2 * EX + 1]};
-          double yz[PTS / 2];
+          const int slot = kl_triple[3 * m] - i0;
+          const double* py = s_y + (m * EY + ly) * 2;
+          const double* pz = s_z + (m * EZ + lz) * 2;
+          const double y0 = py[0], y1 = py[1], z0 = c[m] * pz[0], z1 = c[m] * pz[1];
 #pragma unroll
-          for (int j = 0; j < PTS / 2; ++j) yz[j] = c[m] * pyz[m * 4 * EY * EZ + j];
-#pragma unroll
-          for (int q = 0; q < PTS; ++q) kq[q] += fx[q & 1] * yz[q >> 1];
+          for (int i = 0; i < kColSlots; ++i)
+            if (slot == i) {
+              w[i][0] = fma(y0, z0, w[i][0]);
+              w[i][1] = fma(y1, z0, w[i][1]);
+              w[i][2] = fma(y0, z1, w[i][2]);
+              w[i][3] = fma(y1, z1, w[i][3]);
+            }
         }
       }
 #pragma unroll
-      for (int q = 0; q < PTS; ++q) {
-        const double k = kappa0 + kq[q];
-        s_k[kslot<SB>(le, q + 4 * hz, sb)] = SCALED ? k * scale : k;
+      for (int i = 0; i < kColSlots; ++i) {
+        if (i0 + i < nx) {
+#pragma unroll
+          for (int l = 0; l < HX; ++l) {
+            // (the slot past a shorter half's last element is read, not used)
+            const double* px = s_x + ((i0 + i) * EX + lx0 + l) * 2;
+            const double f0 = px[0], f1 = px[1];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              kq[l][2 * j] = fma(f0, w[i][j], kq[l][2 * j]);
+              kq[l][2 * j + 1] = fma(f1, w[i][j], kq[l][2 * j + 1]);
+            }
+          }
+        }
       }
     }
-    lx += DX;
-    ly += DY;
-    lz += DZ;
-    if (lx >= EX) {
-      lx -= EX;
-      ++ly;
-    }
-    if (ly >= EY) {
-      ly -= EY;
-      ++lz;
+#pragma unroll
+    for (int l = 0; l < HX; ++l) {
+      const int lx = lx0 + l, ex = ex0 + lx;
+      if (lx < EX && ex >= 0 && ex < N) {
+        const int le = lx + EX * (ly + EY * lz);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) s_k[kslot<EX * EY * EZ, SB>(le, q, sb)] = kq[l][q];
+      }
     }
   }
   __syncthreads();
@@ -203,17 +211,17 @@ __device__ inline void tile_coefficients(int N, const double* __restrict__ kl_sq
 // take indices 8 apart (same XCD, dispatched together) so their partial
 // writes of each row's sample ensemble meet in one L2.
 template <int TX, int TY, int TZ, int G>
-__device__ inline void tile_decode(int N, int64_t bid, int64_t* tile_id, int* sg, int* x0, int* y0, int* z0) {
-  const int n1 = N + 1;
-  const int ntx = (n1 + TX - 1) / TX, nty = (n1 + TY - 1) / TY, ntz = (n1 + TZ - 1) / TZ;
-  const int64_t tiles = (int64_t)ntx * ntz * nty;
-  int64_t tile;
+__device__ inline void tile_decode(int N, uint32_t bid, int64_t* tile_id, int* sg, int* x0, int* y0, int* z0) {
+  const uint32_t n1 = N + 1;
+  const uint32_t ntx = (n1 + TX - 1) / TX, nty = (n1 + TY - 1) / TY, ntz = (n1 + TZ - 1) / TZ;
+  const uint32_t tiles = ntx * ntz * nty;  // fits: at most 257 x 513 x 257
+  uint32_t tile;
   if (G > 1 && (bid / (8 * G)) < tiles / 8) {
-    const int64_t blk = bid / (8 * G), rem = bid % (8 * G);
+    const uint32_t blk = bid / (8 * G), rem = bid % (8 * G);
     *sg = (int)(rem / 8);
     tile = blk * 8 + rem % 8;
   } else {
-    const int64_t rest = bid - (tiles / 8) * 8 * G;  // the last tiles % 8 tiles, plainly
+    const uint32_t rest = bid - (tiles / 8) * 8 * G;  // the last tiles % 8 tiles, plainly
     *sg = (int)(G > 1 ? rest % G : 0);
     tile = (G > 1 ? (tiles / 8) * 8 + rest / G : bid);
   }
@@ -224,16 +232,96 @@ __device__ inline void tile_decode(int N, int64_t bid, int64_t* tile_id, int* sg
   *y0 = (int)(tile / ntz) * TY;
 }
 
+// Advection of one node's row, scale times sum_q N_a (v.dN_b) / 8 over its eight
+// elements, for the 27 neighbours into s_adv: products over the axes of what
+// the two elements of an axis add up to, the 1D mass (1/6, 2/3, 1/6) and first
+// derivative (-1/2, 0, 1/2); the same for every interior row.
+__device__ inline void advection_entries(double scale, double vx, double vy, double vz, double* s_adv) {
+  if (threadIdx.x >= 27) return;
+  const int d[3] = {(int)threadIdx.x % 3, ((int)threadIdx.x / 3) % 3, (int)threadIdx.x / 9};
+  double m[3], g[3];
+  for (int k = 0; k < 3; ++k) {
+    m[k] = d[k] == 1 ? 2.0 / 3.0 : 1.0 / 6.0;
+    g[k] = 0.5 * (d[k] - 1);
+  }
+  s_adv[threadIdx.x] = scale * (vx * (g[0] * m[1] * m[2]) + vy * (m[0] * g[1] * m[2]) + vz * (m[0] * m[1] * g[2]));
+}
+
+// Off-diagonal diffusion entries of an interior row (rx, ry, rz of the tile,
+// sample sbl) from its four elements below (EZO -1) or above (0) the node,
+// added to acc[neighbour] in ascending element order.  l_0 l_1 is the same at
+// both Gauss points of an axis, so grad N_a . grad N_b does not depend on the
+// point's position along the axes in which a and b differ: the coefficient is
+// summed along those first (38 operations an element instead of 56).
+template <typename T, int SB, int EZO>
+__device__ __forceinline__ void diffusion_elements(const double* s_k, int rx, int ry, int rz, int sbl,
+                                                   double (&acc)[27]) {
+  const double* sk = s_k + kslot<T::NE, SB>(rx + T::EX * (ry + T::EY * (rz + 1 + EZO)), 0, sbl);
+#pragma unroll
+  for (int ey_off = -1; ey_off <= 0; ++ey_off)
+#pragma unroll
+    for (int ex_off = -1; ex_off <= 0; ++ex_off) {
+      const int ai = (-ex_off) + 2 * (-ey_off) + 4 * (-EZO);
+      double kq[8], sx[4], sy[4], sz[4];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) kq[q] = sk[kslot<T::NE, SB>(1 + ex_off + T::EX * (1 + ey_off), q, 0)];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        sx[j] = kq[2 * j] + kq[2 * j + 1];                              // j = qy + 2 qz
+        sy[j] = kq[(j & 1) + 4 * (j >> 1)] + kq[(j & 1) + 4 * (j >> 1) + 2];  // qx + 2 qz
+        sz[j] = kq[j] + kq[j + 4];                                      // qx + 2 qy
+      }
+      const double sxy[2] = {sx[0] + sx[1], sx[2] + sx[3]};  // by qz
+      const double sxz[2] = {sx[0] + sx[2], sx[1] + sx[3]};  // by qy
+      const double syz[2] = {sy[0] + sy[2], sy[1] + sy[3]};  // by qx
+      auto entry = [&](int b) -> double& {
+        return acc[(EZO + (b >> 2) + 1) * 9 + (ey_off + ((b >> 1) & 1) + 1) * 3 + ex_off + (b & 1) + 1];
+      };
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        entry(ai ^ 1) = fma(sx[j], kQ1.G[2 * j][ai][ai ^ 1], entry(ai ^ 1));
+        entry(ai ^ 2) = fma(sy[j], kQ1.G[(j & 1) + 4 * (j >> 1)][ai][ai ^ 2], entry(ai ^ 2));
+        entry(ai ^ 4) = fma(sz[j], kQ1.G[j][ai][ai ^ 4], entry(ai ^ 4));
+      }
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        entry(ai ^ 3) = fma(sxy[j], kQ1.G[4 * j][ai][ai ^ 3], entry(ai ^ 3));
+        entry(ai ^ 5) = fma(sxz[j], kQ1.G[2 * j][ai][ai ^ 5], entry(ai ^ 5));
+        entry(ai ^ 6) = fma(syz[j], kQ1.G[j][ai][ai ^ 6], entry(ai ^ 6));
+      }
+      entry(ai ^ 7) = fma(sxy[0] + sxy[1], kQ1.G[0][ai][ai ^ 7], entry(ai ^ 7));
+      __builtin_amdgcn_sched_barrier(0);  // (an element's coefficients live at a time)
+    }
+}
+
+// Whether any row of the wavefront has neighbours on the boundary.
+__device__ inline bool near_boundary(int ii, int jj, int kk, int N) {
+  return __ballot(ii <= 1 || jj <= 1 || kk <= 1 || ii >= N - 1 || jj >= N - 1 || kk >= N - 1) != 0;
+}
+
+// Entries T0 .. T1 - 1 of an interior row whose neighbour lies on the boundary
+// become zero (near: near_boundary).
+template <int T0, int T1>
+__device__ inline void zero_edges(bool near, int ii, int jj, int kk, int N, double (&acc)[27]) {
+  if (!near) return;
+  auto edge = [&](int d, int i) { return d == 0 ? i == 1 : d == 2 ? i == N - 1 : false; };
+#pragma unroll
+  for (int t = T0; t < T1; ++t) {
+    double v = acc[t];
+    asm("" : "+v"(v));  // a select, not a branch around what v comes from
+    acc[t] = edge(t % 3, ii) | edge((t / 3) % 3, jj) | edge(t / 9, kk) ? 0.0 : v;
+  }
+}
+
 // Ensemble assembly (Alg. "assembly" made atomic-free by row ownership): a
 // workgroup owns a 4 x 2 x 4 block of nodes for all S samples (32 S lanes,
 // one per row and sample, sample fastest).  It first evaluates the
 // coefficient (times h/8) at the 8 Gauss points of each of the 5 x 3 x 5
 // elements touching the block, once per element and sample, into LDS
-// (153.6 KB for s = 32; the Gauss points of an element in a swizzled order
-// instead of padded rows); then each (row, sample) lane gathers its (up to
-// 8) elements from LDS in ascending element id and adds the element rows in
-// that fixed order, so the sums are deterministic and the coefficient is
-// evaluated 2.3 times per row instead of 8.  A wavefront holds whole sample
+// (153.6 KB for s = 32); then each (row, sample) lane of an interior row
+// gathers its 8 elements from LDS in ascending element id and adds the element
+// rows in that fixed order, so the sums are deterministic and the coefficient
+// is evaluated 2.3 times per row instead of 8.  A wavefront holds whole sample
 // ensembles of its rows, so every store of a matrix entry writes full
 // 128-byte lines (s = 32: two FP64 lines, one FP32 line); split over
 // workgroups of fewer samples, the partial lines of the FP32 copy alone took
@@ -245,8 +333,13 @@ __device__ inline void tile_decode(int N, int64_t bid, int64_t* tile_id, int* sg
 // the maximum over its rows per sample to bpart[tile][s].
 // ADV: the advection-diffusion operator D + alpha C instead (the linear part
 // of the nonlinear problem's Jacobian, Eq. fenl_lin_sys with beta = 0):
-// every element row also gets alpha (h^2/8) C_ab, C_ab = sum_q N_a (v.dN_b)
-// one 8x8 table per launch.
+// every element row also gets alpha (h^2/8) C_ab, C_ab = sum_q N_a (v.dN_b),
+// summed over the elements for the 27 neighbours (advection_entries).
+// Bound by its FP64 operations and its writes, which overlap only in part.  With
+// the coefficient summed along columns, 38 operations an element and no
+// boundary tests around them, FP64 values of 64^3, s = 16 take 231 us (396
+// before; the writes alone 134), s = 32 447 (578; 269), 128^3, s = 32 with the
+// FP32 copy 4.11 ms (4.65; 3.20).
 // The body of k_assemble_tile for tile `bid`; xzero (nullable): a solution
 // [n][s] whose rows of the tile are set to zero too.
 template <int S, int BND, bool ADV>
@@ -263,10 +356,10 @@ __device__ __forceinline__ void assemble_tile_body(int N, const double* __restri
   constexpr int SB = S, NT = T::R * S;
   constexpr int TX = T::TX, TY = T::TY, EX = T::EX, EY = T::EY, NE = T::NE;
   constexpr int NTAB = tab_doubles<T::EX, T::EY, T::EZ>(kAsmMaxM);
-  static_assert(NT <= NE * 8 * SB && NTAB >= 64, "tile shape");
+  static_assert(NT <= NE * 8 * SB && NTAB >= 27, "tile shape");
   // [kappa at the Gauss points, [element][q][sample] | the tile's 1D KL
   // factors]; after the coefficients the factor area takes the advection
-  // table, after the row pass the kappa area the per-row bounds
+  // entries, after the row pass the kappa area the per-row bounds
   __shared__ double s_buf[NE * 8 * SB + NTAB];
   double* s_k = s_buf;
   double* s_tab = s_buf + NE * 8 * SB;
@@ -274,19 +367,13 @@ __device__ __forceinline__ void assemble_tile_body(int N, const double* __restri
   const int n1 = N + 1;
   int64_t tile_id;
   int sg, x0, y0, z0;
-  tile_decode<TX, TY, T::TZ, 1>(N, bid, &tile_id, &sg, &x0, &y0, &z0);
+  tile_decode<TX, TY, T::TZ, 1>(N, (uint32_t)bid, &tile_id, &sg, &x0, &y0, &z0);
   const int e0 = 0;
   const double h = 1.0 / (double)N;
-  tile_coefficients<NT, SB, EX, EY, T::EZ, true, 8>(N, kl_sqrt_lam, kl_triple, kl_phi, M, kappa0, sigma, xi, e0,
+  tile_coefficients<NT, SB, EX, EY, T::EZ>(N, kl_sqrt_lam, kl_triple, kl_phi, M, kappa0, sigma, xi, e0,
                                                   x0 - 1, y0 - 1, z0 - 1, h * 0.125, s_tab, s_k);
   if (ADV) {
-    if (threadIdx.x < 64) {
-      const int a = threadIdx.x >> 3, b = threadIdx.x & 7;
-      double c = 0.0;
-      for (int q = 0; q < 8; ++q)
-        c += kQ1.N[q][a] * (vx * kQ1.dN[q][b][0] + vy * kQ1.dN[q][b][1] + vz * kQ1.dN[q][b][2]);
-      s_adv[threadIdx.x] = c;
-    }
+    advection_entries(alpha * h * h, vx, vy, vz, s_adv);
     __syncthreads();
   }
 
@@ -298,100 +385,72 @@ __device__ __forceinline__ void assemble_tile_body(int N, const double* __restri
   double qrow = 0.0;  // this row's Gershgorin ratio (BND)
   const int e = e0 + sb;
   if (live) {
-  const int64_t row = (int64_t)ii + n1 * ((int64_t)jj + (int64_t)n1 * kk);
-
-  double acc[27];
-#pragma unroll
-  for (int t = 0; t < 27; ++t) acc[t] = 0.0;
-  int nelem = 0;
-#pragma unroll
-  for (int ez_off = -1; ez_off <= 0; ++ez_off)
-#pragma unroll
-    for (int ey_off = -1; ey_off <= 0; ++ey_off)
-#pragma unroll
-      for (int ex_off = -1; ex_off <= 0; ++ex_off) {
-        const int ex = ii + ex_off, ey = jj + ey_off, ez = kk + ez_off;
-        if (ex < 0 || ey < 0 || ez < 0 || ex >= N || ey >= N || ez >= N) continue;
-        ++nelem;
-        const int ai = (-ex_off) + 2 * (-ey_off) + 4 * (-ez_off);
-        const int le = (rx + 1 + ex_off) + EX * ((ry + 1 + ey_off) + EY * (rz + 1 + ez_off));
-        double kq[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) kq[q] = s_k[kslot<SB>(le, q, sb)];
-#pragma unroll
-        for (int b = 0; b < 8; ++b) {
-          if (b == ai) continue;  // the diagonal follows from the row sum below
-          const int dx = ex_off + (b & 1), dy = ey_off + ((b >> 1) & 1), dz = ez_off + ((b >> 2) & 1);
-          const int slot27 = (dz + 1) * 9 + (dy + 1) * 3 + (dx + 1);
-          double kab = 0.0;
-#pragma unroll
-          for (int q = 0; q < 8; ++q) kab += kq[q] * kQ1.G[q][ai][b];
-          if (ADV) kab += h * h * 0.125 * alpha * s_adv[ai * 8 + b];
-          acc[slot27] += kab;
-        }
+    const int64_t row = (int64_t)ii + n1 * ((int64_t)jj + (int64_t)n1 * kk);
+    const bool bnd_row = (ii == 0 || ii == N || jj == 0 || jj == N || kk == 0 || kk == N);
+    const int64_t at = (int64_t)row_ptr[row] * S + e;
+    // with 32 samples a wavefront's store covers whole 128-byte lines (FP32
+    // and FP64), which then go out non-temporally (measured 4.98 -> 4.87 ms at
+    // 128^3); smaller ensembles write partial lines, whose pieces are better
+    // merged in L2 by ordinary stores
+    constexpr bool NT = S == 32;
+    auto st = [](auto* p, auto v) {
+      if (NT) __builtin_nontemporal_store(v, p);
+      else *p = v;
+    };
+    const bool near = near_boundary(ii, jj, kk, N);
+    double dg = 1.0;
+    if (bnd_row) {  // an identity row
+      int k = 0;
+      for (int t = 0; t < 27; ++t) {
+        const int x = ii + t % 3 - 1, y = jj + (t / 3) % 3 - 1, z = kk + t / 9 - 1;
+        if (x < 0 || y < 0 || z < 0 || x > N || y > N || z > N) continue;
+        const double v = t == 13 ? 1.0 : 0.0;
+        if (values) st(values + at + k * S, v);
+        if (values32) st(values32 + at + k * S, (float)v);
+        ++k;
       }
-
-  // every element row sums to zero (the shape functions sum to one, so
-  // sum_b grad N_b = 0, and C_ab = sum_q N_a v . grad N_b too), hence so
-  // does the assembled row before the boundary conditions: its diagonal is
-  // minus the sum of its other entries (added in ascending neighbour order),
-  // which saves the 8 diagonal element entries' Gauss sums
-  {
-    double off = 0.0;
+      qrow = 1.0;
+    } else {
+      double acc[27];
 #pragma unroll
-    for (int t = 0; t < 27; ++t)
-      if (t != 13) off += acc[t];
-    acc[13] = -off;
-  }
-  const bool bnd_row = (ii == 0 || ii == N || jj == 0 || jj == N || kk == 0 || kk == N);
-  const int64_t start = row_ptr[row];
-  double sabs = 0.0, dg = 0.0;
-  // with 32 samples a wavefront's store covers whole 128-byte lines (FP32
-  // and FP64), which then go out non-temporally (measured 4.98 -> 4.87 ms at
-  // 128^3); smaller ensembles write partial lines, whose pieces are better
-  // merged in L2 by ordinary stores
-  constexpr bool NT = S == 32;
-  auto st = [](auto* p, auto v) {
-    if (NT) __builtin_nontemporal_store(v, p);
-    else *p = v;
-  };
-  auto put = [&](int64_t k, int slot27, double v) {
-    if (values) st(values + k, v);
-    if (values32) st(values32 + k, (float)v);
-    if (BND) {
-      const double vc = BND == 1 ? (double)(float)v : v;  // the value the cycle runs on
-      sabs += fabs(vc);
-      if (slot27 == 13) dg = vc;
-    }
-  };
-  if (ii >= 2 && jj >= 2 && kk >= 2 && ii <= N - 2 && jj <= N - 2 && kk <= N - 2) {
-    // all 27 neighbours interior: entry t of the row is neighbour t
+      for (int t = 0; t < 27; ++t) acc[t] = 0.0;
+      diffusion_elements<T, SB, -1>(s_k, rx, ry, rz, sb, acc);
+      diffusion_elements<T, SB, 0>(s_k, rx, ry, rz, sb, acc);
+      // every element row sums to zero (the shape functions sum to one, so
+      // sum_b grad N_b = 0, and C_ab = sum_q N_a v . grad N_b too), hence so
+      // does the assembled row before the boundary conditions: its diagonal is
+      // minus the sum of its other entries (added in ascending neighbour
+      // order), which saves the 8 diagonal element entries' Gauss sums
+      double off = 0.0;
 #pragma unroll
-    for (int t = 0; t < 27; ++t) put((start + t) * S + e, t, acc[t]);
-  } else {
-    int pos = 0;
-#pragma unroll
-    for (int dz = -1; dz <= 1; ++dz)
-#pragma unroll
-      for (int dy = -1; dy <= 1; ++dy)
-#pragma unroll
-        for (int dx = -1; dx <= 1; ++dx) {
-          const int x = ii + dx, yy = jj + dy, z = kk + dz;
-          if (x < 0 || yy < 0 || z < 0 || x > N || yy > N || z > N) continue;
-          const int slot27 = (dz + 1) * 9 + (dy + 1) * 3 + (dx + 1);
-          double v = acc[slot27];
-          const bool bnd_col = (x == 0 || x == N || yy == 0 || yy == N || z == 0 || z == N);
-          if (bnd_row) v = (slot27 == 13) ? 1.0 : 0.0;
-          else if (bnd_col) v = 0.0;
-          put((start + pos) * S + e, slot27, v);
-          ++pos;
+      for (int t = 0; t < 27; ++t)
+        if (t != 13) {
+          if (ADV) acc[t] += s_adv[t];
+          off += acc[t];
         }
-  }
-  st(rhs + row * S + e, bnd_row ? 0.0 : (double)nelem * (fsrc * h * h * h * 0.125));
-  if (xzero) st(xzero + row * S + e, 0.0);
-  if (BND == 1) st((float*)dinv + row * S + e, 1.0f / (float)dg);
-  if (BND == 2) st((double*)dinv + row * S + e, 1.0 / dg);
-  if (BND) qrow = sabs / dg;
+      acc[13] = -off;
+      zero_edges<0, 27>(near, ii, jj, kk, N, acc);
+      if (BND) {
+        double sabs = 0.0;
+#pragma unroll
+        for (int t = 0; t < 27; ++t) {
+          const double vc = BND == 1 ? (double)(float)acc[t] : acc[t];  // the value the cycle runs on
+          sabs += fabs(vc);
+          if (t == 13) dg = vc;
+        }
+        qrow = sabs / dg;
+      }
+      if (values)
+#pragma unroll
+        for (int t = 0; t < 27; ++t) st(values + at + t * S, acc[t]);
+      if (values32)
+#pragma unroll
+        for (int t = 0; t < 27; ++t) st(values32 + at + t * S, (float)acc[t]);
+    }
+    st(rhs + row * S + e, bnd_row ? 0.0 : 8.0 * (fsrc * h * h * h * 0.125));  // of eight elements
+    if (xzero) st(xzero + row * S + e, 0.0);
+    if (BND == 1) st((float*)dinv + row * S + e, 1.0f / (float)dg);
+    if (BND == 2) st((double*)dinv + row * S + e, 1.0 / dg);
   }
   if (BND) {
     __syncthreads();  // every lane is done with s_k
@@ -409,8 +468,12 @@ __device__ __forceinline__ void assemble_tile_body(int N, const double* __restri
   }
 }
 
+// Waves a SIMD that the tiles in LDS allow: the registers are cut to match.
+template <int S>
+constexpr int kAsmWaves = S >= 16 ? 4 : 3;
+
 template <int S, int BND, bool ADV>
-__global__ __launch_bounds__(32 * S) void k_assemble_tile(int N, const double* __restrict__ kl_sqrt_lam,
+__global__ __launch_bounds__((32 * S), (kAsmWaves<S>)) void k_assemble_tile(int N, const double* __restrict__ kl_sqrt_lam,
                                                            const int32_t* __restrict__ kl_triple,
                                                            const double* __restrict__ kl_phi, int M, double kappa0,
                                                            double sigma, double fsrc, double alpha, double vx,
@@ -427,7 +490,7 @@ __global__ __launch_bounds__(32 * S) void k_assemble_tile(int N, const double* _
 // tile b - tile0 of group blk_grp[b] (FP64 values and load vector, the
 // solution set to zero).
 template <int S>
-__global__ __launch_bounds__(32 * S) void kb_assemble(const AsmGroupDev* __restrict__ groups,
+__global__ __launch_bounds__((32 * S), (kAsmWaves<S>)) void kb_assemble(const AsmGroupDev* __restrict__ groups,
                                                        const int32_t* __restrict__ blk_grp, int M, double kappa0,
                                                        double sigma, double fsrc) {
   const AsmGroupDev& g = groups[blk_grp[blockIdx.x]];
@@ -437,26 +500,53 @@ __global__ __launch_bounds__(32 * S) void kb_assemble(const AsmGroupDev* __restr
 
 // Residual and Jacobian of the nonlinear problem (Sec. 4, Eq.
 // diffusion_sys, Eq. fenl_lin_sys, Alg. "assembly" with alpha, beta != 0),
-// row-owned like k_assemble_tile (same tiling, the coefficient kept in LDS
-// per patch element): lane e of a row's group gathers the element
-// solution u_e of its sample for each element around the node (ascending
-// element id) and forms the element's Jacobian row a
-//   J_ab = D_ab + alpha (h^2/8) C_ab + 2 beta (h^3/8) sum_q u_q N_a N_b,
-//   D_ab = (h/8) sum_q kappa_q G_q[a][b],   C_ab = sum_q N_a (v.dN_b)
-// (C does not depend on the element: one 8x8 table per launch), with u_q
-// the interpolated solution at Gauss point q.  Since the diffusion and
+// row-owned like k_assemble_tile (same tiling, the coefficient times h/8 kept
+// in LDS per patch element).  The Jacobian's row a is
+//   J_ab = D_ab + alpha (h^2/8) C_ab + 2 beta (h^3/8) R_ab, summed over the
+//   elements, D_ab = (h/8) sum_q kappa_q G_q[a][b], C_ab = sum_q N_a (v.dN_b),
+//   R_ab = sum_q u_q N_a N_b,
+// u_q the interpolated solution at Gauss point q.  Since the diffusion and
 // advection terms are linear in u and the reaction term quadratic, the
-// element residual is
-//   F_a = sum_b (D_ab + alpha (h^2/8) C_ab + beta (h^3/8) sum_q u_q N_a N_b) u_b
+// residual is
+//   F_a = sum_b (D_ab + alpha (h^2/8) C_ab + beta (h^3/8) R_ab) u_b
 //         - (h^3/8) f sum_q N_a,
-// so no gradient of u_h is formed; the reaction sums sum_q u_q N_a N_b are
-// contracted from the nodal values directly (the triple products of the
-// shape functions factor over the axes), so u_h at the Gauss points is not
-// formed either.  Boundary rows: F = u and identity rows;
-// boundary columns of interior rows stored as zeros; load (optional) = the
+// so no gradient of u_h is formed.  Boundary rows (F = u, identity rows) need
+// no element, and every other row has all eight, so only D takes a loop over
+// them (its diagonal is minus the sum of the row's other linear entries, whose
+// sum is zero as in k_assemble_tile).  C and R come for the 27 neighbours at
+// once, as products over the axes of what the two elements of an axis add up
+// to: C has the 1D mass (1/6, 2/3, 1/6) and first derivative (-1/2, 0, 1/2),
+// the same for all rows; R contracts the 27 nodal values axis by axis with the
+// 1D triple products sum_q l_a l_b l_c, 1/2 when a = b = c and 1/6 otherwise
+// (reaction_line).  The nodal values of the tile and its rim are staged in LDS
+// (the KL factors' area) once, on their way while the coefficient is summed.
+// Boundary columns of interior rows are stored as zeros; load (optional) = the
 // source part of F.
-template <int S, int SB, bool JAC>
-__global__ __launch_bounds__(32 * SB) void k_nl_assemble(int N, const double* __restrict__ kl_sqrt_lam,
+// Bound by the issue of its FP64 operations, about 1000 a row and sample: at
+// 64^3, s = 16 F alone takes 236 us and F with the FP32 Jacobian 300 (451 and
+// 510 with C and R summed element by element and the nodal values gathered from
+// memory by every element).
+//
+// Reaction sums of one axis, times 6: from the values at the nodes -1, 0, 1
+// those of the row's neighbours -1, 0, 1.
+__device__ inline void reaction_line(double um, double u0, double up, double& rm, double& r0, double& rp) {
+  rm = um + u0;
+  rp = u0 + up;
+  r0 = fma(u0, 4.0, rm + rp);
+}
+
+// What a tile holds in LDS beside the coefficient: its KL factors, then the
+// nodal values of the tile and its rim and the 27 advection entries.
+template <typename T, int SB>
+__host__ __device__ constexpr int nl_tab_doubles() {
+  constexpr int nodes = (T::TX + 2) * (T::TY + 2) * (T::TZ + 2) * SB + 27;
+  constexpr int factors = tab_doubles<T::EX, T::EY, T::EZ>(kAsmMaxM);
+  return nodes > factors ? nodes : factors;
+}
+
+// OUT: the Jacobian in FP64 (1), in FP32 (2), both (3), or F alone (0).
+template <int S, int SB, int OUT>
+__global__ __launch_bounds__((32 * SB), 3) void k_nl_assemble(int N, const double* __restrict__ kl_sqrt_lam,
                                                          const int32_t* __restrict__ kl_triple,
                                                          const double* __restrict__ kl_phi, int M, double kappa0,
                                                          double sigma, double fsrc, double alpha, double beta,
@@ -465,163 +555,141 @@ __global__ __launch_bounds__(32 * SB) void k_nl_assemble(int N, const double* __
                                                          const double* __restrict__ u, double* __restrict__ values,
                                                          float* __restrict__ values32, double* __restrict__ F,
                                                          double* __restrict__ load) {
-  // the workgroup tiling of k_assemble_tile (SB of the S samples of a
-  // 4 x 2 x 4 node block), the coefficient kept raw (kappa0 + sum) in LDS;
-  // after the coefficients the factor area holds the advection table
-  // C_ab = sum_q N_a (v . dN_b)
-  using T = AsmTile<32, 2>;
+  using T = AsmTile<32, 2>;  // SB of the S samples of a 4 x 2 x 4 node block
   constexpr int NT = T::R * SB, G = S / SB;
-  constexpr int TX = T::TX, TY = T::TY, EX = T::EX, EY = T::EY, NE = T::NE;
-  constexpr int NTAB = tab_doubles<T::EX, T::EY, T::EZ>(kAsmMaxM);
-  static_assert(NTAB >= 64, "tile shape");
-  __shared__ double s_buf[NE * 8 * SB + NTAB];
+  constexpr int TX = T::TX, TY = T::TY, TZ = T::TZ, EX = T::EX, EY = T::EY, NE = T::NE;
+  constexpr int UX = TX + 2, UY = TY + 2, UZ = TZ + 2, NU = UX * UY * UZ * SB, LU = (NU + NT - 1) / NT;
+  __shared__ double s_buf[NE * 8 * SB + nl_tab_doubles<T, SB>()];
   double* s_k = s_buf;
   double* s_tab = s_buf + NE * 8 * SB;
-  double* s_adv = s_tab;
+  double* s_u = s_tab;         // [z][y][x][sample]
+  double* s_adv = s_tab + NU;  // advection entry of neighbour t
   int64_t tile_id;
   int sg, x0, y0, z0;
-  tile_decode<TX, TY, T::TZ, G>(N, blockIdx.x, &tile_id, &sg, &x0, &y0, &z0);
+  tile_decode<TX, TY, TZ, G>(N, blockIdx.x, &tile_id, &sg, &x0, &y0, &z0);
   const int e0 = sg * SB;
-  tile_coefficients<NT, SB, EX, EY, T::EZ, false, 8>(N, kl_sqrt_lam, kl_triple, kl_phi, M, kappa0, sigma, xi, e0,
-                                                   x0 - 1, y0 - 1, z0 - 1, 1.0, s_tab, s_k);
-  if (threadIdx.x < 64) {
-    const int a = threadIdx.x >> 3, b = threadIdx.x & 7;
-    double c = 0.0;
-    for (int q = 0; q < 8; ++q)
-      c += kQ1.N[q][a] * (vx * kQ1.dN[q][b][0] + vy * kQ1.dN[q][b][1] + vz * kQ1.dN[q][b][2]);
-    s_adv[threadIdx.x] = c;
+  const int n1 = N + 1;
+  const double h = 1.0 / (double)N;
+  double un[LU];
+#pragma unroll
+  for (int i = 0; i < LU; ++i) {
+    const int t = threadIdx.x + i * NT, node = t / SB;
+    const int x = x0 - 1 + node % UX, y = y0 - 1 + (node / UX) % UY, z = z0 - 1 + node / (UX * UY);
+    un[i] = t < NU && x >= 0 && y >= 0 && z >= 0 && x <= N && y <= N && z <= N
+                ? u[((int64_t)x + n1 * ((int64_t)y + (int64_t)n1 * z)) * S + e0 + t % SB]
+                : 0.0;
   }
+  tile_coefficients<NT, SB, EX, EY, T::EZ>(N, kl_sqrt_lam, kl_triple, kl_phi, M, kappa0, sigma, xi, e0,
+                                                  x0 - 1, y0 - 1, z0 - 1, h * 0.125, s_tab, s_k);
+#pragma unroll
+  for (int i = 0; i < LU; ++i)
+    if (threadIdx.x + i * NT < NU) s_u[threadIdx.x + i * NT] = un[i];
+  advection_entries(alpha * h * h, vx, vy, vz, s_adv);
   __syncthreads();
 
-  const int n1 = N + 1;
   const int rr = threadIdx.x / SB, sbl = threadIdx.x % SB;
   const int rx = rr % TX, ry = (rr / TX) % TY, rz = rr / (TX * TY);
   const int ii = x0 + rx, jj = y0 + ry, kk = z0 + rz;
   if (ii > N || jj > N || kk > N) return;
   const int e = e0 + sbl;
   const int64_t row = (int64_t)ii + n1 * ((int64_t)jj + (int64_t)n1 * kk);
-  const double h = 1.0 / (double)N;
-  const double wd = h * 0.125;             // diffusion: w_q / h^2
-  const double wa = h * h * 0.125 * alpha; // advection: alpha w_q / h
-  const double wr = h * h * h * 0.125;     // reaction and source: w_q
-  const double wb = wr * beta;
-  const double wrf = wr * fsrc;     // an element's load on a node
+  const bool bnd_row = (ii == 0 || ii == N || jj == 0 || jj == N || kk == 0 || kk == N);
+  const int64_t at = OUT ? (int64_t)row_ptr[row] * S + e : 0;
+  auto put = [&](int k, double v) {  // entry k of the row
+    if (OUT & 1) values[at + k * S] = v;
+    if (OUT & 2) values32[at + k * S] = (float)v;
+  };
+  const double* su = s_u + ((rz * UY + ry) * UX + rx) * SB + sbl;  // node (-1, -1, -1) of the row
+  if (bnd_row) {
+    if (OUT) {
+      int k = 0;
+      for (int t = 0; t < 27; ++t) {
+        const int x = ii + t % 3 - 1, y = jj + (t / 3) % 3 - 1, z = kk + t / 9 - 1;
+        if (x >= 0 && y >= 0 && z >= 0 && x <= N && y <= N && z <= N) put(k++, t == 13 ? 1.0 : 0.0);
+      }
+    }
+    F[row * S + e] = u[row * S + e];
+    if (load) load[row * S + e] = 0.0;
+    return;
+  }
 
+  const double wr = h * h * h * 0.125;  // reaction and source: w_q
+  const double wb = wr * beta / 216.0;  // the reaction sums are 6^3 times theirs
+  const double la = 8.0 * (wr * fsrc);  // an element's load on a node, of eight
+  double fa = 0.0, off = 0.0;
   double acc[27];
 #pragma unroll
   for (int t = 0; t < 27; ++t) acc[t] = 0.0;
-  double fa = 0.0, la = 0.0;
-  const bool bnd_row = (ii == 0 || ii == N || jj == 0 || jj == N || kk == 0 || kk == N);
-  const int64_t start = JAC ? (int64_t)row_ptr[row] : 0;
-  int pos = 0;
-  // the entries of neighbour plane dz are final once the elements below
-  // it are added (plane -1 after the lower elements, planes 0 and +1 after
-  // all): stored then, in entry order, so fewer accumulators stay live
-  const bool deep = ii >= 2 && jj >= 2 && kk >= 2 && ii <= N - 2 && jj <= N - 2 && kk <= N - 2;
-  auto store_plane = [&](int dz) {
-    if (deep) {  // all 27 neighbours interior: entry t of the row is neighbour t
+  // reaction sums of neighbour plane z over its own axes
+  auto plane_sums = [&](int z, double* r) {
+    double a[9];
 #pragma unroll
-      for (int t = (dz + 1) * 9; t < (dz + 2) * 9; ++t) {
-        if (values) values[(start + t) * S + e] = acc[t];
-        if (values32) values32[(start + t) * S + e] = (float)acc[t];
-      }
-      return;
+    for (int y = 0; y < 3; ++y) {
+      const double* p = su + (z * UY + y) * UX * SB;
+      reaction_line(p[0], p[SB], p[2 * SB], a[3 * y], a[3 * y + 1], a[3 * y + 2]);
     }
 #pragma unroll
-    for (int dy = -1; dy <= 1; ++dy)
+    for (int x = 0; x < 3; ++x) reaction_line(a[x], a[3 + x], a[6 + x], r[x], r[3 + x], r[6 + x]);
+  };
+  // entries of neighbour plane z from its linear ones and reaction sums; the
+  // linear entries of a row sum to zero, so they take differences of u (fewer
+  // digits cancel)
+  const double u0 = su[((UY + 1) * UX + 1) * SB];
+  auto finish_plane = [&](int z, const double* r) {
 #pragma unroll
-      for (int dx = -1; dx <= 1; ++dx) {
-        const int x = ii + dx, y = jj + dy, z = kk + dz;
-        if (x < 0 || y < 0 || z < 0 || x > N || y > N || z > N) continue;
-        const int slot27 = (dz + 1) * 9 + (dy + 1) * 3 + (dx + 1);
-        double v = acc[slot27];
-        const bool bnd_col = (x == 0 || x == N || y == 0 || y == N || z == 0 || z == N);
-        if (bnd_row) v = (slot27 == 13) ? 1.0 : 0.0;
-        else if (bnd_col) v = 0.0;
-        if (values) values[(start + pos) * S + e] = v;
-        if (values32) values32[(start + pos) * S + e] = (float)v;
-        ++pos;
+    for (int j = 0; j < 9; ++j) {
+      const int t = z * 9 + j;
+      const double ut = su[((z * UY + j / 3) * UX + j % 3) * SB], rb = wb * r[j];
+      if (t != 13) fa = fma(acc[t], ut - u0, fa);
+      fa = fma(rb, ut, fa);
+      acc[t] = fma(2.0, rb, acc[t]);
+    }
+    if (!OUT) return;
+    if (z == 0) zero_edges<0, 9>(true, ii, jj, kk, N, acc);
+    if (z == 1) zero_edges<9, 18>(true, ii, jj, kk, N, acc);
+    if (z == 2) zero_edges<18, 27>(true, ii, jj, kk, N, acc);
+#pragma unroll
+    for (int j = 0; j < 9; ++j) put(z * 9 + j, acc[z * 9 + j]);
+  };
+  auto linear_plane = [&](int z) {  // advection; the off-diagonal sum
+#pragma unroll
+    for (int t = z * 9; t < z * 9 + 9; ++t)
+      if (t != 13) {
+        acc[t] += s_adv[t];
+        off += acc[t];
       }
   };
 
+  // plane by plane, so that few accumulators are live: plane -1 is complete
+  // after the lower elements
+  double pm[9], p0[9], r[9];
+  diffusion_elements<T, SB, -1>(s_k, rx, ry, rz, sbl, acc);
+  plane_sums(0, pm);
+  plane_sums(1, p0);
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int ez_off = -1; ez_off <= 0; ++ez_off) {
-#pragma unroll
-    for (int ey_off = -1; ey_off <= 0; ++ey_off)
-#pragma unroll
-      for (int ex_off = -1; ex_off <= 0; ++ex_off) {
-          const int ex = ii + ex_off, ey = jj + ey_off, ez = kk + ez_off;
-          if (ex < 0 || ey < 0 || ez < 0 || ex >= N || ey >= N || ez >= N) continue;
-          const int ai = (-ex_off) + 2 * (-ey_off) + 4 * (-ez_off);
-          const int le = (rx + 1 + ex_off) + EX * ((ry + 1 + ey_off) + EY * (rz + 1 + ez_off));
-          double kq[8];
-#pragma unroll
-          for (int q = 0; q < 8; ++q) kq[q] = s_k[kslot<SB>(le, q, sbl)];
-          double ue[8];
-#pragma unroll
-          for (int b = 0; b < 8; ++b) {
-            const int64_t node = (int64_t)(ex + (b & 1)) + n1 * ((int64_t)(ey + ((b >> 1) & 1)) +
-                                                                (int64_t)n1 * (ez + ((b >> 2) & 1)));
-            ue[b] = u[node * S + e];
-          }
-          // the reaction row rn_b = sum_q u_h(q) N_a(q) N_b(q) = sum_c T_abc u_c,
-          // T_abc = sum_q N_a N_b N_c, a product over the axes of the 1D
-          // sums t(a, b, c) = sum_q l_a l_b l_c over the two Gauss points,
-          // which are 1/2 when a = b = c and 1/6 otherwise: three 2-point
-          // contractions of the element's nodal values, each pair (x0, x1)
-          // giving (x0 + x1)/6 and that plus x_a/3 at the row's own index
-          // (u_h at the Gauss points is never formed)
-          double rnv[8];
-          {
-            constexpr double k6 = 1.0 / 6.0, k3 = 1.0 / 3.0;
-            const int ax = ai & 1, ay = (ai >> 1) & 1, az = ai >> 2;
-            double t1[8], t2[8];
-#pragma unroll
-            for (int r = 0; r < 8; r += 2) {  // along x: (cx) -> (bx), r = 2 cy + 4 cz
-              const double m = (ue[r] + ue[r + 1]) * k6;
-              t1[r + ax] = fma(ue[r + ax], k3, m);
-              t1[r + 1 - ax] = m;
-            }
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {  // along y: i0 = bx + 4 cz
-              const int i0 = (k & 1) + 4 * (k >> 1);
-              const double m = (t1[i0] + t1[i0 + 2]) * k6;
-              t2[i0 + 2 * ay] = fma(t1[i0 + 2 * ay], k3, m);
-              t2[i0 + 2 * (1 - ay)] = m;
-            }
-#pragma unroll
-            for (int i0 = 0; i0 < 4; ++i0) {  // along z: i0 = bx + 2 by
-              const double m = (t2[i0] + t2[i0 + 4]) * k6;
-              rnv[i0 + 4 * az] = fma(t2[i0 + 4 * az], k3, m);
-              rnv[i0 + 4 * (1 - az)] = m;
-            }
-          }
-          la += wrf;  // sum_q N_a(q) = 1 for the 2-point rule
-#pragma unroll
-          for (int b = 0; b < 8; ++b) {
-            double dg = 0.0;
-            const double rn = rnv[b];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) dg += kq[q] * kQ1.G[q][ai][b];
-            const double lin = wd * dg + wa * s_adv[ai * 8 + b];
-            fa += (lin + wb * rn) * ue[b];
-            if (JAC) {
-              const int dx = ex_off + (b & 1), dy = ey_off + ((b >> 1) & 1), dz = ez_off + ((b >> 2) & 1);
-              acc[(dz + 1) * 9 + (dy + 1) * 3 + (dx + 1)] += lin + 2.0 * wb * rn;
-            }
-          }
-        }
-    if (JAC) {
-      if (ez_off < 0) store_plane(-1);
-      else {
-        store_plane(0);
-        store_plane(1);
-      }
-    }
+  for (int j = 0; j < 9; ++j) {
+    r[j] = pm[j] + p0[j];
+    pm[j] = fma(p0[j], 4.0, r[j]);
   }
-
-  F[row * S + e] = bnd_row ? u[row * S + e] : fa - la;
-  if (load) load[row * S + e] = bnd_row ? 0.0 : la;
+  linear_plane(0);
+  finish_plane(0, r);
+  __builtin_amdgcn_sched_barrier(0);
+  diffusion_elements<T, SB, 0>(s_k, rx, ry, rz, sbl, acc);
+  plane_sums(2, r);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int j = 0; j < 9; ++j) {
+    r[j] = p0[j] + r[j];
+    p0[j] = pm[j] + r[j];
+  }
+  linear_plane(1);
+  linear_plane(2);
+  acc[13] = -off;
+  finish_plane(1, p0);
+  finish_plane(2, r);
+  F[row * S + e] = fa - la;
+  if (load) load[row * S + e] = la;
 }
 
 // Per-sample extremes of the coefficient over the 8 N^3 Gauss points of the
@@ -913,8 +981,10 @@ extern "C" ens_status ens_nl_assemble(int32_t N, const ens_graph* graph, const v
                      prob->vz, xi, graph->row_ptr, u, values, values32, F, load)
 #define ENS_NL_CASE(SS)                                  \
   case SS:                                               \
-    if (values || values32) ENS_NL_LAUNCH(SS, true);     \
-    else ENS_NL_LAUNCH(SS, false);                       \
+    if (values && values32) ENS_NL_LAUNCH(SS, 3);        \
+    else if (values32) ENS_NL_LAUNCH(SS, 2);             \
+    else if (values) ENS_NL_LAUNCH(SS, 1);               \
+    else ENS_NL_LAUNCH(SS, 0);                           \
     break;
     ENS_NL_CASE(4)
     ENS_NL_CASE(8)
