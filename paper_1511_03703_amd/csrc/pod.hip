@@ -31,9 +31,10 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 // [z*kchunk, (z+1)*kchunk) and writes its partial product to C + z*cstride.
 // SYM (A = B): blockIdx.x counts the block pairs i <= j of the symmetric C,
 // and with a single K range the mirrored block is written too.
-// The Gram matrix of 2048 snapshots at 64^3: 20.9 ms (58 TFLOP/s of its
-// half; a large library product reaches 72 here); the lane-per-4x4 form
-// with all of C took 70.9 ms.
+// The Gram matrix of 2048 snapshots at 64^3: 18.4 ms (67 TFLOP/s of its
+// half; a large library product reaches 72 here); with a bounds test around
+// every load, workgroups in plain order and a last round of 12 in 512 it took
+// 21.1 ms, the lane-per-4x4 form with all of C 70.9 ms.
 template <int TA, int BN, int KS, bool SYM>
 __global__ __launch_bounds__(256) void k_dgemm(int64_t M, int64_t N, int64_t K, const double* __restrict__ A,
                                                int64_t lda, const double* __restrict__ B, int64_t ldb,
@@ -47,30 +48,50 @@ __global__ __launch_bounds__(256) void k_dgemm(int64_t M, int64_t N, int64_t K, 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = lane & 15, q = lane >> 4;
   const int wm = BN == 128 ? (wave >> 1) * 64 : wave * 32, wn = BN == 128 ? (wave & 1) * 64 : 0;
   int64_t bi = blockIdx.y, bj = blockIdx.x;
+  uint32_t bz = blockIdx.z;
   if (SYM) {  // pair p -> (i, j), i <= j, column by column
-    const int64_t p = blockIdx.x;
+    // workgroups are dealt to the 8 XCDs in turn: each XCD takes a run of the
+    // pairs of one K range, whose rows of A then meet in its L2
+    const uint32_t total = gridDim.x * gridDim.z, lin = bz * gridDim.x + blockIdx.x, xcd = lin % 8;
+    const uint32_t at = xcd * (total / 8) + (xcd < total % 8 ? xcd : total % 8) + lin / 8;
+    bz = at / gridDim.x;
+    const int64_t p = at % gridDim.x;
     bj = (int64_t)((sqrt(8.0 * (double)p + 1.0) - 1.0) * 0.5);
     while (bj * (bj + 1) / 2 > p) --bj;
     while ((bj + 1) * (bj + 2) / 2 <= p) ++bj;
     bi = p - bj * (bj + 1) / 2;
   }
   const int64_t i0 = bi * BM, j0 = bj * BN;
-  const int64_t kb = (int64_t)blockIdx.z * kchunk;
+  const int64_t kb = (int64_t)bz * kchunk;
   const int64_t ke = kb + kchunk < K ? kb + kchunk : K;
   double ra[UA], rb[UB];
+  // rows and columns past the edge are read from the last one (what they give
+  // is not stored), so only a K range's last slice needs a test per element
+  const int ka = TA ? tid / BM : tid % KS, kbr = tid / BN;
+  int64_t offa[TA ? 1 : UA];
+#pragma unroll
+  for (int u = 0; u < (TA ? 1 : UA); ++u) {
+    const int64_t i = i0 + (TA ? tid % BM : (tid + 256 * u) / KS);
+    offa[u] = TA ? ka * lda + (i < M ? i : M - 1) : (i < M ? i : M - 1) * lda + ka;
+  }
+  const int64_t jb = j0 + tid % BN, offb = kbr * ldb + (jb < N ? jb : N - 1);
   auto load = [&](int64_t k0) {
+    const double* Ak = A + (TA ? k0 * lda : k0);
+    const double* Bk = B + k0 * ldb;
+    if (k0 + KS <= ke) {
 #pragma unroll
-    for (int u = 0; u < UA; ++u) {
-      const int t = tid + 256 * u;
-      const int64_t k = k0 + (TA ? t / BM : t % KS), i = i0 + (TA ? t % BM : t / KS);
-      ra[u] = (i < M && k < ke) ? (TA ? A[k * lda + i] : A[i * lda + k]) : 0.0;
-    }
+      for (int u = 0; u < UA; ++u) ra[u] = TA ? (Ak + u * (256 / BM) * lda)[offa[0]] : Ak[offa[TA ? 0 : u]];
 #pragma unroll
-    for (int u = 0; u < UB; ++u) {
-      const int t = tid + 256 * u;
-      const int64_t k = k0 + t / BN, j = j0 + t % BN;
-      rb[u] = (j < N && k < ke) ? B[k * ldb + j] : 0.0;
+      for (int u = 0; u < UB; ++u) rb[u] = (Bk + u * (256 / BN) * ldb)[offb];
+      return;
     }
+    const int left = (int)(ke - k0);
+#pragma unroll
+    for (int u = 0; u < UA; ++u)
+      ra[u] = ka + (TA ? u * (256 / BM) : 0) < left ? (TA ? (Ak + u * (256 / BM) * lda)[offa[0]] : Ak[offa[TA ? 0 : u]])
+                                                    : 0.0;
+#pragma unroll
+    for (int u = 0; u < UB; ++u) rb[u] = kbr + u * (256 / BN) < left ? (Bk + u * (256 / BN) * ldb)[offb] : 0.0;
   };
   auto store = [&](int buf) {
 #pragma unroll
@@ -96,6 +117,9 @@ __global__ __launch_bounds__(256) void k_dgemm(int64_t M, int64_t N, int64_t K, 
   for (int64_t k0 = kb; k0 < ke; k0 += KS, buf ^= 1) {
     const bool more = k0 + KS < ke;
     if (more) load(k0 + KS);
+    // a wave that multiplies goes before one that loads, stores or leaves the
+    // barrier: the two on a SIMD take turns (19.9 -> 18.3 ms)
+    __builtin_amdgcn_s_setprio(1);
 #pragma unroll
     for (int kk = 0; kk < KS; kk += 4) {
       double a[MT], b[NT];
@@ -108,10 +132,11 @@ __global__ __launch_bounds__(256) void k_dgemm(int64_t M, int64_t N, int64_t K, 
 #pragma unroll
         for (int n = 0; n < NT; ++n) acc[m][n] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[m], b[n], acc[m][n], 0, 0, 0);
     }
+    __builtin_amdgcn_s_setprio(0);
     if (more) store(buf ^ 1);
     __syncthreads();
   }
-  double* Cz = C + (int64_t)blockIdx.z * cstride;
+  double* Cz = C + (int64_t)bz * cstride;
 #pragma unroll
   for (int m = 0; m < MT; ++m)
 #pragma unroll
@@ -748,11 +773,24 @@ static int product_splits(int64_t M, int64_t N, int64_t K) {
   return k_splits(tiles128(M) * ((N + bn - 1) / bn), K, 1024);
 }
 
-// The Gram product's last round of workgroups is part empty, so it takes more
-// rounds, of smaller ranges.
+// Ranges of the Gram product: of the counts that give 2 to 8 rounds of the 512
+// workgroups the chip holds at once the one whose last round is fullest, the
+// fewest ranges of equals (2048 snapshots at 64^3: 31 ranges leave the last round
+// almost empty, 21.1 ms; 30 and 15 fill it, 20.4 ms).
 static int gram_splits(int64_t n, int64_t m) {
-  const int64_t t = tiles128(m);
-  return k_splits(t * (t + 1) / 2, n, 4096);
+  const int64_t t = tiles128(m), pairs = t * (t + 1) / 2;
+  const int most = k_splits(pairs, n, 4096);
+  int best = most;
+  double fill = 0.0;
+  for (int s = most; 4 * s >= most; --s) {
+    const int64_t rounds = (pairs * s + 511) / 512;
+    const double f = (double)(pairs * s) / (double)(rounds * 512);
+    if (f >= fill) {
+      fill = f;
+      best = s;
+    }
+  }
+  return best;
 }
 
 // C [M][N] (dense) = op(A) B in `splits` K ranges; scratch [splits][M][N] for
