@@ -327,7 +327,9 @@ __device__ inline void orth_sums(const double (&v)[NV], int n, OrthLds& s) {
   __syncthreads();
 }
 
-__global__ __launch_bounds__(kOrthThreads) void k_orth(int m, int k, double* Y, int once) {
+// done (nullable): nonzero when the columns are orthonormal already.
+__global__ __launch_bounds__(kOrthThreads) void k_orth(int m, int k, double* Y, int once, const int* done) {
+  if (done && *done) return;
   __shared__ OrthLds s;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6, r = lane & 15, q = lane >> 4;
   const int tiles = (m + 15) / 16;
@@ -432,6 +434,71 @@ __global__ __launch_bounds__(kOrthThreads) void k_orth(int m, int k, double* Y, 
 // up to k = 96 (LDS: 2 k^2 doubles).  k = 64: 0.48 ms, against 11.6 ms for the
 // cyclic order's 12 sweeps in L2.
 constexpr int kJacobiLdsK = 96;
+
+// U = R^-1 for the Cholesky factor R of H = Y^T Y [k][k], k <= kJacobiLdsK, so
+// that Y U is orthonormal: all columns of a power step at once, where each keeps
+// at least 1 % of its length off the columns before it (as they do once the
+// first steps have sorted the eigenvectors; Q then is orthonormal to about
+// 1e-11, which serves between power steps).  Otherwise U = I and *done = 0, and
+// k_orth takes over.  One workgroup: the elimination [A | I] -> [R | L^-1] of the
+// matrix scaled to a unit diagonal, in LDS, k steps of one rank-one update, bound
+// by their chain (42 us for k = 64).  With the products Y^T Y and Y U over all of
+// the chip, orth(Y) of 2048 x 64 so takes 75 us, against 390 us in k_orth, whose one
+// workgroup passes over all rows; of 12 power steps the first needs k_orth.
+__global__ __launch_bounds__(1024) void k_cholesky_inverse(int k, const double* __restrict__ H,
+                                                           double* __restrict__ U, int* __restrict__ done) {
+  constexpr int kG = 16;  // wavefronts
+  extern __shared__ double s_chol[];
+  double* A = s_chol;                // [k][k + 1]
+  double* W = s_chol + k * (k + 1);  // [k][k + 1]
+  __shared__ double s_d[kJacobiLdsK];
+  const int t = threadIdx.x, ld = k + 1;
+  if (t < k) {
+    const double h = H[(int64_t)t * k + t];
+    s_d[t] = h > 0.0 ? 1.0 / sqrt(h) : 0.0;
+  }
+  __syncthreads();
+  for (int x = t; x < k * k; x += 64 * kG) {
+    const int i = x / k, j = x % k;
+    A[i * ld + j] = H[x] * s_d[i] * s_d[j];
+    W[i * ld + j] = i == j ? 1.0 : 0.0;
+  }
+  __syncthreads();
+  const int c = t & 63, g = t >> 6;  // columns c and c + 64 of every kG-th row
+  bool ok = true;
+  for (int j = 0; j < k; ++j) {
+    const double p = A[j * ld + j];
+    ok = p >= 1e-4;  // (false for NaN)
+    if (!ok) break;
+    const double inv = 1.0 / p;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int x = c + 64 * h;
+      if (x >= k) break;
+      // columns past j of A, up to j of W (its rows are L's inverse, unscaled)
+      double* const M = (x > j ? A : W) + x;
+      const double top = -inv * M[j * ld];
+      for (int i0 = j + 1 + g; i0 < k; i0 += 4 * kG) {  // four rows in flight
+        double f[4], v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int i = i0 + u * kG < k ? i0 + u * kG : k - 1;
+          f[u] = A[i * ld + j];
+          v[u] = M[i * ld];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (i0 + u * kG < k) M[(i0 + u * kG) * ld] = fma(f[u], top, v[u]);
+      }
+    }
+    __syncthreads();
+  }
+  if (t == 0) *done = ok;
+  for (int x = t; x < k * k; x += 64 * kG) {
+    const int i = x / k, j = x % k;  // U[i][j] = W[j][i] / sqrt(pivot j) in the scaled columns
+    U[x] = !ok ? (i == j ? 1.0 : 0.0) : i <= j ? s_d[i] * W[j * ld + i] / sqrt(A[j * ld + j]) : 0.0;
+  }
+}
 
 template <bool LDS>
 __global__ __launch_bounds__(1024) void k_jacobi(int k, double* Hg, double* Ug, int sweeps) {
@@ -892,16 +959,26 @@ ens_status ens_pod_eig(const double* G, int32_t m, int32_t k, int32_t r, const d
   double* parts = U + 2 * (size_t)k * k + 64;
   const int sy = product_splits(m, k, m), sh = product_splits(k, k, m);
   ENS_HIP_TRY(hipMemcpyAsync(Y, start, (size_t)m * k * sizeof(double), hipMemcpyDeviceToDevice, stream));
-  // power steps: Y <- G orth(Y), between two buffers
+  // power steps: Y <- G orth(Y); orth(Y) from the factor of Y^T Y where it serves
+  int* const done = (int*)(U + 2 * (size_t)k * k);
   for (int it = 0; it < iters; ++it) {
-    hipLaunchKernelGGL(k_orth, dim3(1), dim3(kOrthThreads), 0, stream, m, k, Y, 1);
+    if (k <= kJacobiLdsK) {
+      dgemm<1>(k, k, m, Y, k, Y, k, H, sh, parts, stream);
+      hipLaunchKernelGGL(k_cholesky_inverse, dim3(1), dim3(1024), 2 * (size_t)k * (k + 1) * sizeof(double), stream, k,
+                         H, U, done);
+      dgemm<0>(m, k, k, Y, k, U, k, Q, 1, nullptr, stream);
+      hipLaunchKernelGGL(k_orth, dim3(1), dim3(kOrthThreads), 0, stream, m, k, Q, 1, done);
+      dgemm<0>(m, k, m, G, m, Q, k, Y, sy, parts, stream);
+      continue;
+    }
+    hipLaunchKernelGGL(k_orth, dim3(1), dim3(kOrthThreads), 0, stream, m, k, Y, 1, (const int*)nullptr);
     dgemm<0>(m, k, m, G, m, Y, k, Q, sy, parts, stream);
     double* const tmp = Y;
     Y = Q;
     Q = tmp;
   }
   // Rayleigh-Ritz on span(Y)
-  hipLaunchKernelGGL(k_orth, dim3(1), dim3(kOrthThreads), 0, stream, m, k, Y, 0);
+  hipLaunchKernelGGL(k_orth, dim3(1), dim3(kOrthThreads), 0, stream, m, k, Y, 0, (const int*)nullptr);
   dgemm<0>(m, k, m, G, m, Y, k, T, sy, parts, stream);   // T = G Q
   dgemm<1>(k, k, m, Y, k, T, k, H, sh, parts, stream);   // H = Q^T G Q
   if (k <= kJacobiLdsK)

@@ -114,11 +114,13 @@ def test_basis_and_projection_products(E, n, m, r):
 # panels of 16 columns whole and ragged, one panel and many, few rows, rows past
 # a workgroup's; spectra that fall slowly, fast enough that the first power
 # step's columns are dependent to 1e-2 of their length or to rounding, and with
-# exact zeros; k on both sides of what the rotations keep in LDS, and odd.
+# exact zeros; k on both sides of what the rotations and the
+# Cholesky factor of all columns keep in LDS, and odd.
 # Columns orthonormal to 64 k roundings; eigenpair residuals and eigenvalues
 # to m k roundings of the largest eigenvalue where the iteration has converged.
 @pytest.mark.parametrize("m,k,r,ratio,rank", [
-    (1, 1, 1, 2.0, 1), (5, 3, 2, 30.0, 5), (96, 48, 16, 2.25, 96), (300, 64, 32, 3.0, 300), (200, 97, 40, 1.3, 200), (200, 96, 40, 1.3, 200),
+    (1, 1, 1, 2.0, 1), (5, 3, 2, 30.0, 5), (96, 48, 16, 2.25, 96), (300, 64, 32, 3.0, 300), (200, 97, 40, 1.3, 200),
+    (200, 96, 40, 1.3, 200), (140, 65, 30, 1.4, 140), (2050, 64, 32, 1.3, 2050),
     (300, 64, 32, 1.5, 20), (700, 33, 20, 1.6, 700), (40, 16, 16, 1e3, 40), (300, 256, 64, 1.2, 300),
     (16, 16, 16, 10.0, 1)])
 def test_eigenpairs(E, m, k, r, ratio, rank):
