@@ -309,7 +309,7 @@ __device__ inline void zero_edges(bool near, int ii, int jj, int kk, int N, doub
   for (int t = T0; t < T1; ++t) {
     double v = acc[t];
     asm("" : "+v"(v));  // a select, not a branch around what v comes from
-    acc[t] = edge(t % 3, ii) | edge((t / 3) % 3, jj) | edge(t / 9, kk) ? 0.0 : v;
+    acc[t] = ((int)edge(t % 3, ii) | (int)edge((t / 3) % 3, jj) | (int)edge(t / 9, kk)) ? 0.0 : v;
   }
 }
 

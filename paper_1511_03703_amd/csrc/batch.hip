@@ -85,18 +85,17 @@ __global__ __launch_bounds__(256) void kb_update(BatchDev bd) {
   if (g.ctl->n_active == 0) return;
   const int64_t nchunks = (int64_t)g.n * S / VecMap<double, S>::V;
   const Ctl* c = g.ctl;
-  update_body<double, S>(nchunks, g.x, g.p, g.q, g.r, g.dinv, [=]() { return c; }, blk - g.vec0,
-                         bd.part + blk * 2 * S);
+  update_body<double, S>(nchunks, g.q, g.r, g.dinv, [=]() { return c; }, blk - g.vec0, bd.part + blk * 2 * S);
 }
 
 template <int S>
 __global__ __launch_bounds__(256) void kb_pupdate(BatchDev bd) {
   const int64_t blk = blockIdx.x;
   const GroupDev& g = bd.groups[bd.vec_grp[blk]];
-  if (g.ctl->n_active == 0) return;
+  if (g.ctl->n_step == 0) return;
   const int64_t nchunks = (int64_t)g.n * S / VecMap<double, S>::V;
   const Ctl* c = g.ctl;
-  pupdate_body<double, S>(nchunks, g.r, g.dinv, g.p, [=]() { return c; }, blk - g.vec0);
+  pupdate_body<double, S>(nchunks, g.x, g.r, g.dinv, g.p, [=]() { return c; }, blk - g.vec0);
 }
 
 template <int S>
@@ -127,7 +126,7 @@ template <int S, int NQ, int VEC>
 __global__ __launch_bounds__(256) void kb_final(BatchDev bd, int op, int arg, int gate) {
   const GroupDev& g = bd.groups[blockIdx.x];
   Ctl* c = g.ctl;
-  if (gate && c->n_active == 0) return;
+  if (gate && gated(c, op)) return;
   sum_rows<NQ * S>(bd.out1 + (VEC ? g.redv0 : g.red0) * NQ * S, VEC ? g.nredv : g.nred, c->tot);
   if (NQ == 1 && threadIdx.x < S) c->tot[S + threadIdx.x] = 0.0;
   __syncthreads();
@@ -182,11 +181,13 @@ static __global__ void kb_ctl_init(BatchDev bd, int ngroups, double rtol, int ma
       c->xnz = 1;
       c->n_active = 0;
       c->n_oactive = 0;
+      c->n_step = 0;
       c->progress0 = c->progress = 0.0;
     }
     if (threadIdx.x < kMaxS) {
       const int e = threadIdx.x;
       c->ratio[e] = 0.0;
+      c->step[e] = 0;
       c->active[e] = 0;
       c->oactive[e] = 0;
       c->iters[e] = 0;

@@ -13,9 +13,9 @@
 // One iteration is three fused streaming kernels plus two small reduction
 // kernels after each of the first two:
 //   A: q = A p and per-block partials of p.q          -> alpha_e
-//   B: x += alpha p, r -= alpha q, z = D^-1 r, partials of r.z and r.r
+//   B: r -= alpha q, z = D^-1 r, partials of r.z and r.r
 //                                                      -> masks, beta_e, rho_e
-//   C: p = z + beta p
+//   C: x += alpha p, p = z + beta p
 // Reductions are deterministic: wave butterflies between lanes holding the
 // same samples, a fixed-order LDS sum per block, then the block partials are
 // summed by a striped first stage and a one-block final stage, each in a
@@ -24,7 +24,7 @@
 // ending (no device-scope fences inside kernels: on this part a fence
 // writes back and invalidates the XCD's L2, which costs more than the
 // launch it saves).  Every kernel of the iteration returns immediately when
-// the active count is zero, and the host reads the count once per chunk of
+// no sample is active (C: when none took a step), and the host reads the count once per chunk of
 // iterations, so the loop ends on the device.
 #include <stddef.h>
 #include <string.h>
@@ -60,7 +60,7 @@ __global__ __launch_bounds__(256) void k_reduce_stage1(const double* __restrict_
 template <int S, int NQ>
 __global__ __launch_bounds__(256) void k_reduce_final(const double* __restrict__ rows, int64_t nrows, Ctl* c,
                                                       int op, int arg, int gate) {
-  if (gate && c->n_active == 0) return;
+  if (gate && gated(c, op)) return;
   sum_rows<NQ * S>(rows, nrows, c->tot);
   if (NQ == 1 && threadIdx.x < S) c->tot[S + threadIdx.x] = 0.0;
   __syncthreads();
@@ -121,20 +121,18 @@ __global__ __launch_bounds__(64 * kProdWaves<KS>) void k_cg_spmv_dot(int n, cons
 }
 
 template <typename T, int S>
-__global__ __launch_bounds__(256) void k_cg_update(int64_t nchunks, T* __restrict__ x, const T* __restrict__ p,
-                                                   const T* __restrict__ q, T* __restrict__ r,
-                                                   const T* __restrict__ dinv, const Ctl* c,
+__global__ __launch_bounds__(256) void k_cg_update(int64_t nchunks, const T* __restrict__ q,
+                                                   T* __restrict__ r, const T* __restrict__ dinv, const Ctl* c,
                                                    double* __restrict__ part) {
   if (c->n_active == 0) return;
-  update_body<T, S>(nchunks, x, p, q, r, dinv, [=]() { return c; }, blockIdx.x,
-                    part + (int64_t)blockIdx.x * 2 * S);
+  update_body<T, S>(nchunks, q, r, dinv, [=]() { return c; }, blockIdx.x, part + (int64_t)blockIdx.x * 2 * S);
 }
 
 template <typename T, int S>
-__global__ __launch_bounds__(256) void k_cg_pupdate(int64_t nchunks, const T* __restrict__ r,
+__global__ __launch_bounds__(256) void k_cg_pupdate(int64_t nchunks, T* __restrict__ x, const T* __restrict__ r,
                                                     const T* __restrict__ dinv, T* __restrict__ p, const Ctl* c) {
-  if (c->n_active == 0) return;
-  pupdate_body<T, S>(nchunks, r, dinv, p, [=]() { return c; }, blockIdx.x);
+  if (c->n_step == 0) return;
+  pupdate_body<T, S>(nchunks, x, r, dinv, p, [=]() { return c; }, blockIdx.x);
 }
 
 // The update and the new direction of a small system, each with the reduction
@@ -165,31 +163,34 @@ __device__ inline const Ctl* fused_state(Ctl& sc, const Ctl* cin, Ctl* cout, con
     __syncthreads();
     finalize<S>(&sc, op, 0);
     __syncthreads();
+  } else {
+    gated(&sc, op);
+    __syncthreads();
   }
   if (blockIdx.x == 0)
     for (int i = threadIdx.x; i < W; i += kBlock) ((uint64_t*)cout)[i] = ((const uint64_t*)&sc)[i];
-  return live && (op == OP_ALPHA || sc.n_active != 0) ? &sc : nullptr;
+  return live && sc.n_step != 0 ? &sc : nullptr;
 }
 
 template <int S>
-__global__ __launch_bounds__(256) void k_cg_update_fused(int64_t nchunks, double* __restrict__ x,
-                                                         const double* __restrict__ p, const double* __restrict__ q,
+__global__ __launch_bounds__(256) void k_cg_update_fused(int64_t nchunks, const double* __restrict__ q,
                                                          double* __restrict__ r, const double* __restrict__ dinv,
                                                          const Ctl* cin, Ctl* cout, const double* __restrict__ rows,
                                                          int nrows, double* __restrict__ part) {
   __shared__ Ctl sc;
-  update_body<double, S>(nchunks, x, p, q, r, dinv,
+  update_body<double, S>(nchunks, q, r, dinv,
                          [&]() { return fused_state<S, 1>(sc, cin, cout, rows, nrows, OP_ALPHA); }, blockIdx.x,
                          part + (int64_t)blockIdx.x * 2 * S);
 }
 
 template <int S>
-__global__ __launch_bounds__(256) void k_cg_pupdate_fused(int64_t nchunks, const double* __restrict__ r,
+__global__ __launch_bounds__(256) void k_cg_pupdate_fused(int64_t nchunks, double* __restrict__ x,
+                                                          const double* __restrict__ r,
                                                           const double* __restrict__ dinv, double* __restrict__ p,
                                                           const Ctl* cin, Ctl* cout, const double* __restrict__ rows,
                                                           int nrows) {
   __shared__ Ctl sc;
-  pupdate_body<double, S>(nchunks, r, dinv, p,
+  pupdate_body<double, S>(nchunks, x, r, dinv, p,
                           [&]() { return fused_state<S, 2>(sc, cin, cout, rows, nrows, OP_UPDATE); }, blockIdx.x);
 }
 
@@ -490,10 +491,11 @@ static void cg_iteration_fused(const ens_graph* g, const double* vals, double* x
   };
   int nr = 0;
   const double* pr = rows(w.rpart, sb, std::integral_constant<int, 1>(), &nr);
-  hipLaunchKernelGGL(k_cg_update_fused<S>, dim3(vb), dim3(kBlock), 0, st, nchunks, x, p, q, r, dinv, w.ctl, w.ctl2, pr,
+  hipLaunchKernelGGL(k_cg_update_fused<S>, dim3(vb), dim3(kBlock), 0, st, nchunks, q, r, dinv, w.ctl, w.ctl2, pr,
                      nr, w.part);
   pr = rows(w.part, vb, std::integral_constant<int, 2>(), &nr);
-  hipLaunchKernelGGL(k_cg_pupdate_fused<S>, dim3(vb), dim3(kBlock), 0, st, nchunks, r, dinv, p, w.ctl2, w.ctl, pr, nr);
+  hipLaunchKernelGGL(k_cg_pupdate_fused<S>, dim3(vb), dim3(kBlock), 0, st, nchunks, x, r, dinv, p, w.ctl2, w.ctl, pr,
+                     nr);
 }
 
 // Launches of one CG iteration (A, reductions, B, reductions, C).
@@ -506,9 +508,9 @@ static void cg_iteration(const ens_graph* g, const T* vals, T* x, T* r, T* p, T*
   const unsigned vb = grid_for(nchunks, (int64_t)kBlock * kU);
   const unsigned sb = product<T, S>(g, vals, p, q, w, st);
   reduce<S, 1>(w, w.rpart, sb, OP_ALPHA, 0, 1, st);
-  hipLaunchKernelGGL((k_cg_update<T, S>), dim3(vb), dim3(kBlock), 0, st, nchunks, x, p, q, r, dinv, w.ctl, w.part);
+  hipLaunchKernelGGL((k_cg_update<T, S>), dim3(vb), dim3(kBlock), 0, st, nchunks, q, r, dinv, w.ctl, w.part);
   reduce<S, 2>(w, w.part, vb, OP_UPDATE, k, 1, st);
-  hipLaunchKernelGGL((k_cg_pupdate<T, S>), dim3(vb), dim3(kBlock), 0, st, nchunks, r, dinv, p, w.ctl);
+  hipLaunchKernelGGL((k_cg_pupdate<T, S>), dim3(vb), dim3(kBlock), 0, st, nchunks, x, r, dinv, p, w.ctl);
 }
 
 // CG loop on already-initialised state; x is the solution (FP64 CG) or
@@ -644,6 +646,7 @@ __global__ void k_ctl_compact(const Ctl* __restrict__ src, Ctl* __restrict__ dst
     dst->xnz = src->xnz;
     dst->n_active = m;
     dst->n_oactive = 0;
+    dst->n_step = 0;
     dst->progress0 = src->progress0;
     dst->progress = src->progress;
   }
@@ -658,6 +661,7 @@ __global__ void k_ctl_compact(const Ctl* __restrict__ src, Ctl* __restrict__ dst
     dst->rel_res[j] = src->rel_res[e];
     dst->orr_prev[j] = src->orr_prev[e];
     dst->ratio[j] = src->ratio[e];
+    dst->step[j] = 0;
     dst->active[j] = live ? src->active[e] : 0;
     dst->oactive[j] = 0;
     dst->iters[j] = src->iters[e];
@@ -853,9 +857,9 @@ static void scalar_iters(const ens_graph* g, const double* vals, double* x, cons
                          p, q, w.ctl, w.part);
     prof_end(ENS_K_SCALAR_SPMV, st, (double)g->nnz * 12.0 + 4.0 * (n + 1) + 16.0 * n);
     reduce<1, 1>(w, w.part, rb, OP_ALPHA, 0, 1, st);
-    hipLaunchKernelGGL((k_cg_update<double, 1>), dim3(vb), dim3(kBlock), 0, st, n, x, p, q, r, dinv, w.ctl, w.part);
+    hipLaunchKernelGGL((k_cg_update<double, 1>), dim3(vb), dim3(kBlock), 0, st, n, q, r, dinv, w.ctl, w.part);
     reduce<1, 2>(w, w.part, vb, OP_UPDATE, k, 1, st);
-    hipLaunchKernelGGL((k_cg_pupdate<double, 1>), dim3(vb), dim3(kBlock), 0, st, n, r, dinv, p, w.ctl);
+    hipLaunchKernelGGL((k_cg_pupdate<double, 1>), dim3(vb), dim3(kBlock), 0, st, n, x, r, dinv, p, w.ctl);
   }
 }
 

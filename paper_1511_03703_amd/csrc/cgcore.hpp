@@ -20,6 +20,7 @@ struct Ctl {
   int32_t active[kMaxS], oactive[kMaxS], iters[kMaxS], oiters[kMaxS], kiter[kMaxS], status[kMaxS];
   int32_t zero_b[kMaxS];
   int32_t compacted[kMaxS];  // the sample finished in the compacted ensemble
+  int32_t step[kMaxS];       // the sample takes a step x += alpha p in this iteration
   // what a poll reads: the largest |r|^2 / tol^2 of the samples that iterate, at
   // the start and now, and their number
   double progress0, progress;
@@ -27,6 +28,7 @@ struct Ctl {
   double rtol, inner_rtol;
   int32_t max_iter, inner_max_iter, max_outer, mixed;
   int32_t coupled;
+  int32_t n_step;  // samples that take a step
   int32_t xnz;  // set when the initial guess has a nonzero entry
   double ratio[kMaxS];  // |r|^2 / tol^2
   double tot[2 * kMaxS];
@@ -101,6 +103,7 @@ __device__ void finalize(Ctl* c, int op, int arg) {
             c->alpha[e] = rho / t0;
           }
         }
+        c->step[e] = c->active[e];
         break;
       }
       case OP_UPDATE: {  // t0 = r.z, t1 = r.r
@@ -216,6 +219,7 @@ __device__ void finalize(Ctl* c, int op, int arg) {
     c->n_active = na;
     c->n_oactive = no;
     c->progress = most;
+    if (op == OP_ALPHA) c->n_step = na;
     if (op == OP_START || op == OP_OUTER) c->progress0 = most;
   }
 }
@@ -257,11 +261,13 @@ static __global__ void k_ctl_init(Ctl* c, double rtol, double inner_rtol, int ma
     c->xnz = 0;
     c->n_active = 0;
     c->n_oactive = 0;
+    c->n_step = 0;
     c->progress0 = c->progress = 0.0;
   }
   if (threadIdx.x < kMaxS) {
     const int e = threadIdx.x;
     c->ratio[e] = 0.0;
+    c->step[e] = 0;
     c->active[e] = 0;
     c->oactive[e] = 0;
     c->iters[e] = 0;
@@ -392,14 +398,21 @@ __device__ inline void spmv_dot_body(int n, const int32_t* __restrict__ rp, cons
   block_partials<S, M::V, 1, NW>(acc, dst);
 }
 
-// B: x += alpha p; r -= alpha q; z = D^-1 r for chunk block `blk`; partials
-// r.z, r.r to dst[2][S].  Samples that are not active stay frozen.  state()
-// gives the control block (null: nothing is to be done), called by every lane
-// while the vectors are on their way.
+// A gated reduction of a control block without active samples: nothing is
+// summed; the steps of the iteration that stopped them are over.
+__device__ inline bool gated(Ctl* c, int op) {
+  if (c->n_active != 0) return false;
+  if (op == OP_ALPHA && threadIdx.x == 0) c->n_step = 0;
+  return true;
+}
+
+// B: r -= alpha q; z = D^-1 r for chunk block `blk`; partials r.z, r.r to
+// dst[2][S].  Samples that are not active stay frozen.  state() gives the
+// control block (null: nothing is to be done), called by every lane while the
+// vectors are on their way.
 template <typename T, int S, typename State>
-__device__ inline void update_body(int64_t nchunks, T* __restrict__ x, const T* __restrict__ p,
-                                   const T* __restrict__ q, T* __restrict__ r, const T* __restrict__ dinv,
-                                   State state, int64_t blk, double* __restrict__ dst) {
+__device__ inline void update_body(int64_t nchunks, const T* __restrict__ q, T* __restrict__ r,
+                                   const T* __restrict__ dinv, State state, int64_t blk, double* __restrict__ dst) {
   using M = VecMap<T, S>;
   using vt = typename M::vt;
   const int sub = (threadIdx.x & 63) % M::L;
@@ -407,15 +420,13 @@ __device__ inline void update_body(int64_t nchunks, T* __restrict__ x, const T* 
 #pragma unroll
   for (int j = 0; j < M::VS; ++j) acc[0][j] = acc[1][j] = 0.0;
   const int64_t base = blk * kBlock * kU + threadIdx.x;
-  vt pv[kU], qv[kU], rv[kU], xv[kU], dv[kU];
+  vt qv[kU], rv[kU], dv[kU];
 #pragma unroll
   for (int u = 0; u < kU; ++u) {
     const int64_t i = base + u * kBlock;
     if (i < nchunks) {
-      pv[u] = load_stream((const vt*)p + i);
       qv[u] = load_stream((const vt*)q + i);
       rv[u] = load_stream((const vt*)r + i);
-      xv[u] = load_stream((const vt*)x + i);
       dv[u] = load_stream((const vt*)dinv + i);
     }
   }
@@ -433,15 +444,10 @@ __device__ inline void update_body(int64_t nchunks, T* __restrict__ x, const T* 
   for (int u = 0; u < kU; ++u) {
     const int64_t i = base + u * kBlock;
     if (i < nchunks) {
-      vt xn = xv[u] + al * pv[u];
       vt rn = rv[u] - al * qv[u];
 #pragma unroll
       for (int v = 0; v < M::V; ++v)  // converged or stopped samples stay frozen
-        if (!act[v]) {
-          xn[v] = xv[u][v];
-          rn[v] = rv[u][v];
-        }
-      xv[u] = xn;
+        if (!act[v]) rn[v] = rv[u][v];
       rv[u] = rn;
       vt z = dv[u] * rn;
 #pragma unroll
@@ -455,24 +461,25 @@ __device__ inline void update_body(int64_t nchunks, T* __restrict__ x, const T* 
 #pragma unroll
   for (int u = 0; u < kU; ++u) {
     const int64_t i = base + u * kBlock;
-    if (i < nchunks) {
-      store_stream((vt*)x + i, xv[u]);
-      store_stream((vt*)r + i, rv[u]);
-    }
+    if (i < nchunks) store_stream((vt*)r + i, rv[u]);
   }
   block_partials<S, M::VS, 2, kBlock / 64>(acc, dst);
 }
 
-// C: p = D^-1 r + beta p for the samples still active, chunk block `blk`;
-// state() as in update_body.
+// C: x += alpha p for the samples that take a step, with p before
+// p = D^-1 r + beta p for those still active, chunk block `blk`; state() as in
+// update_body.  Here, and not beside r -= alpha q, because p is read here
+// anyway: 10 passes over vectors an iteration instead of 11 (a batch of 8 groups,
+// meshes 32 to 96, s = 16: 283 -> 277 ms; beside a multigrid cycle, 8 instead of
+// 9, it measured no gain at 64^3, s = 16 and 128^3, s = 32, and x moves with r).
 template <typename T, int S, typename State>
-__device__ inline void pupdate_body(int64_t nchunks, const T* __restrict__ r, const T* __restrict__ dinv,
-                                    T* __restrict__ p, State state, int64_t blk) {
+__device__ inline void pupdate_body(int64_t nchunks, T* __restrict__ x, const T* __restrict__ r,
+                                    const T* __restrict__ dinv, T* __restrict__ p, State state, int64_t blk) {
   using M = VecMap<T, S>;
   using vt = typename M::vt;
   const int sub = (threadIdx.x & 63) % M::L;
   const int64_t base = blk * kBlock * kU + threadIdx.x;
-  vt pv[kU], rv[kU], dv[kU];
+  vt pv[kU], rv[kU], dv[kU], xv[kU];
 #pragma unroll
   for (int u = 0; u < kU; ++u) {
     const int64_t i = base + u * kBlock;
@@ -480,30 +487,37 @@ __device__ inline void pupdate_body(int64_t nchunks, const T* __restrict__ r, co
       pv[u] = load_stream((const vt*)p + i);
       rv[u] = load_stream((const vt*)r + i);
       dv[u] = load_stream((const vt*)dinv + i);
+      xv[u] = load_stream((const vt*)x + i);
     }
   }
   const Ctl* c = state();
   if (!c) return;
-  vt be;
-  int act[M::V];
-  bool any = false;
+  vt al, be;
+  int act[M::V], stp[M::V];
+  bool any_act = false, any_step = false;
 #pragma unroll
   for (int v = 0; v < M::V; ++v) {
     const int e = M::sample(sub, v);
     act[v] = c->active[e];
+    stp[v] = c->step[e];
+    al[v] = stp[v] ? (T)c->alpha[e] : (T)0;
     be[v] = act[v] ? (T)c->beta[e] : (T)0;
-    any |= act[v] != 0;
+    any_act |= act[v] != 0;
+    any_step |= stp[v] != 0;
   }
-  if (!any) return;
+  if (!any_step) return;  // (an active sample has taken a step)
 #pragma unroll
   for (int u = 0; u < kU; ++u) {
     const int64_t i = base + u * kBlock;
     if (i < nchunks) {
-      vt pn = dv[u] * rv[u] + be * pv[u];
+      vt xn = xv[u] + al * pv[u], pn = dv[u] * rv[u] + be * pv[u];
 #pragma unroll
-      for (int v = 0; v < M::V; ++v)  // inactive samples keep their p
+      for (int v = 0; v < M::V; ++v) {  // the others keep theirs
+        if (!stp[v]) xn[v] = xv[u][v];
         if (!act[v]) pn[v] = pv[u][v];
-      store_stream((vt*)p + i, pn);
+      }
+      store_stream((vt*)x + i, xn);
+      if (any_act) store_stream((vt*)p + i, pn);
     }
   }
 }
