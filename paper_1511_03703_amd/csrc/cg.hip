@@ -117,7 +117,7 @@ __global__ __launch_bounds__(64 * kProdWaves<KS>) void k_cg_spmv_dot(int n, cons
                                                      const T* __restrict__ p, T* __restrict__ q, const Ctl* c,
                                                      double* __restrict__ part) {
   if (c->n_active == 0) return;
-  spmv_dot_body<T, S, KS, kProdWaves<KS>>(n, rp, ci, vals, p, q, blockIdx.x, part + (int64_t)blockIdx.x * S);
+  spmv_dot_body<T, S, KS, kProdWaves<KS>>(n, rp, ci, vals, p, q, row_tile<T, S>(n), part + (int64_t)blockIdx.x * S);
 }
 
 template <typename T, int S>

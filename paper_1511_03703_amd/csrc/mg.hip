@@ -359,7 +359,7 @@ __global__ __launch_bounds__(256) void k_mg_row(int n, const int32_t* __restrict
   const RowPlace<T, S, KS, 4> at;
   constexpr int R = at.R;
   __shared__ RowTileLds<R> tile;
-  const int64_t r0 = (int64_t)blockIdx.x * R, row = r0 + at.lr;
+  const int64_t r0 = row_tile<T, S>(n) * R, row = r0 + at.lr;
   const bool staged = stage_row_tile(tile, n, rp, ci, r0);
   double acc[1][M::V];
 #pragma unroll

@@ -291,7 +291,7 @@ static __global__ __launch_bounds__(kBlock) void k_gm_spmv(int n, const int32_t*
   const RowPlace<double, S, KS, kBlock / 64> at;
   constexpr int R = at.R;
   __shared__ RowTileLds<R> tile;  // the row tile's offsets and indices, as in the CG product
-  const int64_t r0 = (int64_t)blockIdx.x * R, row = r0 + at.lr;
+  const int64_t r0 = row_tile<TZ, S>(n) * R, row = r0 + at.lr;
   const bool staged = stage_row_tile(tile, n, rp, ci, r0);
   if (row >= n) return;
   const typename M::vt y = tile_row_product<double>(at, tile, staged, ci, vals, z);
@@ -310,7 +310,7 @@ static __global__ __launch_bounds__(kBlock) void k_gm_spmv_v32(int n, const int3
   const RowPlace<float, S, KS, kBlock / 64> at;  // V = 4 samples per lane
   constexpr int R = at.R;
   __shared__ RowTileLds<R> tile;  // the row tile's offsets and indices, as in the CG product
-  const int64_t r0 = (int64_t)blockIdx.x * R, row = r0 + at.lr;
+  const int64_t r0 = row_tile<TZ, S>(n) * R, row = r0 + at.lr;
   const bool staged = stage_row_tile(tile, n, rp, ci, r0);
   if (row >= n) return;
   const d4 acc = tile_row_product<double>(at, tile, staged, ci, vals, z);

@@ -169,6 +169,21 @@ __device__ inline typename vec_t<TA, V>::type row_sum(const int32_t* ci, const T
   return acc;
 }
 
+// Row tile of a workgroup.  Workgroups are dealt to the 8 XCDs in turn; runs of
+// 16 consecutive tiles go to one XCD where the gathered vector is 16 MB or less
+// (n rows of S samples in T), so that neighbouring rows read it through one L2
+// (product, us: 27^3, FP64 s = 8 9.2 -> 8.9, 32^3, FP32 s = 16 14.3 -> 13.6, 48^3,
+// FP64 s = 16 73.3 -> 70.8).  A larger vector does not stay in the L2s, and the
+// matrix then streams best in launch order (96^3, FP32 s = 32 544 -> 553 in runs,
+// 128^3 1342 -> 1364).
+template <typename T, int S>
+__device__ inline int64_t row_tile(int n) {
+  constexpr uint32_t C = 16;
+  const uint32_t b = blockIdx.x, run = b / (8 * C), in = b % (8 * C);
+  if ((int64_t)n * (S * (int)sizeof(T)) > ((int64_t)16 << 20) || (run + 1) * (8 * C) > gridDim.x) return b;
+  return run * (8 * C) + (in % 8) * C + in / 8;
+}
+
 // A lane's place in a row tile of NW wavefronts: its samples sub*V .., lane
 // group g (the one with g = 0 does the row's vector work) and row.
 template <typename T, int S, int KS, int NW>

@@ -49,9 +49,13 @@ def test_products_of_ragged_rows(E, s, dt):
         _check(E, _graph(E, lengths, n, s + n), s, dt, s)
 
 
-# 256 MB of values lie between these meshes for s = 32 in FP64 and FP32
+# 256 MB of values lie between the first pairs of meshes for s = 32 in FP64 and
+# FP32; 16 MB of gathered vector, up to which tiles go to an XCD in runs (of which
+# the last is ragged), between the last two pairs
 @pytest.mark.parametrize("N,s,dt", [(33, 32, torch.float64), (34, 32, torch.float64), (42, 32, torch.float32),
-                                    (43, 32, torch.float32), (5, 4, torch.float32), (42, 16, torch.float64)])
+                                    (43, 32, torch.float32), (5, 4, torch.float32), (42, 16, torch.float64),
+                                    (39, 32, torch.float64), (40, 32, torch.float64), (49, 32, torch.float32),
+                                    (50, 32, torch.float32)])
 def test_products_on_either_side_of_the_cache_size(E, N, s, dt):
     _check(E, E.graph_build(N), s, dt, N)
 
