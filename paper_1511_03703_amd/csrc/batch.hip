@@ -186,7 +186,7 @@ static __global__ void kb_ctl_init(BatchDev bd, int ngroups, double rtol, int ma
     }
     if (threadIdx.x < kMaxS) {
       const int e = threadIdx.x;
-      c->ratio[e] = 0.0;
+      c->ratio[e] = 0.0f;
       c->step[e] = 0;
       c->active[e] = 0;
       c->oactive[e] = 0;

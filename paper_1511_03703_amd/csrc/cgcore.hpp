@@ -18,9 +18,11 @@ struct Ctl {
   double rho[kMaxS], alpha[kMaxS], beta[kMaxS], tol2[kMaxS], bnorm2[kMaxS];
   double rel_res[kMaxS], orr_prev[kMaxS];
   int32_t active[kMaxS], oactive[kMaxS], iters[kMaxS], oiters[kMaxS], kiter[kMaxS], status[kMaxS];
-  int32_t zero_b[kMaxS];
-  int32_t compacted[kMaxS];  // the sample finished in the compacted ensemble
-  int32_t step[kMaxS];       // the sample takes a step x += alpha p in this iteration
+  // (flags in bytes and ratios in FP32: the block, and with it every workspace,
+  // keeps its size)
+  uint8_t zero_b[kMaxS];
+  uint8_t compacted[kMaxS];  // the sample finished in the compacted ensemble
+  uint8_t step[kMaxS];       // the sample takes a step x += alpha p in this iteration
   // what a poll reads: the largest |r|^2 / tol^2 of the samples that iterate, at
   // the start and now, and their number
   double progress0, progress;
@@ -30,9 +32,11 @@ struct Ctl {
   int32_t coupled;
   int32_t n_step;  // samples that take a step
   int32_t xnz;  // set when the initial guess has a nonzero entry
-  double ratio[kMaxS];  // |r|^2 / tol^2
+  float ratio[kMaxS];  // |r|^2 / tol^2
+  double spare;
   double tot[2 * kMaxS];
 };
+static_assert(sizeof(Ctl) == 3376, "workspaces keep their sizes");
 
 // ------------------------------------------------------------- finalize ---
 
@@ -72,7 +76,7 @@ __device__ void finalize(Ctl* c, int op, int arg) {
           c->status[e] = ENS_SAMPLE_MAXITER;
           c->active[e] = 1;
         }
-        c->ratio[e] = t0 / c->tol2[e];
+        c->ratio[e] = (float)(t0 / c->tol2[e]);
         break;
       }
       case OP_RHO: {  // t0 = r.z
@@ -111,7 +115,7 @@ __device__ void finalize(Ctl* c, int op, int arg) {
           c->iters[e] += 1;
           c->kiter[e] += 1;
           const int cap = c->mixed ? c->inner_max_iter : c->max_iter;
-          c->ratio[e] = t1 / c->tol2[e];
+          c->ratio[e] = (float)(t1 / c->tol2[e]);
           if (!isfinite(t0) || !isfinite(t1)) {
             c->status[e] = ENS_SAMPLE_NONFINITE;
             c->active[e] = 0;
@@ -134,7 +138,7 @@ __device__ void finalize(Ctl* c, int op, int arg) {
           c->iters[e] += 1;
           c->kiter[e] += 1;
           const int cap = c->mixed ? c->inner_max_iter : c->max_iter;
-          c->ratio[e] = t1 / c->tol2[e];
+          c->ratio[e] = (float)(t1 / c->tol2[e]);
           if (!isfinite(t1)) {
             c->status[e] = ENS_SAMPLE_NONFINITE;
             c->active[e] = 0;
@@ -197,7 +201,7 @@ __device__ void finalize(Ctl* c, int op, int arg) {
             const double it = c->inner_rtol * c->inner_rtol * t0;
             const double fl = 0.09 * rt * rt * t1;
             c->tol2[e] = it > fl ? it : fl;
-            c->ratio[e] = t0 / c->tol2[e];
+            c->ratio[e] = (float)(t0 / c->tol2[e]);
             c->active[e] = 1;
             c->oiters[e] += 1;
           }
@@ -266,7 +270,7 @@ static __global__ void k_ctl_init(Ctl* c, double rtol, double inner_rtol, int ma
   }
   if (threadIdx.x < kMaxS) {
     const int e = threadIdx.x;
-    c->ratio[e] = 0.0;
+    c->ratio[e] = 0.0f;
     c->step[e] = 0;
     c->active[e] = 0;
     c->oactive[e] = 0;
