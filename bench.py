@@ -575,8 +575,10 @@ def run_solve(args):
 
 def cg_iteration_bytes(n, nnz, s, w):
     """Algorithmic bytes of one Jacobi-CG iteration of an ensemble: the
-    product q = A p (with p.q), the update pass (reads x, p, q, r, D^-1,
-    writes x, r) and the direction pass (reads r, D^-1, p, writes p)."""
+    product q = A p (with p.q), the update pass (x, p, q, r, D^-1 read, x, r
+    written) and the direction pass (r, D^-1, p read, p written).  The model of
+    the published batch figures; the kernels step x in the direction pass, where p
+    is read anyway, and move one vector less (2.5 % of the bytes)."""
     return spmv_bytes(n, nnz, s, w) + 11.0 * n * s * w
 
 
