@@ -988,7 +988,9 @@ static void mg_iterations(const ens_graph* g, const T* vals, const MgPlan& plan,
                           const Work& w, int k0, int k1, hipStream_t st) {
   const int64_t n = g->n;
   const int64_t nchunks = n * S / VecMap<T, S>::V;
-  const unsigned db = grid_for(n, mg_dot_rows<T, S>(g->nnz));  // row tiles of the cycle's last pass
+  // row tiles of the cycle's last pass, by the entries the hierarchy counts (the
+  // caller's graph may store fewer)
+  const unsigned db = grid_for(n, mg_dot_rows<T, S>(plan.lv[0].nnz));
   const unsigned vb = grid_for(nchunks, (int64_t)kBlock * kU);
   for (int k = k0 + 1; k <= k1; ++k) {
     const unsigned sb = product<T, S>(g, vals, p, q, w, st);

@@ -88,8 +88,8 @@ void mg_attach_fine(MgPlan* plan, const int32_t* rp, const int32_t* ci, const do
 // z = M r for all samples in the cycle precision T; every kernel returns at
 // once when the control block (nullable) reports no active sample.  With
 // dot (nullable), the last fine-level pass also writes the per-sample
-// partials of r . z, one row of S doubles per mg_dot_rows<T, S>(nnz of the
-// fine matrix) rows.
+// partials of r . z, one row of S doubles per mg_dot_rows<T, S>(plan.lv[0].nnz)
+// rows.
 template <typename T, int S>
 inline int mg_dot_rows(int64_t nnz) {
   return cached_matrix<T, S>(nnz) ? RowPlace<T, S, row_groups<T, S, true, true>(), 4>::R
