@@ -91,7 +91,7 @@ const char* ens_last_error(void);
 const char* ens_status_string(ens_status st);
 int32_t ens_abi_version(void);
 /* Release the library's own per-device state: each device context (its
- * pinned poll word, work stream, join events and the concurrent baseline's
+ * pinned poll words, work stream, join events and the concurrent baseline's
  * side streams, whose queued work is waited for first) and the pool of
  * profiling events (pending timings are completed and kept; profiling is
  * switched off).  Caller-owned buffers are untouched, and the state is

@@ -33,7 +33,8 @@ DeviceCtx* device_ctx() {
   if (!g_ctx[dev]) {
     DeviceCtx* c = new DeviceCtx();
     c->device = dev;
-    if (hipHostMalloc((void**)&c->host_flag, 64 * sizeof(int32_t), hipHostMallocDefault) != hipSuccess ||
+    if (hipHostMalloc((void**)&c->poll_words, (size_t)PollSlots::kSlots * PollSlots::kBytes, hipHostMallocDefault) !=
+            hipSuccess ||
         hipStreamCreateWithFlags(&c->work_stream, hipStreamNonBlocking) != hipSuccess ||
         hipEventCreateWithFlags(&c->ev_in, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&c->ev_out, hipEventDisableTiming) != hipSuccess) {
@@ -81,7 +82,7 @@ static hipError_t release_contexts() {
     keep(hipEventDestroy(c->ev_in));
     keep(hipEventDestroy(c->ev_out));
     keep(hipStreamDestroy(c->work_stream));
-    keep(hipHostFree(c->host_flag));
+    keep(hipHostFree(c->poll_words));
     delete c;
     c = nullptr;
   }

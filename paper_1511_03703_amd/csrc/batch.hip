@@ -319,9 +319,10 @@ static ens_status poll(int32_t* dev_count, hipStream_t st, int32_t* out) {
     set_error("device context unavailable");
     return ENS_E_HIP;
   }
-  ENS_HIP_TRY(hipMemcpyAsync(cx->host_flag, dev_count, sizeof(int32_t), hipMemcpyDeviceToHost, st));
+  PollBuffer host(cx);
+  ENS_HIP_TRY(hipMemcpyAsync(host.words(), dev_count, sizeof(int32_t), hipMemcpyDeviceToHost, st));
   ENS_HIP_TRY(hipStreamSynchronize(st));
-  *out = *cx->host_flag;
+  *out = *(const int32_t*)host.words();
   return ENS_OK;
 }
 

@@ -419,19 +419,19 @@ static_assert(offsetof(Ctl, progress) == offsetof(Ctl, progress0) + 8 &&
               "polled words lie side by side");
 
 static ens_status poll(const Work& w, hipStream_t st, PollWords* out) {
-  void* to = out;
+  DeviceCtx* cx = nullptr;
   if (!w.pageable_poll) {
-    DeviceCtx* cx = device_ctx();
+    cx = device_ctx();
     if (!cx) {
       set_error("device context unavailable");
       return ENS_E_HIP;
     }
-    to = cx->host_flag;
   }
-  ENS_HIP_TRY(hipMemcpyAsync(to, &w.ctl->progress0, sizeof(PollWords), hipMemcpyDeviceToHost, st));
+  PollBuffer host(cx);
+  ENS_HIP_TRY(hipMemcpyAsync(host.words(), &w.ctl->progress0, sizeof(PollWords), hipMemcpyDeviceToHost, st));
   ENS_HIP_TRY(hipStreamSynchronize(st));
   prof_collect();
-  if (to != out) memcpy(out, to, sizeof(PollWords));
+  memcpy(out, host.words(), sizeof(PollWords));
   return ENS_OK;
 }
 
@@ -908,6 +908,9 @@ static ens_status cg_scalar_concurrent(const ens_graph* g, int s, const double* 
   ENS_HIP_TRY(hipEventRecord(cx->ev_in, user));
   for (int i = 0; i < ns; ++i) ENS_HIP_TRY(hipStreamWaitEvent(cx->side[i], cx->ev_in, 0));
   ens_status agg = ENS_OK;
+  PollBuffer host(cx);
+  int32_t* const left = (int32_t*)host.words();
+  static_assert(kMaxSideStreams * sizeof(int32_t) <= PollSlots::kBytes, "a word per side stream");
   for (int e0 = 0; e0 < s; e0 += ns) {
     const int m = s - e0 < ns ? s - e0 : ns;
     std::vector<int> active;
@@ -922,7 +925,7 @@ static ens_status cg_scalar_concurrent(const ens_graph* g, int s, const double* 
       for (int i : active) {
         const int e = e0 + i;
         scalar_iters<G>(g, values + (int64_t)e * nnz, x + (int64_t)e * n, w[i], k0, k1, cx->side[i]);
-        ENS_HIP_TRY(hipMemcpyAsync(cx->host_flag + i, &w[i].ctl->n_active, sizeof(int32_t), hipMemcpyDeviceToHost,
+        ENS_HIP_TRY(hipMemcpyAsync(left + i, &w[i].ctl->n_active, sizeof(int32_t), hipMemcpyDeviceToHost,
                                    cx->side[i]));
       }
       ENS_LAUNCH_CHECK();
@@ -930,7 +933,7 @@ static ens_status cg_scalar_concurrent(const ens_graph* g, int s, const double* 
       prof_collect();
       std::vector<int> still;
       for (int i : active)
-        if (cx->host_flag[i] != 0) still.push_back(i);
+        if (left[i] != 0) still.push_back(i);
       active.swap(still);
     }
     for (int i = 0; i < m; ++i) {

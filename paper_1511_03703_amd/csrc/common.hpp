@@ -14,6 +14,7 @@
 #include <stddef.h>
 
 #include "../../include/ens.h"
+#include "pollslots.hpp"
 
 namespace ens {
 
@@ -86,7 +87,8 @@ constexpr int kMaxSideStreams = 32;
 
 struct DeviceCtx {
   int device = -1;
-  int32_t* host_flag = nullptr;         // pinned [64], for the once-per-chunk polls
+  char* poll_words = nullptr;           // pinned [kSlots][kBytes], for the once-per-chunk polls
+  PollSlots poll_slots;
   hipStream_t work_stream = nullptr;    // non-default stream for graph capture
   hipEvent_t ev_in = nullptr, ev_out = nullptr;  // joins with the caller's stream
   // streams of the concurrent one-sample baseline (default priority),
@@ -95,6 +97,24 @@ struct DeviceCtx {
   std::vector<hipEvent_t> side_ev;
 };
 DeviceCtx* device_ctx();
+
+// Host words of one call's polls: a pinned slot of the device's context, or
+// words of its own without a context or when every slot is taken.
+class PollBuffer {
+ public:
+  explicit PollBuffer(DeviceCtx* c) : ctx_(c), slot_(c ? c->poll_slots.take() : -1) {}
+  ~PollBuffer() {
+    if (slot_ >= 0) ctx_->poll_slots.give(slot_);
+  }
+  PollBuffer(const PollBuffer&) = delete;
+  PollBuffer& operator=(const PollBuffer&) = delete;
+  void* words() { return slot_ >= 0 ? ctx_->poll_words + slot_ * PollSlots::kBytes : own_; }
+
+ private:
+  DeviceCtx* ctx_;
+  int slot_;
+  alignas(16) char own_[PollSlots::kBytes];
+};
 // Make sure the context holds at least `count` side streams.
 bool ensure_side_streams(DeviceCtx* c, int count);
 

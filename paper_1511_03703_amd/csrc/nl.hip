@@ -682,10 +682,11 @@ static ens_status read_flag(const int32_t* dev, hipStream_t st, int32_t* out) {
     set_error("device context unavailable");
     return ENS_E_HIP;
   }
-  ENS_HIP_TRY(hipMemcpyAsync(cx->host_flag, dev, sizeof(int32_t), hipMemcpyDeviceToHost, st));
+  PollBuffer host(cx);
+  ENS_HIP_TRY(hipMemcpyAsync(host.words(), dev, sizeof(int32_t), hipMemcpyDeviceToHost, st));
   ENS_HIP_TRY(hipStreamSynchronize(st));
   prof_collect();
-  *out = *cx->host_flag;
+  *out = *(const int32_t*)host.words();
   return ENS_OK;
 }
 
