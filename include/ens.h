@@ -687,14 +687,20 @@ ens_status ens_mlp_adam(float* params, const float* grad, float* adam_m, float* 
  * solution per column.
  * ens_pod_collect: S[i][col0 + e] = x[i][e] for an ensemble x [n][s].
  * ens_pod_gram:    G [m][m] = S^T S (split-K workspace of
- *                  ens_pod_gram_workspace_bytes).
+ *                  ens_pod_gram_workspace_bytes; with fewer bytes, from
+ *                  min(n / 4096, 32) times 8 m^2 up, the sum takes fewer
+ *                  ranges, and below n = 8192 the workspace may be NULL).
  * ens_pod_eig:     top-r eigenpairs of G by `iters` steps of block subspace
  *                  iteration on k >= r columns from the seeded start block
  *                  start [m][k], then Rayleigh-Ritz (Jacobi on k x k);
- *                  V [m][r] orthonormal, lambda [r] descending (device).
+ *                  V [m][r] orthonormal, lambda [r] descending (device);
+ *                  workspace of ens_pod_eig_workspace_bytes, or, with
+ *                  unsplit products, from 8 (3 m k + 3 k^2 + 64) bytes up.
  * ens_pod_basis:   Phi [n][r] = S V diag(lambda)^(-1/2), each column's
  *                  largest-magnitude entry made positive.
- * ens_pod_project: C [s][r] = X^T Phi for an ensemble X [n][s].
+ * ens_pod_project: C [s][r] = X^T Phi for an ensemble X [n][s] (workspace of
+ *                  ens_pod_project_workspace_bytes, or less as for
+ *                  ens_pod_gram with r s in place of m^2).
  * ens_pod_standardize: per-coefficient mean mu [r] over the m rows of
  *                  C [m][r] (r <= 1024), a scale sd [r] and the network
  *                  targets T [m][r] = (C - mu) / sd in FP32; common = 0:

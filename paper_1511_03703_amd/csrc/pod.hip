@@ -860,6 +860,23 @@ static int gram_splits(int64_t n, int64_t m) {
   return best;
 }
 
+// Ranges that a product over n rows takes with the workspace it is given, `slice`
+// bytes a range: `want` where it holds them, fewer where it does not.  Refused
+// is a workspace of fewer than n / 4096 ranges (32 at most, `want` at most); none
+// is needed where that is one.
+static ens_status ranges_held(int want, int64_t n, size_t slice, const void* ws, size_t ws_bytes, int* ranges) {
+  int64_t least = n / 4096 < 32 ? n / 4096 : 32;
+  if (least > want) least = want;
+  ENS_ARG_CHECK(least <= 1 || ws, "null workspace");
+  const int64_t held = ws ? (int64_t)(ws_bytes / slice) : 0;
+  if (least > 1 && held < least) {
+    set_error("workspace of %zu bytes is smaller than the %zu required", ws_bytes, (size_t)least * slice);
+    return ENS_E_NOMEM;
+  }
+  *ranges = held < 1 ? 1 : held < want ? (int)held : want;
+  return ENS_OK;
+}
+
 // C [M][N] (dense) = op(A) B in `splits` K ranges; scratch [splits][M][N] for
 // more than one.
 template <int TA>
@@ -885,7 +902,9 @@ static void dgemm(int64_t M, int64_t N, int64_t K, const double* A, int64_t lda,
                        M * N, C);
 }
 
-// Doubles of split-K scratch of the eigensolver's products.
+// Doubles of workspace the eigensolver cannot do without, and those of its
+// products' split-K scratch.
+static size_t eig_least(int64_t m, int64_t k) { return 3 * (size_t)m * k + 3 * (size_t)k * k + 64; }
 static size_t eig_scratch(int64_t m, int64_t k) {
   const size_t a = (size_t)product_splits(m, k, m) * m * k, b = (size_t)product_splits(k, k, m) * k * k;
   return a > b ? a : b;
@@ -915,12 +934,9 @@ ens_status ens_pod_gram_workspace_bytes(int64_t n, int32_t m, size_t* bytes) {
 ens_status ens_pod_gram(const double* S, int64_t n, int32_t m, double* G, void* workspace, size_t ws_bytes,
                         hipStream_t stream) {
   ENS_ARG_CHECK(S && G && n >= 1 && m >= 1, "bad Gram arguments");
-  const int sp = gram_splits(n, m);
-  ENS_ARG_CHECK(sp == 1 || workspace, "null workspace");
-  if (sp > 1 && ws_bytes < (size_t)sp * m * m * sizeof(double)) {
-    set_error("Gram workspace too small");
-    return ENS_E_NOMEM;
-  }
+  int sp = 1;
+  const ens_status rc = ranges_held(gram_splits(n, m), n, (size_t)m * m * sizeof(double), workspace, ws_bytes, &sp);
+  if (rc != ENS_OK) return rc;
   // G = S^T S: op(A) = S^T, K = n; the blocks on and above the diagonal
   const int64_t tm = tiles128(m), m64 = m;
   const int64_t kchunk = ((n + sp - 1) / sp + 31) / 32 * 32;
@@ -937,7 +953,7 @@ ens_status ens_pod_gram(const double* S, int64_t n, int32_t m, double* G, void* 
 
 ens_status ens_pod_eig_workspace_bytes(int32_t m, int32_t k, size_t* bytes) {
   ENS_ARG_CHECK(bytes && m >= 1 && k >= 1, "bad sizes");
-  *bytes = (size_t)(3 * (size_t)m * k + 3 * (size_t)k * k + 64 + eig_scratch(m, k)) * sizeof(double);
+  *bytes = (eig_least(m, k) + eig_scratch(m, k)) * sizeof(double);
   return ENS_OK;
 }
 
@@ -945,9 +961,8 @@ ens_status ens_pod_eig(const double* G, int32_t m, int32_t k, int32_t r, const d
                        double* V, double* lambda, void* workspace, size_t ws_bytes, hipStream_t stream) {
   ENS_ARG_CHECK(G && start && V && lambda && workspace, "null pointer");
   ENS_ARG_CHECK(m >= 1 && k >= 1 && k <= 256 && k <= m && r >= 1 && r <= k && iters >= 0, "bad sizes");
-  size_t need = 0;
-  ens_pod_eig_workspace_bytes(m, k, &need);
-  if (ws_bytes < need) {
+  const size_t least = eig_least(m, k);
+  if (ws_bytes < least * sizeof(double)) {
     set_error("eigen workspace too small");
     return ENS_E_NOMEM;
   }
@@ -957,7 +972,12 @@ ens_status ens_pod_eig(const double* G, int32_t m, int32_t k, int32_t r, const d
   double* H = T + (size_t)m * k;
   double* U = H + (size_t)k * k;
   double* parts = U + 2 * (size_t)k * k + 64;
-  const int sy = product_splits(m, k, m), sh = product_splits(k, k, m);
+  // K ranges as far as the workspace holds their products
+  const size_t room = ws_bytes / sizeof(double) - least;
+  auto held = [&](int want, size_t product) {
+    return room < product ? 1 : room / product < (size_t)want ? (int)(room / product) : want;
+  };
+  const int sy = held(product_splits(m, k, m), (size_t)m * k), sh = held(product_splits(k, k, m), (size_t)k * k);
   ENS_HIP_TRY(hipMemcpyAsync(Y, start, (size_t)m * k * sizeof(double), hipMemcpyDeviceToDevice, stream));
   // power steps: Y <- G orth(Y); orth(Y) from the factor of Y^T Y where it serves
   int* const done = (int*)(U + 2 * (size_t)k * k);
@@ -1008,12 +1028,9 @@ ens_status ens_pod_project_workspace_bytes(int64_t n, int32_t r, int32_t s, size
 ens_status ens_pod_project(const double* Phi, const double* X, int64_t n, int32_t r, int32_t s, double* C,
                            void* workspace, size_t ws_bytes, hipStream_t stream) {
   ENS_ARG_CHECK(Phi && X && C && n >= 1 && r >= 1 && s >= 1, "bad projection arguments");
-  const int sp = product_splits(s, r, n);
-  ENS_ARG_CHECK(sp == 1 || workspace, "null workspace");
-  if (sp > 1 && ws_bytes < (size_t)sp * r * s * sizeof(double)) {
-    set_error("projection workspace too small");
-    return ENS_E_NOMEM;
-  }
+  int sp = 1;
+  const ens_status rc = ranges_held(product_splits(s, r, n), n, (size_t)r * s * sizeof(double), workspace, ws_bytes, &sp);
+  if (rc != ENS_OK) return rc;
   // C[e][j] = sum_i X[i][e] Phi[i][j]: op(A) = X^T
   dgemm<1>(s, r, n, X, s, Phi, r, C, sp, (double*)workspace, stream);
   ENS_LAUNCH_CHECK();

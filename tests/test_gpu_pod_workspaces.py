@@ -1,0 +1,89 @@
+"""The POD products with every workspace they take: none, the least, and what
+their bytes functions ask for; and what they refuse.  A sum of n products in
+any order differs from FP64's by at most (n + 2) roundings of the sum of their
+magnitudes."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+@pytest.fixture(scope="module")
+def E():
+    from paper_1511_03703_amd import ens
+    ens.lib()
+    return ens
+
+
+def _rand(shape, seed):
+    return torch.as_tensor(np.random.default_rng(seed).standard_normal(shape), device=DEV)
+
+
+def _close(got, a, b, n):
+    ref, mag = a.t() @ b, a.abs().t() @ b.abs()
+    assert bool(((got - ref).abs() <= (2 * n + 3) * 2.0 ** -53 * mag).all())
+
+
+def _need(fn, *sizes):
+    b = ctypes.c_size_t()
+    assert fn(*sizes, ctypes.byref(b)) == 0
+    return b.value
+
+
+@pytest.mark.parametrize("n", [1, 300, 8191, 8192, 20000])
+@pytest.mark.parametrize("m", [5, 130])
+def test_gram_and_projection(E, n, m):
+    L, st = E.lib(), E._stream()
+    least = min(n // 4096, 32)
+    S, X, Phi = _rand((n, m), 1), _rand((n, m), 2), _rand((n, 7), 3)
+    G, C = (torch.empty(k, dtype=torch.float64, device=DEV) for k in ((m, m), (m, 7)))
+    gram = lambda ws, b: L.ens_pod_gram(E._ptr(S), n, m, E._ptr(G), E._ptr(ws), b, st)  # noqa: E731
+    proj = lambda ws, b: L.ens_pod_project(E._ptr(Phi), E._ptr(X), n, 7, m, E._ptr(C), E._ptr(ws), b, st)  # noqa: E731
+    for call, out, slice_, full, a, b in (
+            (gram, G, 8 * m * m, _need(L.ens_pod_gram_workspace_bytes, n, m), S, S),
+            (proj, C, 8 * m * 7, _need(L.ens_pod_project_workspace_bytes, n, 7, m), X, Phi)):
+        ws = torch.empty(max(full, (least + 1) * slice_), dtype=torch.uint8, device=DEV)
+        sizes = {full, least * slice_, least * slice_ + slice_ - 1, (least + 1) * slice_}
+        if least <= 1:
+            sizes |= {0, 1}
+        for size in sorted(sizes):
+            out.fill_(float("nan"))
+            assert call(ws, size) == E.ENS_OK, (n, m, size)
+            _close(out, a, b, n)
+        if least <= 1:
+            out.fill_(float("nan"))
+            assert call(None, 0) == E.ENS_OK
+            _close(out, a, b, n)
+        else:
+            assert call(None, full) == E.ENS_E_ARG
+            assert call(ws, least * slice_ - 1) == E.ENS_E_NOMEM
+
+
+@pytest.mark.parametrize("m,k", [(40, 12), (600, 40), (600, 100)])
+def test_eigenpairs(E, m, k):
+    # a spectrum that falls by half an index: 20 steps leave the first 4 pairs
+    # to 2^(-20 (k - 3)) of their size, under rounding
+    L, st = E.lib(), E._stream()
+    q, _ = np.linalg.qr(np.random.default_rng(4).standard_normal((m, m)))
+    lam = 0.5 ** np.arange(m)
+    G = torch.as_tensor(q @ np.diag(lam) @ q.T, device=DEV)
+    start = _rand((m, k), 5)
+    least, full = 8 * (3 * m * k + 3 * k * k + 64), _need(L.ens_pod_eig_workspace_bytes, m, k)
+    ws = torch.empty(max(full, least + 8 * 3 * m * k), dtype=torch.uint8, device=DEV)
+    for size in (least, least + 8 * k * k, least + 8 * 3 * m * k, full):
+        V = torch.full((m, 4), float("nan"), dtype=torch.float64, device=DEV)
+        ev = torch.full((4,), float("nan"), dtype=torch.float64, device=DEV)
+        rc = L.ens_pod_eig(E._ptr(G), m, k, 4, E._ptr(start), 20, E._ptr(V), E._ptr(ev), E._ptr(ws), size, st)
+        assert rc == E.ENS_OK, size
+        # rounding of G itself and of the products: m eps each, an eigenvector's
+        # over its gap (half the eigenvalue)
+        tol = 8 * m * 2.0 ** -53
+        assert np.abs(ev.cpu().numpy() - lam[:4]).max() <= tol
+        dot = np.abs((V.cpu().numpy() * q[:, :4]).sum(0))
+        assert np.abs(dot - 1.0).max() <= tol / lam[4]
+    rc = L.ens_pod_eig(E._ptr(G), m, k, 4, E._ptr(start), 20, E._ptr(V), E._ptr(ev), E._ptr(ws), least - 1, st)
+    assert rc == E.ENS_E_NOMEM
