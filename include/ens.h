@@ -350,7 +350,10 @@ typedef struct {
                            replay it; 0: launch the same kernels directly      */
 } ens_batch_opts;
 
-/* Bytes of workspace ens_solve_batch needs for these groups. */
+/* Bytes of workspace ens_solve_batch uses for these groups.  At s = 8 it also
+ * runs, a few per cent slower, without the last 256 bytes for every opts->tile *
+ * 16 rows of a group and 256 more for every 256 of those (rounded up to 256
+ * bytes over all groups); less is refused (ENS_E_NOMEM). */
 ens_status ens_batch_workspace_bytes(const ens_group* groups, int32_t n_groups, int32_t s,
                                      const ens_batch_opts* opts, size_t* bytes);
 

@@ -53,29 +53,42 @@ struct BatchDev {
   const int32_t* redv_grp;  // [stage-1 rows of vector reductions]
   double* part;             // [max(row, vector blocks)][2S]
   double* out1;             // [max(stage-1 rows)][2S]
+  double* wide;             // [row blocks][KS][S], then [stage-1 rows of row reductions][KS][S]; or null: see Plan
 };
 
+// A tile of rows is what NW wavefronts hold with one lane group a row; where KS
+// groups share a row it is KS pieces.  The tables of a batch have an entry a
+// tile, and the partial sums room for 2 S values a tile: the residual's workgroups
+// take a tile each, piece by piece.  The product runs best with a workgroup a
+// piece (s = 8, meshes 57, 64 and 40: 37.2 ms; two pieces a workgroup 38.6,
+// four 40.0; one lane group a row 45.0), whose KS S partials a tile, and their
+// stage-1 sums, are an area of their own at the end of the workspace; in a
+// workspace without it, a workgroup takes half a tile, so that its two S partials
+// fit.
 template <int S, int NW>
 struct Plan {
   static constexpr int KS = row_groups<double, S, true, false>();
-  static constexpr int RB = RowPlace<double, S, KS, NW>::R;  // rows per row tile
+  static constexpr int RB = KS * RowPlace<double, S, KS, NW>::R;  // rows per row tile
   static constexpr int VB = kBlock * kU;                  // chunks per vector block
 };
 
-template <int S, int NW>
-__global__ __launch_bounds__(NW * 64) void kb_spmv_dot(BatchDev bd) {
+// D workgroups a row tile.
+template <int S, int NW, int D>
+__global__ __launch_bounds__(NW * 64) void kb_spmv_dot(BatchDev bd, double* __restrict__ part) {
+  constexpr int KS = Plan<S, NW>::KS;
   const int64_t blk = blockIdx.x;
-  const GroupDev& g = bd.groups[bd.row_grp[blk]];
+  const GroupDev& g = bd.groups[bd.row_grp[blk / D]];
   if (g.ctl->n_active == 0) return;
-  spmv_dot_body<double, S, Plan<S, NW>::KS, NW>(g.n, g.rp, g.ci, g.vals, g.p, g.q, blk - g.row0, bd.part + blk * S);
+  spmv_dot_body<double, S, KS, NW, KS / D>(g.n, g.rp, g.ci, g.vals, g.p, g.q, blk - g.row0 * D, part + blk * S);
 }
 
 template <int S, int NW>
 __global__ __launch_bounds__(NW * 64) void kb_residual(BatchDev bd, int store_r) {
   const int64_t blk = blockIdx.x;
   const GroupDev& g = bd.groups[bd.row_grp[blk]];
-  residual_body<S, double, Plan<S, NW>::KS, NW>(g.n, g.rp, g.ci, g.vals, g.x, g.b, store_r ? g.r : (double*)nullptr, blk - g.row0,
-                               bd.part + blk * 2 * S);
+  constexpr int KS = Plan<S, NW>::KS;
+  residual_body<S, double, KS, NW, KS>(g.n, g.rp, g.ci, g.vals, g.x, g.b, store_r ? g.r : (double*)nullptr,
+                                       blk - g.row0, bd.part + blk * 2 * S);
 }
 
 template <int S>
@@ -107,27 +120,30 @@ __global__ __launch_bounds__(256) void kb_cg_start(BatchDev bd) {
 }
 
 // Stage 1: stage-1 row c of group g sums partial rows
-// [first + j kSegRows, first + (j+1) kSegRows) of that group, j = c - red0.
-template <int P, int VEC>
-__global__ __launch_bounds__(256) void kb_stage1(BatchDev bd, int gate) {
+// [first + j kSegRows, first + (j+1) kSegRows) of that group, j = c - red0
+// (D partial rows a tile: D times as many rows of both stages).
+template <int P, int VEC, int D = 1>
+__global__ __launch_bounds__(256) void kb_stage1(BatchDev bd, const double* __restrict__ part,
+                                                 double* __restrict__ out1, int gate) {
   const int64_t c = blockIdx.x;
-  const GroupDev& g = bd.groups[(VEC ? bd.redv_grp : bd.red_grp)[c]];
+  const GroupDev& g = bd.groups[(VEC ? bd.redv_grp : bd.red_grp)[c / D]];
   if (gate && g.ctl->n_active == 0) return;
-  const int64_t first = VEC ? g.vec0 : g.row0;
-  const int64_t count = VEC ? g.nvecb : g.nrowb;
-  const int64_t j = c - (VEC ? g.redv0 : g.red0);
+  const int64_t first = D * (VEC ? g.vec0 : g.row0);
+  const int64_t count = D * (VEC ? g.nvecb : g.nrowb);
+  const int64_t j = c - D * (VEC ? g.redv0 : g.red0);
   const int64_t r0 = j * kSegRows;
   const int64_t r1 = r0 + kSegRows < count ? r0 + kSegRows : count;
-  sum_rows<P>(bd.part + (first + r0) * P, r1 - r0, bd.out1 + c * P);
+  sum_rows<P>(part + (first + r0) * P, r1 - r0, out1 + c * P);
 }
 
 // Stage 2: workgroup g sums its stage-1 rows and updates its state.
-template <int S, int NQ, int VEC>
-__global__ __launch_bounds__(256) void kb_final(BatchDev bd, int op, int arg, int gate) {
+template <int S, int NQ, int VEC, int D = 1>
+__global__ __launch_bounds__(256) void kb_final(BatchDev bd, const double* __restrict__ out1, int op, int arg,
+                                                int gate) {
   const GroupDev& g = bd.groups[blockIdx.x];
   Ctl* c = g.ctl;
   if (gate && gated(c, op)) return;
-  sum_rows<NQ * S>(bd.out1 + (VEC ? g.redv0 : g.red0) * NQ * S, VEC ? g.nredv : g.nred, c->tot);
+  sum_rows<NQ * S>(out1 + D * (VEC ? g.redv0 : g.red0) * NQ * S, D * (VEC ? g.nredv : g.nred), c->tot);
   if (NQ == 1 && threadIdx.x < S) c->tot[S + threadIdx.x] = 0.0;
   __syncthreads();
   finalize<S>(c, op, arg);
@@ -208,7 +224,8 @@ struct Layout {
   std::vector<GroupDev> g;
   std::vector<int32_t> row_grp, vec_grp, red_grp, redv_grp;
   int64_t row_blocks = 0, vec_blocks = 0, red_rows = 0, redv_rows = 0;
-  size_t bytes = 0;
+  size_t bytes = 0;       // without the product's own partial sums
+  size_t wide_bytes = 0;  // of those
   size_t off_groups, off_tables, off_part, off_out1, off_ctl, off_vec, off_count;
 };
 
@@ -274,6 +291,7 @@ static ens_status plan(const ens_group* groups, int ng, Layout& L) {
   L.off_vec = off;
   off += vec_bytes;
   L.bytes = off;
+  L.wide_bytes = PL::KS > 1 ? r256(sizeof(double) * PL::KS * S * (size_t)(L.row_blocks + L.red_rows)) : 0;
   return ENS_OK;
 }
 
@@ -302,14 +320,22 @@ static BatchDev bind(Layout& L, char* ws, int ng, int S) {
   return bd;
 }
 
+// q = A p and alpha, D workgroups a row tile.
+template <int S, int NW, int D>
+static void batch_product(const BatchDev& bd, const Layout& L, int ng, double* part, double* out1, hipStream_t st) {
+  hipLaunchKernelGGL((kb_spmv_dot<S, NW, D>), dim3((unsigned)(D * L.row_blocks)), dim3(NW * 64), 0, st, bd, part);
+  hipLaunchKernelGGL((kb_stage1<S, 0, D>), dim3((unsigned)(D * L.red_rows)), dim3(256), 0, st, bd, part, out1, 1);
+  hipLaunchKernelGGL((kb_final<S, 1, 0, D>), dim3((unsigned)ng), dim3(256), 0, st, bd, out1, (int)OP_ALPHA, 0, 1);
+}
+
 template <int S, int NW>
 static void batch_iteration(const BatchDev& bd, const Layout& L, int ng, hipStream_t st) {
-  hipLaunchKernelGGL((kb_spmv_dot<S, NW>), dim3((unsigned)L.row_blocks), dim3(NW * 64), 0, st, bd);
-  hipLaunchKernelGGL((kb_stage1<S, 0>), dim3((unsigned)L.red_rows), dim3(256), 0, st, bd, 1);
-  hipLaunchKernelGGL((kb_final<S, 1, 0>), dim3((unsigned)ng), dim3(256), 0, st, bd, (int)OP_ALPHA, 0, 1);
+  constexpr int KS = Plan<S, NW>::KS;
+  if (bd.wide) batch_product<S, NW, KS>(bd, L, ng, bd.wide, bd.wide + KS * S * L.row_blocks, st);
+  else batch_product<S, NW, (KS > 1 ? 2 : 1)>(bd, L, ng, bd.part, bd.out1, st);
   hipLaunchKernelGGL(kb_update<S>, dim3((unsigned)L.vec_blocks), dim3(256), 0, st, bd);
-  hipLaunchKernelGGL((kb_stage1<2 * S, 1>), dim3((unsigned)L.redv_rows), dim3(256), 0, st, bd, 1);
-  hipLaunchKernelGGL((kb_final<S, 2, 1>), dim3((unsigned)ng), dim3(256), 0, st, bd, (int)OP_UPDATE, 0, 1);
+  hipLaunchKernelGGL((kb_stage1<2 * S, 1>), dim3((unsigned)L.redv_rows), dim3(256), 0, st, bd, bd.part, bd.out1, 1);
+  hipLaunchKernelGGL((kb_final<S, 2, 1>), dim3((unsigned)ng), dim3(256), 0, st, bd, bd.out1, (int)OP_UPDATE, 0, 1);
   hipLaunchKernelGGL(kb_pupdate<S>, dim3((unsigned)L.vec_blocks), dim3(256), 0, st, bd);
 }
 
@@ -342,12 +368,12 @@ static void batch_setup(const BatchDev& bd, const Layout& L, int ng, double rtol
   hipLaunchKernelGGL(kb_ctl_init, dim3((unsigned)(ng < 1024 ? ng : 1024)), dim3(64), 0, st, bd, ng, rtol, max_iter);
   hipLaunchKernelGGL(kb_diag_inv<S>, dim3(2048), dim3(256), 0, st, bd, ng);
   hipLaunchKernelGGL((kb_residual<S, NW>), dim3((unsigned)L.row_blocks), dim3(NW * 64), 0, st, bd, 1);
-  hipLaunchKernelGGL((kb_stage1<2 * S, 0>), dim3((unsigned)L.red_rows), dim3(256), 0, st, bd, 0);
-  hipLaunchKernelGGL((kb_final<S, 2, 0>), dim3((unsigned)ng), dim3(256), 0, st, bd, (int)OP_START, 0, 0);
+  hipLaunchKernelGGL((kb_stage1<2 * S, 0>), dim3((unsigned)L.red_rows), dim3(256), 0, st, bd, bd.part, bd.out1, 0);
+  hipLaunchKernelGGL((kb_final<S, 2, 0>), dim3((unsigned)ng), dim3(256), 0, st, bd, bd.out1, (int)OP_START, 0, 0);
   hipLaunchKernelGGL(kb_zero_where<S>, dim3(1024), dim3(256), 0, st, bd, ng);
   hipLaunchKernelGGL(kb_cg_start<S>, dim3((unsigned)L.vec_blocks), dim3(256), 0, st, bd);
-  hipLaunchKernelGGL((kb_stage1<2 * S, 1>), dim3((unsigned)L.redv_rows), dim3(256), 0, st, bd, 0);
-  hipLaunchKernelGGL((kb_final<S, 2, 1>), dim3((unsigned)ng), dim3(256), 0, st, bd, (int)OP_RHO, 0, 0);
+  hipLaunchKernelGGL((kb_stage1<2 * S, 1>), dim3((unsigned)L.redv_rows), dim3(256), 0, st, bd, bd.part, bd.out1, 0);
+  hipLaunchKernelGGL((kb_final<S, 2, 1>), dim3((unsigned)ng), dim3(256), 0, st, bd, bd.out1, (int)OP_RHO, 0, 0);
 }
 
 // Capture `enqueue` on st into an executable graph.
@@ -375,7 +401,7 @@ static ens_status capture(hipStream_t st, F&& enqueue, hipGraph_t* graph, hipGra
 
 template <int S, int NW>
 static ens_status solve_batch(const ens_group* groups, int ng, const ens_batch_opts& o, void* ws, size_t ws_bytes,
-                              hipStream_t user, const Prologue* pro = nullptr) {
+                              hipStream_t user, const Prologue* pro = nullptr, size_t pro_end = 0) {
   Layout L;
   ens_status rc = plan<S, NW>(groups, ng, L);
   if (rc != ENS_OK) return rc;
@@ -385,6 +411,8 @@ static ens_status solve_batch(const ens_group* groups, int ng, const ens_batch_o
   }
   char* w = (char*)ws;
   BatchDev bd = bind(L, w, ng, S);
+  const size_t used = pro_end > L.bytes ? pro_end : L.bytes;
+  bd.wide = L.wide_bytes > 0 && ws_bytes >= used + L.wide_bytes ? (double*)(w + used) : nullptr;
   int32_t* dcount = (int32_t*)(w + L.off_count);
   DeviceCtx* cx = device_ctx();
   if (!cx) {
@@ -465,8 +493,8 @@ static ens_status solve_batch(const ens_group* groups, int ng, const ens_batch_o
   if (out != ENS_OK) return out;
   // true residuals
   hipLaunchKernelGGL((kb_residual<S, NW>), dim3((unsigned)L.row_blocks), dim3(NW * 64), 0, st, bd, 0);
-  hipLaunchKernelGGL((kb_stage1<2 * S, 0>), dim3((unsigned)L.red_rows), dim3(256), 0, st, bd, 0);
-  hipLaunchKernelGGL((kb_final<S, 2, 0>), dim3((unsigned)ng), dim3(256), 0, st, bd, (int)OP_TRUE, 0, 0);
+  hipLaunchKernelGGL((kb_stage1<2 * S, 0>), dim3((unsigned)L.red_rows), dim3(256), 0, st, bd, bd.part, bd.out1, 0);
+  hipLaunchKernelGGL((kb_final<S, 2, 0>), dim3((unsigned)ng), dim3(256), 0, st, bd, bd.out1, (int)OP_TRUE, 0, 0);
   ENS_LAUNCH_CHECK();
   std::vector<Ctl> h(ng);
   ENS_HIP_TRY(hipMemcpyAsync(h.data(), w + L.off_ctl, sizeof(Ctl) * ng, hipMemcpyDeviceToHost, st));
@@ -521,7 +549,7 @@ static ens_status assemble_solve(const ens_group* groups, const ens_group_input*
   const size_t off_ag = r256(L.bytes), off_bg = off_ag + r256(sizeof(AsmGroupDev) * ng);
   const size_t total = off_bg + r256(sizeof(int32_t) * (size_t)blocks);
   if (need) {
-    *need = total;
+    *need = total + L.wide_bytes;
     return ENS_OK;
   }
   if (ws_bytes < total) {
@@ -537,14 +565,19 @@ static ens_status assemble_solve(const ens_group* groups, const ens_group_input*
   pro.blocks = blocks;
   pro.prob = &prob;
   // the host tables stay alive until solve_batch has synchronised
-  return solve_batch<S, NW>(groups, ng, o, ws, ws_bytes, user, &pro);
+  return solve_batch<S, NW>(groups, ng, o, ws, ws_bytes, user, &pro, total);
 }
 
 static bool tile_ok(int t) { return t == 2 || t == 4 || t == 8; }
 
+// Bytes of a batch's workspace: what it cannot do without, and all it uses.
+struct Need {
+  size_t least = 0, full = 0;
+};
+
 template <int S>
 static ens_status dispatch_tile(const ens_group* g, int ng, const ens_batch_opts& o, void* ws, size_t b,
-                                hipStream_t st, size_t* need) {
+                                hipStream_t st, Need* need) {
   Layout L;
   ens_status rc;
   switch (o.tile) {
@@ -552,12 +585,12 @@ static ens_status dispatch_tile(const ens_group* g, int ng, const ens_batch_opts
     case 4: rc = need ? plan<S, 4>(g, ng, L) : solve_batch<S, 4>(g, ng, o, ws, b, st); break;
     default: rc = need ? plan<S, 8>(g, ng, L) : solve_batch<S, 8>(g, ng, o, ws, b, st); break;
   }
-  if (need && rc == ENS_OK) *need = L.bytes;
+  if (need && rc == ENS_OK) *need = Need{L.bytes, L.bytes + L.wide_bytes};
   return rc;
 }
 
 static ens_status dispatch(const ens_group* g, int ng, int32_t s, const ens_batch_opts& o, void* ws, size_t b,
-                           hipStream_t st, size_t* need) {
+                           hipStream_t st, Need* need) {
   switch (s) {
     case 8: return dispatch_tile<8>(g, ng, o, ws, b, st, need);
     case 16: return dispatch_tile<16>(g, ng, o, ws, b, st, need);
@@ -617,7 +650,10 @@ ens_status ens_batch_workspace_bytes(const ens_group* groups, int32_t n_groups, 
                                      size_t* bytes) {
   ENS_ARG_CHECK(groups && n_groups >= 1 && opts && bytes, "bad batch arguments");
   ENS_ARG_CHECK(tile_ok(opts->tile), "tile must be 2, 4 or 8 wavefronts");
-  return dispatch(groups, n_groups, s, *opts, nullptr, 0, nullptr, bytes);
+  Need need;
+  const ens_status rc = dispatch(groups, n_groups, s, *opts, nullptr, 0, nullptr, &need);
+  if (rc == ENS_OK) *bytes = need.full;
+  return rc;
 }
 
 ens_status ens_solve_batch(const ens_group* groups, int32_t n_groups, int32_t s, const ens_batch_opts* opts,
@@ -682,14 +718,14 @@ struct TrialMesh {
 constexpr int kTrial = 32;  // samples per mesh in every trial
 
 // The autotuner's caller-owned workspace: each mesh's trial buffers at
-// 256-byte aligned offsets from `base`, then the largest batch-solver
-// workspace any candidate needs.  With base == nullptr only the sizes are
+// 256-byte aligned offsets from `base`, then the batch-solver workspace that
+// holds any candidate's (at the least, and with all they use).  With base == nullptr only the sizes are
 // formed (the solver's need depends on the shapes alone, so its plan runs
 // on the offsets themselves).
 static ens_status tune_layout(char* base, const int32_t* meshes, int nm, const ens_problem& pr,
                               const int32_t* s_cand, int ns, const int32_t* tile_cand, int nt,
-                              const ens_batch_opts& o0, std::vector<TrialMesh>& t, char** ws, size_t* ws_need,
-                              size_t* total) {
+                              const ens_batch_opts& o0, std::vector<TrialMesh>& t, char** ws, Need* ws_need,
+                              Need* total) {
   // a non-null stand-in address keeps the plan's pointer checks meaningful
   // when only sizes are wanted; nothing is dereferenced then
   char* b0 = base ? base : (char*)(uintptr_t)256;
@@ -718,7 +754,7 @@ static ens_status tune_layout(char* base, const int32_t* meshes, int nm, const e
     m.x = (double*)take(sizeof(double) * kTrial * m.n);
     m.g = ens_graph{(int32_t)m.n, m.nnz, m.rp, m.ci};
   }
-  size_t need = 0;
+  Need need;
   std::vector<ens_cg_stat> stats((size_t)kTrial);
   for (int a = 0; a < ns; ++a) {
     const int s = s_cand[a];
@@ -729,15 +765,16 @@ static ens_status tune_layout(char* base, const int32_t* meshes, int nm, const e
     for (int c = 0; c < nt; ++c) {
       ens_batch_opts o = o0;
       o.tile = tile_cand[c];
-      size_t nb = 0;
-      ens_status rc = ens_batch_workspace_bytes(gr.data(), (int)gr.size(), s, &o, &nb);
+      Need nb;
+      ens_status rc = dispatch(gr.data(), (int)gr.size(), s, o, nullptr, 0, nullptr, &nb);
       if (rc != ENS_OK) return rc;
-      need = nb > need ? nb : need;
+      need.least = nb.least > need.least ? nb.least : need.least;
+      need.full = nb.full > need.full ? nb.full : need.full;
     }
   }
-  *ws = take(need);
+  *total = Need{off + r256(need.least), off + r256(need.full)};
+  *ws = take(need.full);
   *ws_need = need;
-  *total = off;
   return ENS_OK;
 }
 
@@ -766,8 +803,10 @@ extern "C" ens_status ens_batch_autotune_workspace_bytes(const int32_t* meshes, 
   if (rc != ENS_OK) return rc;
   std::vector<TrialMesh> t;
   char* ws = nullptr;
-  size_t need = 0;
-  return tune_layout(nullptr, meshes, nm, *prob, s_cand, ns, tile_cand, nt, *base, t, &ws, &need, bytes);
+  Need need, total;
+  rc = tune_layout(nullptr, meshes, nm, *prob, s_cand, ns, tile_cand, nt, *base, t, &ws, &need, &total);
+  if (rc == ENS_OK) *bytes = total.full;
+  return rc;
 }
 
 extern "C" ens_status ens_batch_autotune(const int32_t* meshes, int32_t nm, const ens_problem* prob,
@@ -790,13 +829,14 @@ extern "C" ens_status ens_batch_autotune(const int32_t* meshes, int32_t nm, cons
   const int M = prob->M;
   std::vector<TrialMesh> t;
   char* ws = nullptr;
-  size_t ws_need = 0, total = 0;
+  Need ws_need, total;
   rc = tune_layout((char*)workspace, meshes, nm, *prob, s_cand, ns, tile_cand, nt, *base, t, &ws, &ws_need, &total);
   if (rc != ENS_OK) return rc;
-  if (ws_bytes < total) {
-    set_error("autotune workspace too small: %zu < %zu bytes", ws_bytes, total);
+  if (ws_bytes < total.least) {
+    set_error("autotune workspace too small: %zu < %zu bytes", ws_bytes, total.least);
     return ENS_E_ARG;
   }
+  const size_t ws_held = ws_bytes < total.full ? ws_need.least : ws_need.full;
   std::vector<ens_cg_stat> stats((size_t)nm * kTrial);
   hipEvent_t e0 = nullptr, e1 = nullptr;
   double best = -1.0;
@@ -842,7 +882,7 @@ extern "C" ens_status ens_batch_autotune(const int32_t* meshes, int32_t nm, cons
       for (int rep = 0; rep < reps; ++rep) {
         for (int i = 0; i < nm; ++i) TUNE_TRY(hipMemsetAsync(t[i].x, 0, sizeof(double) * kTrial * t[i].n, stream));
         TUNE_TRY(hipEventRecord(e0, stream));
-        rc = ens_solve_batch(gr.data(), (int)gr.size(), s, &o, ws, ws_need, stream);
+        rc = ens_solve_batch(gr.data(), (int)gr.size(), s, &o, ws, ws_held, stream);
         if (rc != ENS_OK && rc != ENS_W_NOT_CONVERGED) goto done;
         TUNE_TRY(hipEventRecord(e1, stream));
         TUNE_TRY(hipEventSynchronize(e1));

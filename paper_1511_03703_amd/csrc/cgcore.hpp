@@ -300,31 +300,33 @@ __device__ inline void diag_inv_body(int n, const int32_t* __restrict__ rp, cons
 }
 
 // r = b - A x in FP64 for the row tile `blk` (NW wavefronts, KS lane groups a
-// row), optionally stored (rounded to TR), with the block's partials |r|^2 and
-// |b|^2 written to dst[2][S].
-template <int S, typename TR, int KS, int NW>
+// row, PIECES times the rows they hold at once), optionally stored (rounded to
+// TR), with the block's partials |r|^2 and |b|^2 written to dst[2][S].
+template <int S, typename TR, int KS, int NW, int PIECES = 1>
 __device__ inline void residual_body(int n, const int32_t* __restrict__ rp, const int32_t* __restrict__ ci,
                                      const double* __restrict__ vals, const double* __restrict__ x,
                                      const double* __restrict__ b, TR* __restrict__ rout, int64_t blk,
                                      double* __restrict__ dst, bool x_zero = false) {
   using M = EnsMap<double, S, KS>;
-  const RowPlace<double, S, KS, NW> at;
-  constexpr int R = at.R;
+  RowPlace<double, S, KS, NW> at;
+  constexpr int R = PIECES * at.R;
   double acc[2][M::V];
 #pragma unroll
   for (int j = 0; j < M::V; ++j) acc[0][j] = acc[1][j] = 0.0;
   __shared__ RowTileLds<R> tile;
   const bool staged = !x_zero && stage_row_tile(tile, n, rp, ci, blk * R);
-  const int64_t row = blk * R + at.lr;
-  if (row < n) {
+#pragma unroll 1
+  for (int piece = 0; piece < PIECES; ++piece, at.lr += at.R) {
+    const int64_t row = blk * R + at.lr;
+    if (row >= n) break;
     const typename M::vt ax = x_zero ? (typename M::vt)0.0 : tile_row_product<double>(at, tile, staged, ci, vals, x);
     if (at.g == 0) {
       const typename M::vt bv = load_stream((const typename M::vt*)b + row * M::L + at.sub);
       const typename M::vt r = bv - ax;
 #pragma unroll
       for (int j = 0; j < M::V; ++j) {
-        acc[0][j] = r[j] * r[j];
-        acc[1][j] = bv[j] * bv[j];
+        acc[0][j] += r[j] * r[j];
+        acc[1][j] += bv[j] * bv[j];
       }
       if (rout) {
         typename vec_t<TR, M::V>::type rv;
@@ -375,28 +377,30 @@ __device__ inline void cg_start_body(int64_t nchunks, const T* __restrict__ r, c
   block_partials<S, M::VS, 2, kBlock / 64>(acc, dst);
 }
 
-// A: q = A p for row tile `blk` (NW wavefronts, KS lane groups a row),
-// partials p.q to dst[S].
-template <typename T, int S, int KS, int NW>
+// A: q = A p for row tile `blk` (NW wavefronts, KS lane groups a row, PIECES
+// times the rows they hold at once), partials p.q to dst[S].
+template <typename T, int S, int KS, int NW, int PIECES = 1>
 __device__ inline void spmv_dot_body(int n, const int32_t* __restrict__ rp, const int32_t* __restrict__ ci,
                                      const T* __restrict__ vals, const T* __restrict__ p, T* __restrict__ q,
                                      int64_t blk, double* __restrict__ dst) {
   using M = EnsMap<T, S, KS>;
-  const RowPlace<T, S, KS, NW> at;
-  constexpr int R = at.R;
+  RowPlace<T, S, KS, NW> at;
+  constexpr int R = PIECES * at.R;
   double acc[1][M::V];
 #pragma unroll
   for (int j = 0; j < M::V; ++j) acc[0][j] = 0.0;
   __shared__ RowTileLds<R> tile;
   const bool staged = stage_row_tile(tile, n, rp, ci, blk * R);
-  const int64_t row = blk * R + at.lr;
-  if (row < n) {
+#pragma unroll 1
+  for (int piece = 0; piece < PIECES; ++piece, at.lr += at.R) {
+    const int64_t row = blk * R + at.lr;
+    if (row >= n) break;
     const typename M::vt qv = tile_row_product<T>(at, tile, staged, ci, vals, p);
     if (at.g == 0) {
       store_stream((typename M::vt*)q + row * M::L + at.sub, qv);
       const typename M::vt pv = ((const typename M::vt*)p)[row * M::L + at.sub];
 #pragma unroll
-      for (int j = 0; j < M::V; ++j) acc[0][j] = (double)pv[j] * (double)qv[j];
+      for (int j = 0; j < M::V; ++j) acc[0][j] += (double)pv[j] * (double)qv[j];
     }
   }
   block_partials<S, M::V, 1, NW>(acc, dst);

@@ -879,7 +879,8 @@ def solve_batch(groups, s, opts: ens_batch_opts | None = None, workspace=None, s
                 strict_workspace=False):
     """groups: list of (Graph, values [nnz][s], b [n][s], x [n][s]).  Returns
     (per-group stats lists, status, workspace).  A workspace smaller than
-    required is replaced by a new one, or refused with strict_workspace."""
+    ens_batch_workspace_bytes is replaced by a new one; with strict_workspace
+    it is taken if it is enough and refused if not."""
     if opts is None:
         opts = batch_opts()
     keep = []
@@ -894,9 +895,8 @@ def solve_batch(groups, s, opts: ens_batch_opts | None = None, workspace=None, s
     nb = _SZ()
     _check(lib().ens_batch_workspace_bytes(arr, len(groups), s, ctypes.byref(opts), ctypes.byref(nb)),
            "ens_batch_workspace_bytes")
-    if workspace is not None and workspace.numel() < nb.value and strict_workspace:
-        raise EnsError(ENS_E_NOMEM, "solve_batch", f"workspace of {workspace.numel()} bytes, {nb.value} required")
-    if workspace is None or workspace.numel() < nb.value:
+    # (a strict caller's workspace is the library's to refuse: it may be enough)
+    if workspace is None or (workspace.numel() < nb.value and not strict_workspace):
         workspace = torch.empty(nb.value, dtype=torch.uint8, device=groups[0][1].device)
     rc = _check(lib().ens_solve_batch(arr, len(groups), s, ctypes.byref(opts), _ptr(workspace), workspace.numel(),
                                       _stream(stream)), "ens_solve_batch", allow=(ENS_OK, ENS_W_NOT_CONVERGED))
@@ -927,10 +927,8 @@ def assemble_solve_batch(groups, inputs, s, M, sigma, opts: ens_batch_opts | Non
     _check(lib().ens_assemble_solve_batch_workspace_bytes(arr, inp, len(groups), s, ctypes.byref(prob),
                                                           ctypes.byref(opts), ctypes.byref(nb)),
            "ens_assemble_solve_batch_workspace_bytes")
-    if workspace is not None and workspace.numel() < nb.value and strict_workspace:
-        raise EnsError(ENS_E_NOMEM, "assemble_solve_batch",
-                       f"workspace of {workspace.numel()} bytes, {nb.value} required")
-    if workspace is None or workspace.numel() < nb.value:
+    # (a strict caller's workspace is the library's to refuse: it may be enough)
+    if workspace is None or (workspace.numel() < nb.value and not strict_workspace):
         workspace = torch.empty(nb.value, dtype=torch.uint8, device=groups[0][1].device)
     rc = _check(lib().ens_assemble_solve_batch(arr, inp, len(groups), s, ctypes.byref(prob), ctypes.byref(opts),
                                                _ptr(workspace), workspace.numel(), _stream(stream)),
