@@ -211,20 +211,23 @@ __device__ void finalize(Ctl* c, int op, int arg) {
       }
     }
   }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int na = 0, no = 0;
-    double most = 0.0;
-    for (int j = 0; j < S; ++j) {
-      na += c->active[j];
-      no += c->oactive[j];
-      if (c->active[j] && c->ratio[j] > most) most = c->ratio[j];
+  // the samples' flags and ratios meet within the first wavefront, each lane
+  // reading back its own sample's (by one lane in turn, a ratio only of an active
+  // sample: the batch on a 16^3 mesh, s = 32 2.00 -> 2.21 ms, a 37^3, s = 8 solve
+  // 4.42 -> 4.52)
+  if (threadIdx.x < 64) {
+    const bool act = e < S && c->active[e] != 0, out = e < S && c->oactive[e] != 0;
+    double most = act && c->ratio[e] > 0.0f ? (double)c->ratio[e] : 0.0;
+#pragma unroll
+    for (int off = 1; off < S; off <<= 1) most = fmax(most, __shfl_xor(most, off, 64));
+    const int na = __popcll(__ballot(act)), no = __popcll(__ballot(out));
+    if (threadIdx.x == 0) {
+      c->n_active = na;
+      c->n_oactive = no;
+      c->progress = most;
+      if (op == OP_ALPHA) c->n_step = na;
+      if (op == OP_START || op == OP_OUTER) c->progress0 = most;
     }
-    c->n_active = na;
-    c->n_oactive = no;
-    c->progress = most;
-    if (op == OP_ALPHA) c->n_step = na;
-    if (op == OP_START || op == OP_OUTER) c->progress0 = most;
   }
 }
 
