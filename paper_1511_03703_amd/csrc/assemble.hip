@@ -794,7 +794,12 @@ __global__ __launch_bounds__(256) void k_kl_extrema(int N, const double* __restr
   __shared__ int s_bad[4];
   const int64_t e = blockIdx.y;
   if (threadIdx.x < M) s_cm[threadIdx.x] = sigma * kl_sqrt_lam[threadIdx.x] * xi[e * M + threadIdx.x];
-  int nx = 1;  // the x indices of the leading modes are 0 .. nx - 1
+  // The x indices of the leading modes are 0 .. nx - 1.  Mode (i, 0, 0) comes
+  // after all permutations of (j, 0, 0), j < i, and after (0, 0, i) and (0, i, 0), so
+  // index i takes 3 i + 1 modes: kAsmMaxM hold at most 6, and no row of the table
+  // past nx (at most M) is read.
+  static_assert(kAsmMaxM < 3 * 6 + 1, "x indices up to 5");
+  int nx = 1;
   for (int m = 0; m < M; ++m) nx = kl_triple[3 * m] >= nx ? kl_triple[3 * m] + 1 : nx;
   __syncthreads();
   double lo = INFINITY, hi = -INFINITY;
@@ -806,8 +811,8 @@ __global__ __launch_bounds__(256) void k_kl_extrema(int N, const double* __restr
       case 2: lines_extrema<2>(two_n, l0, step, kl_triple, kl_phi, s_cm, M, kappa0, lo, hi, bad); break;
       case 3: lines_extrema<3>(two_n, l0, step, kl_triple, kl_phi, s_cm, M, kappa0, lo, hi, bad); break;
       case 4: lines_extrema<4>(two_n, l0, step, kl_triple, kl_phi, s_cm, M, kappa0, lo, hi, bad); break;
-      case 5: case 6: lines_extrema<6>(two_n, l0, step, kl_triple, kl_phi, s_cm, M, kappa0, lo, hi, bad); break;
-      default: lines_extrema<kAsmMaxM>(two_n, l0, step, kl_triple, kl_phi, s_cm, M, kappa0, lo, hi, bad); break;
+      case 5: lines_extrema<5>(two_n, l0, step, kl_triple, kl_phi, s_cm, M, kappa0, lo, hi, bad); break;
+      default: lines_extrema<6>(two_n, l0, step, kl_triple, kl_phi, s_cm, M, kappa0, lo, hi, bad); break;
     }
   else lo = hi = kappa0;
 #pragma unroll
