@@ -738,15 +738,18 @@ __global__ void k_kl_extrema_values(int64_t s, double* __restrict__ kmin, double
 // about the middle of the axis and the Gauss points mirror there, so the
 // coefficient at a point and at its mirror image is E + O and E - O of the
 // even and the odd part: a pair costs its multiply-adds once, E - |O| and
-// E + |O| (measured 293 -> 201 us).  With CHECK, NaN is looked for.
+// E + |O| (measured 293 -> 201 us).  The extremes are those of the modes' sum:
+// kappa0 is added to them afterwards, one rounding at its size (with E starting
+// from kappa0 there was one a mode index, and twice the error).  With CHECK, NaN
+// is looked for.
 template <int NX, bool CHECK>
-__device__ inline void line_extrema(const double* __restrict__ phi, int two_n, const double* w, double kappa0,
-                                    double& lo, double& hi, int& bad) {
+__device__ inline void line_extrema(const double* __restrict__ phi, int two_n, const double* w, double& lo,
+                                    double& hi, int& bad) {
 #pragma unroll 8
   for (int x = 0; x < two_n / 2; ++x) {
-    double ev = kappa0, od = 0.0;
+    double ev = w[0] * phi[x], od = 0.0;
 #pragma unroll
-    for (int i = 0; i < NX; i += 2) ev = fma(w[i], phi[i * (int64_t)two_n + x], ev);
+    for (int i = 2; i < NX; i += 2) ev = fma(w[i], phi[i * (int64_t)two_n + x], ev);
 #pragma unroll
     for (int i = 1; i < NX; i += 2) od = fma(w[i], phi[i * (int64_t)two_n + x], od);
     const double l = ev - fabs(od), h = ev + fabs(od);
@@ -759,8 +762,8 @@ __device__ inline void line_extrema(const double* __restrict__ phi, int two_n, c
 // The lines of one workgroup: every step-th from line0 (one a lane).
 template <int NX>
 __device__ inline void lines_extrema(int two_n, int64_t line0, int64_t step, const int32_t* __restrict__ kl_triple,
-                                     const double* __restrict__ kl_phi, const double* s_cm, int M, double kappa0,
-                                     double& lo, double& hi, int& bad) {
+                                     const double* __restrict__ kl_phi, const double* s_cm, int M, double& lo,
+                                     double& hi, int& bad) {
   const int64_t lines = (int64_t)two_n * two_n;
   for (int64_t l = line0; l < lines; l += step) {
     const int y = (int)(l % two_n), z = (int)(l / two_n);
@@ -778,8 +781,8 @@ __device__ inline void lines_extrema(int two_n, int64_t line0, int64_t step, con
     bool plain = true;
 #pragma unroll
     for (int i = 0; i < NX; ++i) plain = plain && fabs(w[i]) < 1e290;
-    if (plain) line_extrema<NX, false>(kl_phi, two_n, w, kappa0, lo, hi, bad);
-    else line_extrema<NX, true>(kl_phi, two_n, w, kappa0, lo, hi, bad);
+    if (plain) line_extrema<NX, false>(kl_phi, two_n, w, lo, hi, bad);
+    else line_extrema<NX, true>(kl_phi, two_n, w, lo, hi, bad);
   }
 }
 
@@ -803,18 +806,18 @@ __global__ __launch_bounds__(256) void k_kl_extrema(int N, const double* __restr
   for (int m = 0; m < M; ++m) nx = kl_triple[3 * m] >= nx ? kl_triple[3 * m] + 1 : nx;
   __syncthreads();
   double lo = INFINITY, hi = -INFINITY;
-  int bad = kappa0 != kappa0;
+  int bad = 0;
   const int64_t l0 = (int64_t)blockIdx.x * 256 + threadIdx.x, step = (int64_t)gridDim.x * 256;
   const int two_n = 2 * N;
   if (M > 0) switch (nx) {
-      case 1: lines_extrema<1>(two_n, l0, step, kl_triple, kl_phi, s_cm, M, kappa0, lo, hi, bad); break;
-      case 2: lines_extrema<2>(two_n, l0, step, kl_triple, kl_phi, s_cm, M, kappa0, lo, hi, bad); break;
-      case 3: lines_extrema<3>(two_n, l0, step, kl_triple, kl_phi, s_cm, M, kappa0, lo, hi, bad); break;
-      case 4: lines_extrema<4>(two_n, l0, step, kl_triple, kl_phi, s_cm, M, kappa0, lo, hi, bad); break;
-      case 5: lines_extrema<5>(two_n, l0, step, kl_triple, kl_phi, s_cm, M, kappa0, lo, hi, bad); break;
-      default: lines_extrema<6>(two_n, l0, step, kl_triple, kl_phi, s_cm, M, kappa0, lo, hi, bad); break;
+      case 1: lines_extrema<1>(two_n, l0, step, kl_triple, kl_phi, s_cm, M, lo, hi, bad); break;
+      case 2: lines_extrema<2>(two_n, l0, step, kl_triple, kl_phi, s_cm, M, lo, hi, bad); break;
+      case 3: lines_extrema<3>(two_n, l0, step, kl_triple, kl_phi, s_cm, M, lo, hi, bad); break;
+      case 4: lines_extrema<4>(two_n, l0, step, kl_triple, kl_phi, s_cm, M, lo, hi, bad); break;
+      case 5: lines_extrema<5>(two_n, l0, step, kl_triple, kl_phi, s_cm, M, lo, hi, bad); break;
+      default: lines_extrema<6>(two_n, l0, step, kl_triple, kl_phi, s_cm, M, lo, hi, bad); break;
     }
-  else lo = hi = kappa0;
+  else lo = hi = 0.0;
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
     lo = fmin(lo, __shfl_xor(lo, off, 64));
@@ -834,6 +837,9 @@ __global__ __launch_bounds__(256) void k_kl_extrema(int N, const double* __restr
       hi = fmax(hi, s_hi[v]);
       bad |= s_bad[v];
     }
+    lo += kappa0;  // (every workgroup has a line, so both are a point's)
+    hi += kappa0;
+    bad |= (lo != lo) | (hi != hi);
     atomicMin(klo + e, bad ? kExtNanLo : ext_key(lo));
     atomicMax(khi + e, bad ? kExtNanHi : ext_key(hi));
   }
