@@ -294,6 +294,17 @@ __device__ __forceinline__ void diffusion_elements(const double* s_k, int rx, in
     }
 }
 
+// Sum of the off-diagonal entries of neighbour plane z: its three lines of three,
+// then the lines (26 entries added one after the other round at nearly the size of
+// the diagonal that they make up: values of 16^3 off by 4.5e-17 in the norm instead
+// of 3.2e-17, the nonlinear Jacobian's by 4.9e-17 instead of 3.4e-17).
+__device__ inline double plane_off(const double (&acc)[27], int z) {
+  const double l0 = (acc[9 * z] + acc[9 * z + 1]) + acc[9 * z + 2];
+  const double l1 = z == 1 ? acc[12] + acc[14] : (acc[9 * z + 3] + acc[9 * z + 4]) + acc[9 * z + 5];
+  const double l2 = (acc[9 * z + 6] + acc[9 * z + 7]) + acc[9 * z + 8];
+  return (l0 + l1) + l2;
+}
+
 // Whether any row of the wavefront has neighbours on the boundary.
 __device__ inline bool near_boundary(int ii, int jj, int kk, int N) {
   return __ballot(ii <= 1 || jj <= 1 || kk <= 1 || ii >= N - 1 || jj >= N - 1 || kk >= N - 1) != 0;
@@ -419,16 +430,12 @@ __device__ __forceinline__ void assemble_tile_body(int N, const double* __restri
       // every element row sums to zero (the shape functions sum to one, so
       // sum_b grad N_b = 0, and C_ab = sum_q N_a v . grad N_b too), hence so
       // does the assembled row before the boundary conditions: its diagonal is
-      // minus the sum of its other entries (added in ascending neighbour
-      // order), which saves the 8 diagonal element entries' Gauss sums
-      double off = 0.0;
+      // minus the sum of its other entries (plane_off), which saves the 8 diagonal element entries' Gauss sums
+      if (ADV)
 #pragma unroll
-      for (int t = 0; t < 27; ++t)
-        if (t != 13) {
-          if (ADV) acc[t] += s_adv[t];
-          off += acc[t];
-        }
-      acc[13] = -off;
+        for (int t = 0; t < 27; ++t)
+          if (t != 13) acc[t] += s_adv[t];
+      acc[13] = -((plane_off(acc, 0) + plane_off(acc, 1)) + plane_off(acc, 2));
       zero_edges<0, 27>(near, ii, jj, kk, N, acc);
       if (BND) {
         double sabs = 0.0;
@@ -654,10 +661,8 @@ __global__ __launch_bounds__((32 * SB), 3) void k_nl_assemble(int N, const doubl
   auto linear_plane = [&](int z) {  // advection; the off-diagonal sum
 #pragma unroll
     for (int t = z * 9; t < z * 9 + 9; ++t)
-      if (t != 13) {
-        acc[t] += s_adv[t];
-        off += acc[t];
-      }
+      if (t != 13) acc[t] += s_adv[t];
+    off += plane_off(acc, z);
   };
 
   // plane by plane, so that few accumulators are live: plane -1 is complete
