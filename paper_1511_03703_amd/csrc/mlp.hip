@@ -460,6 +460,22 @@ static void rows_pass(const float* p, int B, const float* xi, const float* tgt, 
   hipLaunchKernelGGL(k_mlp_rows<true>, dim3(B / kRows), dim3(1024), 0, st, B, p, xi, tgt, idx, w, out);
 }
 
+// out = the network's outputs, through the scratch rows `through` [B][kOut] when
+// out shares memory with what the workgroups still read.
+static ens_status forward_pass(const float* p, int B, const float* xi, const MlpWork& w, float* out, float* through,
+                               hipStream_t st) {
+  hipLaunchKernelGGL(k_mlp_rows<false>, dim3(B / kRows), dim3(1024), 0, st, B, p, xi, (const float*)nullptr,
+                     (const int32_t*)nullptr, w, through ? through : out);
+  if (through)
+    ENS_HIP_TRY(hipMemcpyAsync(out, through, (size_t)B * kOut * sizeof(float), hipMemcpyDeviceToDevice, st));
+  return ENS_OK;
+}
+
+// Whether `count` floats at a share memory with the outputs of B rows.
+static bool shares(const float* out, int B, const float* a, int64_t count) {
+  return a < out + (int64_t)B * kOut && out < a + count;
+}
+
 static bool batch_ok(int B) { return B >= 32 && B <= 65536 && B % 32 == 0; }
 
 }  // namespace ens
@@ -488,8 +504,9 @@ ens_status ens_mlp_forward(const float* params, int32_t batch, const float* xi, 
   MlpWork w;
   mlp_layout(batch, &w, (char*)workspace);
   weights_bf16(params, w, stream);
-  hipLaunchKernelGGL(k_mlp_rows<false>, dim3(batch / kRows), dim3(1024), 0, stream, batch, params, xi,
-                     (const float*)nullptr, (const int32_t*)nullptr, w, out);
+  const bool in_place = shares(out, batch, xi, (int64_t)batch * kIn) || shares(out, batch, params, kParams);
+  const ens_status rc = forward_pass(params, batch, xi, w, out, in_place ? w.dy : nullptr, stream);
+  if (rc != ENS_OK) return rc;
   ENS_LAUNCH_CHECK();
   return ENS_OK;
 }
@@ -506,9 +523,17 @@ ens_status ens_mlp_grad(const float* params, int32_t batch, const float* xi, con
   MlpWork w;
   mlp_layout(batch, &w, (char*)workspace);
   weights_bf16(params, w, stream);
-  rows_pass(params, batch, xi, target, nullptr, w, out, stream);
+  // (out in the place of target itself: each lane reads a target before it
+  // writes there)
+  const bool in_place = out && (shares(out, batch, xi, (int64_t)batch * kIn) || shares(out, batch, params, kParams) ||
+                                (out != target && shares(out, batch, target, (int64_t)batch * kOut)));
+  rows_pass(params, batch, xi, target, nullptr, w, in_place ? nullptr : out, stream);
   hipLaunchKernelGGL(k_mlp_update<false>, dim3(kUpdateBlocks), dim3(256), 0, stream, batch, w, (float*)nullptr,
                      (float*)nullptr, (float*)nullptr, AdamStep{}, grad, loss);
+  if (in_place) {  // a forward pass of its own; the update is done with dz1
+    const ens_status rc = forward_pass(params, batch, xi, w, out, w.dz1, stream);
+    if (rc != ENS_OK) return rc;
+  }
   ENS_LAUNCH_CHECK();
   return ENS_OK;
 }
