@@ -845,8 +845,13 @@ __global__ __launch_bounds__(256) void k_kl_extrema(int N, const double* __restr
     lo += kappa0;  // (every workgroup has a line, so both are a point's)
     hi += kappa0;
     bad |= (lo != lo) | (hi != hi);
-    atomicMin(klo + e, bad ? kExtNanLo : ext_key(lo));
-    atomicMax(khi + e, bad ? kExtNanHi : ext_key(hi));
+    if (gridDim.x == 1) {  // a sample's only workgroup: the values themselves
+      ((double*)klo)[e] = bad ? NAN : lo;
+      ((double*)khi)[e] = bad ? NAN : hi;
+    } else {
+      atomicMin(klo + e, bad ? kExtNanLo : ext_key(lo));
+      atomicMax(khi + e, bad ? kExtNanHi : ext_key(hi));
+    }
   }
 }
 
@@ -1027,20 +1032,25 @@ extern "C" ens_status ens_kl_extrema(int32_t N, const void* kl, const ens_proble
   const int32_t* tr = nullptr;
   kl_parts(kl, prob->M, &sq, &tr, &phi);
   // enough workgroups a sample to fill the chip eight times over (or all of
-  // its lines at once); the second grid dimension holds up to 65535 samples
+  // its lines at once); the second grid dimension holds up to 65535 samples.
+  // A sample of up to 1024 lines (16^3) has one, which needs no keys: one launch
+  // instead of three, 10.4 us against 15.7 (20^3, in four more rounds, 16.2 both
+  // ways).
   const int64_t lines = 4 * (int64_t)N * N, most = (lines + 255) / 256;
   int64_t per = (2048 + s - 1) / s;
   if (per > most) per = most;
+  if (lines <= 1024) per = 1;
   const unsigned sb = (unsigned)(((int64_t)s + 255) / 256);
-  hipLaunchKernelGGL(k_kl_extrema_keys, dim3(sb), dim3(256), 0, stream, (int64_t)s, (unsigned long long*)kmin,
-                     (unsigned long long*)kmax);
+  if (per > 1)
+    hipLaunchKernelGGL(k_kl_extrema_keys, dim3(sb), dim3(256), 0, stream, (int64_t)s, (unsigned long long*)kmin,
+                       (unsigned long long*)kmax);
   for (int64_t e0 = 0; e0 < s; e0 += 65535) {
     const int64_t ne = s - e0 < 65535 ? s - e0 : 65535;
     hipLaunchKernelGGL(k_kl_extrema, dim3((unsigned)per, (unsigned)ne), dim3(256), 0, stream, N, sq, tr, phi, prob->M,
                        prob->kappa0, prob->sigma, xi + e0 * prob->M, (unsigned long long*)kmin + e0,
                        (unsigned long long*)kmax + e0);
   }
-  hipLaunchKernelGGL(k_kl_extrema_values, dim3(sb), dim3(256), 0, stream, (int64_t)s, kmin, kmax);
+  if (per > 1) hipLaunchKernelGGL(k_kl_extrema_values, dim3(sb), dim3(256), 0, stream, (int64_t)s, kmin, kmax);
   ENS_LAUNCH_CHECK();
   return ENS_OK;
 }
