@@ -208,8 +208,10 @@ ens_status ens_nl_assemble(int32_t N, const ens_graph* graph, const void* kl, co
 /* ----------------------------------------------------------------- SpMV */
 
 /* Ensemble CRS product y = A x in the commuted layout (Fig.
- * "ensemble_crs"): y[i][e] = sum_k values[k][e] x[col_idx[k]][e], entries
- * summed in ascending k.  values [nnz][s], x and y [n][s] (device) of the
+ * "ensemble_crs"): y[i][e] = sum_k values[k][e] x[col_idx[k]][e], each row's
+ * entries summed in a fixed order that depends on s, the dtype and nnz (one
+ * running sum in ascending k, or 2, 4 or 8 of every 2nd, 4th or 8th entry that are
+ * then added in pairs).  values [nnz][s], x and y [n][s] (device) of the
  * dtype given; y must not overlap x or values.  Never synchronises. */
 ens_status ens_spmv(const ens_graph* graph, int32_t s, ens_dtype dtype, const void* values,
                     const void* x, void* y, hipStream_t stream);
@@ -675,7 +677,7 @@ ens_status ens_mlp_train(float* params, float* adam_m, float* adam_v, int32_t st
                          float lr, float* loss, void* workspace, size_t ws_bytes, hipStream_t stream);
 
 /* One Adam step (Kingma and Ba, ICLR 2015, Algorithm 1; the optimiser of
- * ens_mlp_train, which runs this same kernel after each gradient) on `count`
+ * ens_mlp_train, which takes the same step, bitwise, beside each gradient) on `count`
  * FP32 elements (device): with b1 = 0.9, b2 = 0.999, eps = 1e-8 and t = step
  * (1-based, the bias correction),
  *   m = b1 m + (1 - b1) g;  v = b2 v + (1 - b2) g^2;

@@ -16,16 +16,19 @@
 //   B: r -= alpha q, z = D^-1 r, partials of r.z and r.r
 //                                                      -> masks, beta_e, rho_e
 //   C: x += alpha p, p = z + beta p
+// In FP64 systems of up to kFusedValues the reductions move into B and C, whose
+// workgroups each sum the partials before them (cg_iteration_fused).
 // Reductions are deterministic: wave butterflies between lanes holding the
 // same samples, a fixed-order LDS sum per block, then the block partials are
 // summed by a striped first stage and a one-block final stage, each in a
-// fixed order, and the final stage updates the per-sample scalars and the
-// count of active samples.  Producing kernels publish their partials by
+// fixed order; the final stage also updates the per-sample control block
+// (Ctl), so all control flow is device side and visibility comes from kernels
 // ending (no device-scope fences inside kernels: on this part a fence
 // writes back and invalidates the XCD's L2, which costs more than the
-// launch it saves).  Every kernel of the iteration returns immediately when
-// no sample is active (C: when none took a step), and the host reads the count once per chunk of
-// iterations, so the loop ends on the device.
+// launch it saves).  Every kernel of an iteration returns at once when no
+// sample is active (C: when none took a step; the fused B and C after they have
+// read the control block and the partials), and the host reads the count once
+// per chunk of iterations, so the loop ends on the device.
 #include <stddef.h>
 #include <string.h>
 

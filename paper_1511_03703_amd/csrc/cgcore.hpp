@@ -33,7 +33,7 @@ struct Ctl {
   int32_t n_step;  // samples that take a step
   int32_t xnz;  // set when the initial guess has a nonzero entry
   float ratio[kMaxS];  // |r|^2 / tol^2
-  double spare;
+  double padding;  // (the block keeps its size)
   double tot[2 * kMaxS];
 };
 static_assert(sizeof(Ctl) == 3376, "workspaces keep their sizes");
@@ -481,7 +481,7 @@ __device__ inline void update_body(int64_t nchunks, const T* __restrict__ q, T* 
 // p = D^-1 r + beta p for those still active, chunk block `blk`; state() as in
 // update_body.  Here, and not beside r -= alpha q, because p is read here
 // anyway: 10 passes over vectors an iteration instead of 11 (a batch of 8 groups,
-// meshes 32 to 96, s = 16: 283 -> 277 ms; beside a multigrid cycle, 8 instead of
+// meshes 32 to 96, s = 16, timed in turn: 289.7 -> 283.9 ms; beside a multigrid cycle, 8 instead of
 // 9, it measured no gain at 64^3, s = 16 and 128^3, s = 32, and x moves with r).
 template <typename T, int S, typename State>
 __device__ inline void pupdate_body(int64_t nchunks, T* __restrict__ x, const T* __restrict__ r,

@@ -4,8 +4,10 @@
 //   snapshots S [n][m] (one column per solved sample)
 //   G = S^T S [m][m]                         (FP64 matrix cores, half of the symmetric product, split K)
 //   top-r eigenpairs of G by block subspace iteration with a seeded start
-//   block, Gram-Schmidt (twice), and a final Rayleigh-Ritz step whose k x k
-//   eigenproblem is solved by cyclic Jacobi in one workgroup
+//   block, orthonormalised between its steps (by a Cholesky factor, else by block
+//   Gram-Schmidt), and a final Rayleigh-Ritz step after two rounds of block
+//   Gram-Schmidt, whose k x k eigenproblem is solved by Jacobi rotations in
+//   round-robin order in one workgroup
 //   Phi = S V_r diag(lambda_r)^(-1/2) [n][r], each column's largest-magnitude
 //   entry made positive
 //   coefficients C = X^T Phi and reconstruction x0 = Phi c in the ensemble
@@ -196,8 +198,8 @@ __global__ __launch_bounds__(256) void k_sum_slices_sym(int64_t m, int nz, const
 // leaves the columns orthonormal to rounding (the second round finds them so
 // to about 1e-11 and cleans up).  Between two power steps a basis that close
 // to orthonormal does as well, so there (`once`) the second round is left out
-// for a panel whose columns kept at least 1 % of their length in the first.  One workgroup of 16 wavefronts does it all:
-// the time is a chain of reductions over m, and Y (1 MB for 2048 x 64) stays
+// for a panel whose columns kept at least 1 % of their length in the first.  One
+// workgroup of 8 wavefronts does it all: the time is a chain of reductions over m, and Y (1 MB for 2048 x 64) stays
 // in L2.  Projections, panel Gram matrices and the updates are 16 x 16 tiles
 // on the FP64 matrix cores, whose reads of Y are whole 128-byte pieces of
 // rows; the columns one at a time, each product a strided pass, took 11.1 ms
@@ -716,8 +718,10 @@ __global__ __launch_bounds__(256) void k_reconstruct(int64_t n, int r, int s, co
 // are free to choose, and with k = 32 c + 8 (lane / 16) + t a lane's operands
 // are 8 consecutive entries of one row of Phi (four 16-byte loads, every
 // 64-byte piece of the row used whole).  The coefficients lie in LDS in the
-// order the lanes take them.  Measured at 64^3, r = s = 32: 27.2 us (5.2 TB/s),
-// against 479 us for the lane-per-entry form with its bank conflicts.
+// order the lanes take them.  Measured at 64^3, r = s = 32, where Phi and x0
+// (141 MB) fit the last-level cache: 26 us from there (5.4 TB/s), 32 us where the
+// buffers change from call to call and come from memory (4.4 TB/s), against 475 us
+// both ways for the lane-per-entry form with its bank conflicts.
 // MFMA layout: lane l holds A[l%16][l/16] and B[l/16][l%16]; the result
 // leaves D[l/16 + 4 i][l%16], i = 0..3.
 constexpr int kRecMaxR = 256;  // 64 KB of coefficients in LDS
