@@ -63,7 +63,7 @@ def test_gram_and_projection(E, n, m):
             assert call(ws, least * slice_ - 1) == E.ENS_E_NOMEM
 
 
-@pytest.mark.parametrize("m,k", [(40, 12), (600, 40), (600, 100)])
+@pytest.mark.parametrize("m,k", [(40, 12), (600, 40), (300, 64), (600, 96), (600, 97)])
 def test_eigenpairs(E, m, k):
     # a spectrum that falls by half an index: 20 steps leave the first 4 pairs
     # to 2^(-20 (k - 3)) of their size, under rounding
