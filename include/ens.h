@@ -22,6 +22,10 @@
  *     points that return results on the host (ens_cg, ens_scalar_cg,
  *     ens_solve_batch) synchronise that stream before returning; the others
  *     never synchronise.
+ *   - Calls on several threads may overlap, each with its own stream, buffers
+ *     and workspace.  On one device the batched solves (the autotuner's too)
+ *     and the concurrent baseline take turns; ens_cg_noalloc is the caller's to
+ *     serialise, and so are calls on one hierarchy (ens_mg).
  *   - Errors are reported by the return value, never by aborting: arguments
  *     are validated on the host before any launch (ENS_E_ARG,
  *     ENS_E_UNSUPPORTED, ENS_E_RANGE); HIP failures return ENS_E_HIP.  A

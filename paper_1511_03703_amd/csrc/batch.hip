@@ -419,6 +419,7 @@ static ens_status solve_batch(const ens_group* groups, int ng, const ens_batch_o
     set_error("device context unavailable");
     return ENS_E_HIP;
   }
+  std::lock_guard<std::mutex> turn(cx->work_mu);
   // all work runs on the library's own stream, ordered after and before the
   // caller's stream by events (graph capture needs a non-default stream)
   hipStream_t st = cx->work_stream;

@@ -901,6 +901,8 @@ static ens_status cg_scalar_concurrent(const ens_graph* g, int s, const double* 
                                        const ens_cg_opts& o, int ns, char* ws, size_t slice, ens_cg_stat* stats,
                                        hipStream_t user) {
   DeviceCtx* cx = device_ctx();
+  std::unique_lock<std::mutex> turn;
+  if (cx) turn = std::unique_lock<std::mutex>(cx->work_mu);
   if (!cx || !ensure_side_streams(cx, ns)) {
     set_error("could not create the side streams");
     return ENS_E_HIP;

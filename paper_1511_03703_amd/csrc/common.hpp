@@ -7,6 +7,7 @@
 // entry are spread over L = s/V consecutive lanes of a 64-wide wavefront.
 #pragma once
 
+#include <mutex>
 #include <vector>
 
 #include <hip/hip_runtime.h>
@@ -95,6 +96,9 @@ struct DeviceCtx {
   // created on first use, with one event each to join the caller's stream
   std::vector<hipStream_t> side;
   std::vector<hipEvent_t> side_ev;
+  // held by a call that works on the streams and events above (a batch, the
+  // concurrent baseline): such calls take turns on a device
+  std::mutex work_mu;
 };
 DeviceCtx* device_ctx();
 
